@@ -848,7 +848,9 @@ __global__ void __launch_bounds__(kWG) paper_kernel(PaperArgs a, const T *__rest
         acc[0] += c;
         acc[1] += c * c;
     }
-    group_sum<2>(acc, s_red);
+    const double at = group_sum<2>(acc, s_red, threadIdx.x);
+    acc[0] = readlane_f64(at, 0);
+    acc[1] = readlane_f64(at, 1);
     if (threadIdx.x == 0) {
         double *dst = a.part + (size_t)blockIdx.x * kPartStride;
         dst[0] = acc[0];

@@ -319,18 +319,14 @@ __device__ __forceinline__ void sweep_terminal(const SweepArgs &a, const T *__re
     }
 }
 
-// The solve of date k by thread 0 (registers where the kernel has room,
-// else LDS), and group 0's date record: coefficients, flag and count, the
-// moments, and device clock stamps of the date's phases.
+// The solve of a date by thread 0 (registers where the kernel has room,
+// else LDS).
 // MODE 0: totals and factor in registers; 1: factor in LDS (the compiler may
 // still keep it in registers).
 template <int D, int MODE>
-__device__ __forceinline__ void solve_and_record(const SweepArgs &a, uint32_t gid, int k, const double *s_tot,
-                                                 double *s_beta, double (*s_L)[8], double *s_w,
-                                                 const uint64_t (&stamp)[3])
+__device__ __forceinline__ void solve_thread(const double *s_tot, double *s_beta, double (*s_L)[8], double *s_w)
 {
     constexpr int NV = 3 * D + 4;
-    const uint64_t c_all = __builtin_amdgcn_s_memrealtime();
     if constexpr (MODE == 0) {
         // the totals in registers first: every LDS read issued at once
         double tr[NV], Lr[8][8], wr[32];
@@ -340,26 +336,32 @@ __device__ __forceinline__ void solve_and_record(const SweepArgs &a, uint32_t gi
     } else {
         solve_date<D>(s_tot, s_beta, s_L, s_w);
     }
-    if (gid == 0) {
-        // every group solved the same system; group 0 keeps the record
-        double *rec = a.rec + (size_t)k * kRec;
-#pragma unroll
-        for (int q = 0; q < 10; ++q) rec[q] = s_beta[q];
-        for (int q = 0; q < NV && q < 22; ++q) rec[10 + q] = s_tot[q];
-        rec[kRecTime + 0] = (double)stamp[0];                             // moments summed in the group
-        rec[kRecTime + 1] = (double)c_all;                                // device-wide totals in hand
-        rec[kRecTime + 2] = (double)__builtin_amdgcn_s_memrealtime();     // solved
-        rec[kRecTime + 3] = (double)stamp[1];                             // next date's Gram part summed
-        rec[kRecTime + 4] = (double)stamp[2];                             // date's pass started
-    }
 }
 
-__device__ __forceinline__ double readlane_f64(double x, int l)
+// Device clock for group 0's date records (0 elsewhere: no other group pays
+// for the read).
+__device__ __forceinline__ uint64_t record_clock(uint32_t gid) { return gid == 0 ? __builtin_amdgcn_s_memrealtime() : 0ull; }
+
+// Group 0's record of date k (every group solved the same system):
+// coefficients, flag and count, the moments, and device clock stamps of the
+// date's phases, by one wave in one store, after the barrier that hands the
+// coefficients out (off the way to it).  s_clk: LDS, [0] totals in hand, [1]
+// solved (the solving wave's); stamp: moments summed in the group, next
+// date's Gram part summed, date's pass started.
+template <int D>
+__device__ __forceinline__ void record_date(const SweepArgs &a, int k, const double *s_tot, const double *s_beta,
+                                            const uint64_t *s_clk, const uint64_t (&stamp)[3])
 {
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, l);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), l);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    constexpr int NV = 3 * D + 4, NT = NV < 22 ? NV : 22;
+    const int lane = tid_x() & 63;
+    double v = 0.0;
+    if (lane < 10 + NT) v = lane < 10 ? s_beta[lane < 10 ? lane : 0] : s_tot[lane - 10];
+    if (lane == kRecTime + 0) v = (double)stamp[0];
+    if (lane == kRecTime + 1) v = (double)s_clk[0];
+    if (lane == kRecTime + 2) v = (double)s_clk[1];
+    if (lane == kRecTime + 3) v = (double)stamp[1];
+    if (lane == kRecTime + 4) v = (double)stamp[2];
+    if (lane < 10 + NT || (lane >= kRecTime && lane < kRecTime + 5)) a.rec[(size_t)k * kRec + lane] = v;
 }
 
 // The same solve as solve_date (equilibration by the diagonal, Cholesky with
@@ -435,28 +437,6 @@ __device__ __forceinline__ void solve_date_wave(const double *tot, double *beta,
     }
 }
 
-// The wave-parallel solve of date k by wave 0 and group 0's date record, as
-// solve_and_record.  Call with every lane of wave 0.
-template <int D>
-__device__ __forceinline__ void solve_and_record_wave(const SweepArgs &a, uint32_t gid, int k, const double *s_tot,
-                                                      double *s_beta, double (*s_col)[8], const uint64_t (&stamp)[3])
-{
-    constexpr int NV = 3 * D + 4;
-    const uint64_t c_all = __builtin_amdgcn_s_memrealtime();
-    solve_date_wave<D>(s_tot, s_beta, s_col);
-    if (gid == 0 && tid_x() == 0) {
-        double *rec = a.rec + (size_t)k * kRec;
-#pragma unroll
-        for (int q = 0; q < 10; ++q) rec[q] = s_beta[q];
-        for (int q = 0; q < NV && q < 22; ++q) rec[10 + q] = s_tot[q];
-        rec[kRecTime + 0] = (double)stamp[0];
-        rec[kRecTime + 1] = (double)c_all;
-        rec[kRecTime + 2] = (double)__builtin_amdgcn_s_memrealtime();
-        rec[kRecTime + 3] = (double)stamp[1];
-        rec[kRecTime + 4] = (double)stamp[2];
-    }
-}
-
 // Register-resident tile (KEEP): the date's path values stay in registers
 // across the device-wide sum.  The Gram part of the next date's moments
 // depends only on that date's path values, so it is formed while this
@@ -471,7 +451,8 @@ template <typename T, int PPT, int D, bool LAG, int WG>
 __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restrict__ S, uint32_t gid,
                                            const TileIO<T, PPT, WG> &io, T (&pv)[PPT], uint32_t &epoch, bool &alive,
                                            double (*s_red)[32], double (*s_red2)[32], double *s_tot,
-                                           double *s_beta, double *s_wl, double *s_x, int *s_flag)
+                                           double *s_beta, double *s_wl, double *s_x, int *s_flag, uint64_t *s_clk,
+                                           uint32_t &skipped)
 {
     using SH = SweepShape<T, PPT>;
     constexpr int VW = SH::VW, NVEC = SH::NVEC;
@@ -500,15 +481,18 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
 
     // Gram part of date k's moments from its path values v, pairs of paths
     // into two accumulator sets (independent chains), pinned per pair; the
-    // in-the-money count from wave ballots (scalar unit); result (group
-    // total) valid in thread 0
+    // in-the-money count from wave ballots (scalar unit); returns the group's
+    // totals in the first wave's lanes at their words of the row (Gram sums
+    // 0..NA-1, count NV-1)
+    const uint32_t cg = tid == NV - 1 ? (uint32_t)NA : tid < NA ? (uint32_t)tid : (uint32_t)NG;
+    const uint32_t cr = tid >= NA ? (uint32_t)(tid - NA) : (uint32_t)NB;   // right-hand side: words NA..NA+NB-1
     // kCacheY: the Gram pass also keeps each path's right-hand-side factors
     // y_q (q <= D) in registers, so the right-hand-side pass after the update
     // is one fma per sum (512-thread binary32 tiles, which have the room)
     constexpr bool kCacheY = WG == 512 && sizeof(T) == 4 && PPT * NB <= 32;
     double ys[kCacheY ? PPT : 1][NB];
-    auto gram_pass = [&](const Vec<T>(&v)[NVEC], double xa, double xb, double *wl, double (&g)[NG]) {
-        double g2[NA];
+    auto gram_pass = [&](const Vec<T>(&v)[NVEC], double xa, double xb, double *wl) -> double {
+        double g[NG], g2[NA];
 #pragma unroll
         for (int q = 0; q < NA; ++q) g[q] = g2[q] = 0.0;
         uint32_t cnt = 0;
@@ -533,8 +517,8 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
 #pragma unroll
         for (int q = 0; q < NA; ++q) g[q] += g2[q];
         g[NA] = (double)cnt;
-        if constexpr (WG == 512 && NA <= 8) group_sum_lds<NG, 1, WG>(g, s_x, s_red2);
-        else group_sum<NG, 1, WG>(g, s_red2);
+        if constexpr (WG == 512 && NA <= 8) return group_sum_lds<NG, 1, WG>(g, s_x, s_red2, cg);
+        else return group_sum<NG, 1, WG>(g, s_red2, cg);
     };
 
     if (!(a.allow_exercise && M >= 2)) return;
@@ -559,12 +543,11 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
     };
     prefetch(M - 2);
     double xa = uniform_f64(dcc[1]), xb = uniform_f64(dcc[2]), dk = uniform_f64(dcc[0]);
-    double gt[NG];
-    gram_pass(sc, xa, xb, wbuf(M - 1), gt);
+    double gt = gram_pass(sc, xa, xb, wbuf(M - 1));
 
     for (int k = M - 1; k >= 1; --k) {
         uint64_t stamp[3];
-        stamp[2] = __builtin_amdgcn_s_memrealtime();
+        stamp[2] = record_clock(gid);
         double rs[NB];
         {
             double r2[NB];
@@ -602,18 +585,13 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
 #pragma unroll
             for (int q = 0; q < NB; ++q) rs[q] += r2[q];
         }
-        if constexpr (WG == 512) group_sum_lds<NB, 0, WG>(rs, s_x, s_red);
-        else group_sum<NB, 0, WG>(rs, s_red);
+        double rt;
+        if constexpr (WG == 512) rt = group_sum_lds<NB, 0, WG>(rs, s_x, s_red, cr);
+        else rt = group_sum<NB, 0, WG>(rs, s_red, cr);
         ++epoch;
-        stamp[0] = __builtin_amdgcn_s_memrealtime();
-        double acc[NV];
-#pragma unroll
-        for (int q = 0; q < NA; ++q) acc[q] = gt[q];
-#pragma unroll
-        for (int q = 0; q < NB; ++q) acc[NA + q] = rs[q];
-        acc[NV - 1] = gt[NA];
-        if (!allreduce_publish<NV, RW, WG>(acc, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
-                                       s_flag)) {
+        stamp[0] = record_clock(gid);
+        if (!allreduce_publish<NV, RW, WG>(cr < (uint32_t)NB ? rt : gt, gid, G, a.rows, a.sync, a.err, epoch,
+                                           a.spin_limit, s_tot, s_red, s_flag)) {
             alive = false;
             return;
         }
@@ -629,17 +607,26 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
             dkn = uniform_f64(dcp[0]);
         }
         prefetch(k - 2);
-        if (k >= 2) gram_pass(sn, xan, xbn, wbuf(k - 1), gt);
-        stamp[1] = __builtin_amdgcn_s_memrealtime();
+        if (k >= 2) gt = gram_pass(sn, xan, xbn, wbuf(k - 1));
+        stamp[1] = record_clock(gid);
 
-        if (!allreduce_gather<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag,
-                                          k >= 2)) {
+        if (!gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, k >= 2,
+                                          [&]() {
+                                              const uint64_t c0 = record_clock(gid);
+                                              if (tid == 0) {
+                                                  solve_thread<D, 0>(s_tot, s_beta, nullptr, nullptr);
+                                                  if (gid == 0) {
+                                                      s_clk[0] = c0;
+                                                      s_clk[1] = __builtin_amdgcn_s_memrealtime();
+                                                  }
+                                              }
+                                          })) {
             alive = false;
             return;
         }
-        if (tid == 0) solve_and_record<D, 0>(a, gid, k, s_tot, s_beta, nullptr, nullptr, stamp);
-        __syncthreads();
+        if (gid == 0 && tid >= WG - 64) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
 
+        skipped += s_beta[8] == 0.0 ? 1u : 0u;
         if (s_beta[8] != 0.0) {
             double gam[P];
 #pragma unroll
@@ -659,7 +646,9 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         xa = xan;
         xb = xbn;
         dk = dkn;
-        __syncthreads();   // s_beta reuse
+        // (s_beta, s_tot and the outcome flag are next written after the next
+        // date's in-group sum, whose barriers every wave passes only after
+        // reading them here)
     }
 }
 
@@ -670,7 +659,8 @@ template <typename T, int PPT, int D, bool LAG, int WG>
 __device__ __forceinline__ void sweep_stream(const SweepArgs &a, const T *__restrict__ S, uint32_t gid,
                                              const TileIO<T, PPT, WG> &io, T (&pv)[PPT], uint32_t &epoch, bool &alive,
                                              double (*s_red)[32], double *s_tot, double *s_beta, double (*s_L)[8],
-                                             double *s_w, DateConst *s_dc, Vec<T> *s_keep, int *s_flag)
+                                             double *s_w, DateConst *s_dc, Vec<T> *s_keep, int *s_flag,
+                                             uint64_t *s_clk, uint32_t &skipped)
 {
     constexpr int NK = stream_keep_vecs<T, PPT, WG, LAG>();
     using SH = SweepShape<T, PPT>;
@@ -694,7 +684,7 @@ __device__ __forceinline__ void sweep_stream(const SweepArgs &a, const T *__rest
                      dk = uniform_f64(s_dc[k].disc);
         const T *row = S + (size_t)(k - 1) * ld;
         uint64_t stamp[3];
-        stamp[2] = __builtin_amdgcn_s_memrealtime();
+        stamp[2] = record_clock(gid);
 
         double acc[NV];
 #pragma unroll
@@ -719,17 +709,29 @@ __device__ __forceinline__ void sweep_stream(const SweepArgs &a, const T *__rest
         }
         acc[NV - 1] = (double)cnt;
 
-        group_sum<NV, 0, WG>(acc, s_red);
+        const double at = group_sum<NV, 0, WG>(acc, s_red, (uint32_t)tid);
         ++epoch;
         // (a clock read before group_sum would pin the moment pass's schedule)
-        stamp[0] = stamp[1] = __builtin_amdgcn_s_memrealtime();
-        if (!allreduce<NV, RW, WG>(acc, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag)) {
+        stamp[0] = stamp[1] = record_clock(gid);
+        if (!allreduce_publish<NV, RW, WG>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+                                           s_flag) ||
+            !gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+                                          [&]() {
+                                              const uint64_t c0 = record_clock(gid);
+                                              if (tid == 0) {
+                                                  solve_thread<D, 1>(s_tot, s_beta, s_L, s_w);
+                                                  if (gid == 0) {
+                                                      s_clk[0] = c0;
+                                                      s_clk[1] = __builtin_amdgcn_s_memrealtime();
+                                                  }
+                                              }
+                                          })) {
             alive = false;
             return;
         }
-        if (tid == 0) solve_and_record<D, 1>(a, gid, k, s_tot, s_beta, s_L, s_w, stamp);
-        __syncthreads();
+        if (gid == 0 && tid >= WG - 64) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
 
+        skipped += s_beta[8] == 0.0 ? 1u : 0u;
         if (s_beta[8] != 0.0) {
             double gam[P];
 #pragma unroll
@@ -759,7 +761,8 @@ __device__ __forceinline__ void sweep_stream(const SweepArgs &a, const T *__rest
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        __syncthreads();   // s_beta reuse
+        // (s_beta and s_tot are next written after the next date's in-group
+        // sum, as in sweep_keep)
     }
 }
 
@@ -951,7 +954,7 @@ template <int PPT, int D, bool CALL>
 __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *__restrict__ S, uint32_t gid,
                                                const TileIO<float, PPT, 512> &io, float (&pv)[PPT], uint32_t &epoch,
                                                bool &alive, double (*s_red)[32], double *s_tot, double *s_beta,
-                                               double (*s_L)[8], double *s_w, int *s_flag)
+                                               double (*s_L)[8], int *s_flag, uint64_t *s_clk, uint32_t &skipped)
 {
     constexpr int WG = 512;
     using RS = Resident<float, PPT, WG, false>;
@@ -1035,7 +1038,7 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
         asm volatile("" : "+v"(xb));
         const DC dcn = dconst(k >= 2 ? k - 1 : 1);
         uint64_t stamp[3];
-        stamp[2] = __builtin_amdgcn_s_memrealtime();
+        stamp[2] = record_clock(gid);
         const float *row = S + (size_t)(k - 1) * ld;
 
         // moment pass.  tv is the row the device-wide sum takes: [count,
@@ -1083,20 +1086,30 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
             for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(kr[jj].v[e]));
         tv[0] = 0.0;
         tv[NV - 1] = (double)cnt;   // wave-uniform: summed over the waves only
-        group_sum<NV, 1, WG>(tv, s_red);
-        tv[0] = tv[NV - 1];
+        // word 0 of the row is the count too (the Gram sum of q = 0)
+        const double at = group_sum<NV, 1, WG>(tv, s_red, tid == 0 ? (uint32_t)NV - 1u : (uint32_t)tid);
         ++epoch;
-        stamp[0] = stamp[1] = __builtin_amdgcn_s_memrealtime();
-        if (!allreduce<NV, RW, WG>(tv, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag)) {
+        stamp[0] = stamp[1] = record_clock(gid);
+        if (!allreduce_publish<NV, RW, WG>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+                                           s_flag) ||
+            !gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+                                          [&]() {
+                                              const uint64_t c0 = record_clock(gid);
+                                              solve_date_wave<D>(s_tot, s_beta, s_L);
+                                              if (gid == 0 && tid == 0) {
+                                                  s_clk[0] = c0;
+                                                  s_clk[1] = __builtin_amdgcn_s_memrealtime();
+                                              }
+                                          })) {
             alive = false;
             return;
         }
-        if (wave == 0) solve_and_record_wave<D>(a, gid, k, s_tot, s_beta, s_L, stamp);
-        __syncthreads();
+        if (gid == 0 && wave == WG / 64 - 1) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
 
         // a date that allows no exercise runs the same update with a strike
         // threshold no path passes (branch-free: no copies of the cashflows)
         const bool solved = s_beta[8] != 0.0;
+        skipped += solved ? 0u : 1u;
         const float kthr_u = solved ? kthr : (CALL ? __int_as_float(0x7f800000) : __int_as_float(0xff800000));
         double gam[D + 1];
 #pragma unroll
@@ -1134,7 +1147,8 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
             __builtin_amdgcn_sched_barrier(0);
         });
         dcc = dcn;
-        __syncthreads();   // s_beta reuse
+        // (s_beta and s_tot are next written after the next date's in-group
+        // sum, as in sweep_keep)
     }
 }
 
@@ -1158,6 +1172,7 @@ struct SweepLds {
     // moment pass for the update ([vector][thread])
     Vec<T> keep[stream_keep_vecs<T, PPT, WG, LAG>() > 0 ? stream_keep_vecs<T, PPT, WG, LAG>() * WG : 1];
     int flag[2 + WG / 64];
+    uint64_t clk[2];   // group 0's clock stamps: totals in hand, solved
 };
 
 // SIDE: 1 call, 2 put (slab-resident tiles are compiled per payoff side), 0
@@ -1165,19 +1180,19 @@ struct SweepLds {
 template <typename T, int PPT, int D, bool LAG, int WG, int SIDE = 0>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a, const T *__restrict__ S, uint32_t gid,
                                            uint32_t e0, T (&pv)[PPT], uint32_t &epoch, bool &alive,
-                                           SweepLds<T, PPT, LAG, WG> &L)
+                                           uint32_t &skipped, SweepLds<T, PPT, LAG, WG> &L)
 {
     const TileIO<T, PPT, WG> io(gid, e0);
     sweep_terminal<T, PPT, WG>(a, S, io, pv);
     if constexpr (SweepShape<T, PPT>::KEEP) {
         sweep_keep<T, PPT, D, LAG, WG>(a, S, gid, io, pv, epoch, alive, L.red, L.red2, L.tot, L.beta, L.wl, L.x,
-                                       L.flag);
+                                       L.flag, L.clk, skipped);
     } else if constexpr (Resident<T, PPT, WG, LAG>::on) {
         static_assert(SIDE == 1 || SIDE == 2, "slab-resident tiles are compiled per payoff side");
-        sweep_resident<PPT, D, SIDE == 1>(a, S, gid, io, pv, epoch, alive, L.red, L.tot, L.beta, L.L, L.w, L.flag);
+        sweep_resident<PPT, D, SIDE == 1>(a, S, gid, io, pv, epoch, alive, L.red, L.tot, L.beta, L.L, L.flag, L.clk, skipped);
     } else {
         sweep_stream<T, PPT, D, LAG, WG>(a, S, gid, io, pv, epoch, alive, L.red, L.tot, L.beta, L.L, L.w, L.dc,
-                                         L.keep, L.flag);
+                                         L.keep, L.flag, L.clk, skipped);
     }
 }
 
@@ -1195,8 +1210,8 @@ __device__ __forceinline__ double moment_shift(const SweepArgs &a)
 
 template <typename T, int PPT, int D, int WG>
 __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, uint32_t e0,
-                                            const T (&pv)[PPT], uint32_t epoch, double (*s_red)[32],
-                                            double *s_tot, int *s_flag)
+                                            const T (&pv)[PPT], uint32_t epoch, uint32_t skipped,
+                                            double (*s_red)[32], double *s_tot, int *s_flag)
 {
     constexpr int VW = 16 / sizeof(T), NVEC = PPT / VW;
     constexpr uint32_t JS = 64 * VW;
@@ -1218,11 +1233,13 @@ __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, ui
         }
         *reinterpret_cast<Vec<T> *>(pvo + e0 + (uint32_t)jj * JS) = o;
     }
-    group_sum<2, 0, WG>(fin, s_red);
+    const double ft = group_sum<2, 0, WG>(fin, s_red, (uint32_t)tid);
     ++epoch;
     const uint32_t G = (uint32_t)a.G;
-    if (!allreduce<2, row_words(D), WG>(fin, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
-                                    s_flag))
+    if (!allreduce_publish<2, row_words(D), WG>(ft, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+                                                s_flag) ||
+        !gather_and_solve<2, row_words(D), WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag,
+                                               false, []() {}))
         return;
     if (gid == 0) {
         if (tid == 0) {
@@ -1236,14 +1253,11 @@ __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, ui
                 const double h0 = a.is_call ? a.S0 - a.K : a.K - a.S0;
                 if (h0 > mean) { price = h0; se = 0.0; t0 = 1.0; }
             }
-            double skipped = 0.0;
-            if (a.allow_exercise)
-                for (int k = 1; k < a.M; ++k) skipped += a.rec[(size_t)k * kRec + 8] == 0.0 ? 1.0 : 0.0;
             a.result[0] = price;
             a.result[1] = se;
             a.result[2] = mean;
             a.result[3] = t0;
-            a.result[4] = skipped;
+            a.result[4] = (double)skipped;   // dates that allowed no exercise
             a.result[5] = 0.0;
             if (a.rep_out) {
                 // randomised QMC: replicate prices of earlier launches are
@@ -1285,11 +1299,11 @@ sweep_kernel(SweepArgs a, const T *__restrict__ S)
     const uint32_t gid = blockIdx.x;
     const uint32_t e0 = tile_e0<T, PPT, WG>(gid);
     T pv[PPT];
-    uint32_t epoch = 0;
+    uint32_t epoch = 0, skipped = 0;
     bool alive = true;
-    sweep_body<T, PPT, D, LAG, WG, SIDE>(a, S, gid, e0, pv, epoch, alive, L);
+    sweep_body<T, PPT, D, LAG, WG, SIDE>(a, S, gid, e0, pv, epoch, alive, skipped, L);
     if (!alive) return;
-    sweep_final<T, PPT, D, WG>(a, gid, e0, pv, epoch, L.red, L.tot, L.flag);
+    sweep_final<T, PPT, D, WG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
 }
 
 template <typename T, int PPT, int D, bool LAG>
@@ -1333,11 +1347,11 @@ sweep_batch_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
         const uint32_t gid = (uint32_t)(t - o.tile_base);
         const uint32_t e0 = tile_e0<T, PPT, kWG>(gid);
         T pv[PPT];
-        uint32_t epoch = 0;
+        uint32_t epoch = 0, skipped = 0;
         bool alive = true;
-        sweep_body<T, PPT, D, LAG, kWG>(a, (const T *)o.S, gid, e0, pv, epoch, alive, L);
+        sweep_body<T, PPT, D, LAG, kWG>(a, (const T *)o.S, gid, e0, pv, epoch, alive, skipped, L);
         if (!alive) return;
-        sweep_final<T, PPT, D, kWG>(a, gid, e0, pv, epoch, L.red, L.tot, L.flag);
+        sweep_final<T, PPT, D, kWG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
     }
 }
 

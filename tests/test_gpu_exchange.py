@@ -1,0 +1,40 @@
+"""The per-date device-wide sum at the edges of its forms: one wave spinning
+on every group's row (at most 512 row words: 32 groups of 16-word rows, 16 of
+32-word rows), and the arrival counters above."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# f64 tiles of 512 threads x 2 paths: 1024 paths a group
+TILE = 1024
+# The GPU's sums and solve and the oracle's Givens QR round differently (1e-16
+# relative each, amplified by the standardised design's condition number, below
+# 1e4 for these bases): 1e-9 of a price of order 5 leaves two decades.
+TOL = 5e-9
+
+
+@pytest.mark.parametrize("groups,degree", [(1, 2), (4, 2), (5, 3), (16, 4), (17, 2), (32, 4), (33, 2), (1, 5), (8, 5),
+                                           (9, 6), (16, 5), (17, 5)])
+@pytest.mark.parametrize("ragged", [0, 37])
+def test_row_exchange_edges(orc, groups, degree, ragged):
+    import torch
+    import paper_1205_0106_amd as amq
+    assert torch.cuda.is_available()
+    pr = amq.Pricer(0)
+    kw = dict(S0=36.0, K=40.0, r=0.06, sigma=0.2, T=1.0)
+    N, M = groups * TILE - ragged, 6
+    p, b = amq.make_params(**kw), amq.make_basis("monomial", degree)
+    print(f"  exchange: groups={groups} degree={degree} N={N}", flush=True)
+    amq.am_debug_set_sweep_tile(512, 2)
+    try:
+        price, se = pr.price(p, N, M, b, "fp64")
+        again = pr.price(p, N, M, b, "fp64")
+    finally:
+        amq.am_debug_set_sweep_tile(0, 0)
+    assert again == (price, se)
+    want = orc.price_american(**kw, N=N, M=M, kind=orc.MONOMIAL, degree=degree)
+    assert abs(price - want.price) <= TOL
+    # group 0's record: every date solved, stamps in order
+    rec = pr.views(N, M, b, "fp64")["rec"].cpu().numpy()
+    for k in range(1, M):
+        assert rec[k, 8] == 1.0 and 0 < rec[k, 36] <= rec[k, 32] <= rec[k, 33] <= rec[k, 34]
