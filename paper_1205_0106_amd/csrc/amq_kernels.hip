@@ -15,6 +15,7 @@
 
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 namespace amq {
@@ -803,7 +804,7 @@ hipError_t launch_sweep_batch(const BatchOpt *opts, const int32_t *tile_opt, con
 // exercise value and the Black–Scholes value over the last interval dt
 // (eqs. (1)-(5)); going back, c_i = max(h(S_i), exp(-r dt) c_{i+1}); the price
 // is exp(-r dt) times the path mean of c_1 (eq. (6)).  Every path is
-// independent: one thread per path, no device-wide wait.  The paths come from
+// independent: no device-wide wait.  The paths come from
 // the generation kernel run with m dates and horizon m dt.
 // ---------------------------------------------------------------------------
 template <typename T> __device__ __forceinline__ T cnd(T x);
@@ -820,9 +821,18 @@ __device__ __forceinline__ T bs_value(T S, T K, T r, T sig, T tau, bool call)
     return call ? S * cnd<T>(d1) - dk * cnd<T>(d2) : dk * cnd<T>(-d2) - S * cnd<T>(-d1);
 }
 
+// A date of a thread's paths is one 16-byte load (4 binary32 or 2 binary64
+// consecutive paths), kPaperAhead dates requested before the first is used:
+// a path's steps depend only on its running maximum, so the kernel is bound
+// by the loads in flight.  With one path a thread and a load a step, 2^20
+// paths x 100 dates took 238 us (1.8 TB/s) in binary32.
+constexpr int kPaperAhead = 8;
+
 template <typename T>
 __global__ void __launch_bounds__(kWG) paper_kernel(PaperArgs a, const T *__restrict__ S)
 {
+    constexpr int VW = 16 / sizeof(T);
+    struct alignas(16) V { T v[VW]; };
     __shared__ double s_red[kWaves][32];
     __shared__ double s_red8[8][32];
     __shared__ double s_tot[32];
@@ -835,18 +845,46 @@ __global__ void __launch_bounds__(kWG) paper_kernel(PaperArgs a, const T *__rest
     const double h0 = call ? a.S0 - a.K : a.K - a.S0;
     const double csh = h0 > 0.0 ? h0 : 0.0;
     double acc[2] = {0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < a.N; i += (int64_t)gridDim.x * kWG) {
-        T v = T(0);
-        for (int k = a.m; k >= 1; --k) {
-            const T s = S[(size_t)(k - 1) * a.ld + i];
-            T h = call ? s - K : K - s;
-            h = h > T(0) ? h : T(0);
-            const T cont = (k == a.m) ? bs_value<T>(s, K, r, sig, dt, call) : disc * v;
-            v = h > cont ? h : cont;
+    // rows are padded to whole vectors (ld is a multiple of kLdAlign), so a
+    // vector that straddles N reads padding, which is not counted
+    for (int64_t i = ((int64_t)blockIdx.x * kWG + threadIdx.x) * VW; i < a.N; i += (int64_t)gridDim.x * kWG * VW) {
+        T v[VW];
+        const auto step = [&](const V &s, auto last) {
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+                T h = call ? s.v[e] - K : K - s.v[e];
+                h = h > T(0) ? h : T(0);
+                T cont;
+                if constexpr (decltype(last)::value) cont = bs_value<T>(s.v[e], K, r, sig, dt, call);
+                else cont = disc * v[e];
+                v[e] = h > cont ? h : cont;
+            }
+        };
+        const T *col = S + i;
+        const auto load = [&](int k) { return *reinterpret_cast<const V *>(col + (size_t)(k - 1) * a.ld); };
+        V buf[kPaperAhead];
+        int k = a.m - 1;   // dates m-1 .. 1 after the last point's
+#pragma unroll
+        for (int q = 0; q < kPaperAhead; ++q) buf[q] = load(k - q >= 1 ? k - q : 1);
+        step(load(a.m), std::true_type{});
+        for (; k >= kPaperAhead; k -= kPaperAhead) {
+#pragma unroll
+            for (int q = 0; q < kPaperAhead; ++q) {
+                const V s = buf[q];
+                const int kn = k - q - kPaperAhead;
+                buf[q] = load(kn >= 1 ? kn : 1);
+                step(s, std::false_type{});
+            }
         }
-        const double c = (double)disc * (double)v - csh;
-        acc[0] += c;
-        acc[1] += c * c;
+#pragma unroll
+        for (int q = 0; q < kPaperAhead - 1; ++q)
+            if (k - q >= 1) step(buf[q], std::false_type{});
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+            const double c = i + e < a.N ? (double)disc * (double)v[e] - csh : 0.0;
+            acc[0] += c;
+            acc[1] += c * c;
+        }
     }
     const double at = group_sum<2>(acc, s_red, threadIdx.x);
     acc[0] = readlane_f64(at, 0);
@@ -877,7 +915,8 @@ __global__ void __launch_bounds__(kWG) paper_kernel(PaperArgs a, const T *__rest
 
 hipError_t launch_paper(const PaperArgs &a, int fp64, hipStream_t s)
 {
-    int64_t g = (a.N + kWG - 1) / kWG;
+    const int64_t per = (int64_t)kWG * (fp64 ? 2 : 4);   // paths a group takes per pass
+    int64_t g = (a.N + per - 1) / per;
     if (g > kMaxGroups) g = kMaxGroups;
     if (fp64) hipLaunchKernelGGL((paper_kernel<double>), dim3((unsigned)g), dim3(kWG), 0, s, a, (const double *)a.S);
     else      hipLaunchKernelGGL((paper_kernel<float>), dim3((unsigned)g), dim3(kWG), 0, s, a, (const float *)a.S);
