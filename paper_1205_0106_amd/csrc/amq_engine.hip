@@ -134,7 +134,6 @@ std::vector<amq::BridgeNode> make_schedule(int M)
         n.m = m;
         n.dim = dim_of[m];
         n.sl = sl; n.sr = sr; n.dst = dst;
-        n.fm = (float)m;
         if (l == 0 && r == 0) {           // root: W(t_M) = anchor + sqrt(M) z in sqrt(dt) units
             n.wl = 1.0; n.wr = 0.0; n.sd = sqrt((double)M);
         } else {
@@ -143,7 +142,6 @@ std::vector<amq::BridgeNode> make_schedule(int M)
             n.wr = (double)(m - l) / span;
             n.sd = sqrt((double)(m - l) * (double)(r - m) / span);
         }
-        n.fwl = (float)n.wl; n.fwr = (float)n.wr; n.fsd = (float)n.sd;
         out.push_back(n);
     };
     emit(M, 0, 0, amq::kAnchorSlot, 0, 1);
@@ -164,11 +162,78 @@ std::vector<amq::BridgeNode> make_schedule(int M)
     return out;
 }
 
-int max_slot(const std::vector<amq::BridgeNode> &s)
+
+// The schedule's segment forms (see GenNode), packed: variant v holds 2^v
+// segments of len[v] nodes from node off[v].  Variants whose segments would
+// have fewer than kMinSegDates dates of their own are left out (len 0).
+constexpr int kMinSegDates = 8;
+
+struct SegSchedule {
+    int len[amq::kSegVariants] = {0, 0, 0, 0}, off[amq::kSegVariants] = {0, 0, 0, 0};
+    std::vector<amq::GenNode> nodes;
+};
+
+// The packed node of date m between l and r (depth: the interval's level).
+SegSchedule make_segments(int M)
 {
-    int mx = 0;
-    for (auto &n : s) mx = n.dst > mx ? n.dst : mx;
-    return mx;
+    const std::vector<amq::BridgeNode> all = make_schedule(M);
+    std::vector<amq::GenNode> by_date(M + 1);
+    for (const auto &n : all) {
+        amq::GenNode g;
+        g.md = (uint32_t)n.m | (uint32_t)n.dim << 16;
+        g.slots = (uint32_t)n.sl | (uint32_t)n.sr << 8 | (uint32_t)n.dst << 16;
+        g.wl = n.wl; g.wr = n.wr; g.sd = n.sd;
+        by_date[n.m] = g;
+    }
+    SegSchedule S;
+    for (int v = 0; v < amq::kSegVariants; ++v) {
+        if (v > 0 && (M >> v) < kMinSegDates) break;
+        std::vector<std::vector<int>> seg(1 << v);   // dates, in order
+        size_t longest = 0;
+        for (int s = 0; s < 1 << v; ++s) {
+            std::vector<int> &d = seg[s];
+            d.push_back(M);
+            int l = 0, r = M;
+            for (int b = v - 1; b >= 0; --b) {       // the ancestors
+                const int m = (l + r) / 2;
+                d.push_back(m);
+                if ((s >> b) & 1) l = m; else r = m;
+            }
+            // the interval's own nodes, as make_schedule orders them: it emits
+            // every interval's nodes consecutively
+            for (const auto &n : all)
+                if (n.m > l && n.m < r) d.push_back(n.m);
+            longest = d.size() > longest ? d.size() : longest;
+        }
+        S.off[v] = (int)S.nodes.size();
+        S.len[v] = (int)longest;
+        for (auto &d : seg) {
+            for (int m : d) S.nodes.push_back(by_date[m]);
+            for (size_t q = d.size(); q < longest; ++q) S.nodes.push_back(by_date[d.back()]);
+        }
+    }
+    return S;
+}
+
+// Segments of a generation launch.  The longest chain of a wave is its
+// segment's dates: while whole schedules leave fewer than kGenFillWaves waves
+// (16 a CU, what is resident), splitting them puts idle lanes to work at the
+// cost of recomputed ancestors; and a segment's tables must let four groups
+// share a CU's LDS.
+constexpr int64_t kGenFillWaves = 4096;
+constexpr int kMaxSegLen = 280;
+
+// Nodes of the longest of M dates' 2^v segments: an interval of ceil(M / 2^v)
+// dates holds one node less, its ancestors and the root are v + 1 more.
+int seg_len(int M, int v) { return ((M + (1 << v) - 1) >> v) + v; }
+
+int gen_variant(int M, int64_t blocks)
+{
+    int v = 0;
+    while (v + 1 < amq::kSegVariants && (M >> (v + 1)) >= kMinSegDates &&
+           ((blocks << v) < kGenFillWaves || seg_len(M, v) > kMaxSegLen))
+        ++v;
+    return v;
 }
 
 struct Plan { int wg; int ppt; int G; };
@@ -179,7 +244,8 @@ struct DevState {
     uint32_t *d_V = nullptr;
     int vdims = 0;
     std::mutex mu;                                  // schedule and occupancy maps
-    std::map<int, amq::BridgeNode *> sched;
+    struct DevSchedule { SegSchedule seg; amq::GenNode *d = nullptr; };   // seg.nodes live at d
+    std::map<int, DevSchedule> sched;
     std::mutex sync_mu;                             // synchronous entry point's workspace
     hipStream_t stream = nullptr;                   // synchronous entry point
     void *ws = nullptr;
@@ -195,7 +261,7 @@ struct DevState {
     // allocation-free entry point: this device's copy of `scratch` (set by
     // am_init) and host-side bridge schedules for it, built once per date count
     char *scratch = nullptr;
-    std::map<int, std::vector<amq::BridgeNode>> host_sched;
+    std::map<int, SegSchedule> host_sched;
 };
 
 std::mutex g_dev_mu;
@@ -235,21 +301,48 @@ DevState *find_state()
     return it == g_devs.end() ? nullptr : it->second.get();
 }
 
-int get_schedule(DevState *st, int M, const amq::BridgeNode **out)
+int host_schedule(int M, SegSchedule *out)
+{
+    *out = make_segments(M);
+    int mx = 0;
+    for (const auto &n : out->nodes) mx = (int)(n.slots >> 16) > mx ? (int)(n.slots >> 16) : mx;
+    if (mx >= amq::kAnchorSlot)
+        return fail(AM_EDIM, "bridge schedule for %d dates does not fit the register window", M);
+    return AM_OK;
+}
+
+// Built and uploaded once per date count; the entry stays until am_shutdown.
+int get_schedule(DevState *st, int M, const DevState::DevSchedule **out)
 {
     std::lock_guard<std::mutex> lk(st->mu);
     auto it = st->sched.find(M);
-    if (it != st->sched.end()) { *out = it->second; return AM_OK; }
-    std::vector<amq::BridgeNode> h = make_schedule(M);
-    if ((int)h.size() != M || max_slot(h) >= amq::kAnchorSlot)
-        return fail(AM_EDIM, "bridge schedule for %d dates does not fit the register window", M);
-    amq::BridgeNode *d = nullptr;
-    const size_t b = sizeof(amq::BridgeNode) * (size_t)M;
-    if (hipMalloc((void **)&d, b) != hipSuccess) return fail(AM_ENOMEM, "hipMalloc of bridge schedule failed");
-    HIP_TRY(hipMemcpy(d, h.data(), b, hipMemcpyHostToDevice));
-    st->sched[M] = d;
-    *out = d;
+    if (it != st->sched.end()) { *out = &it->second; return AM_OK; }
+    DevState::DevSchedule e;
+    int rc = host_schedule(M, &e.seg);
+    if (rc) return rc;
+    const size_t b = sizeof(amq::GenNode) * e.seg.nodes.size();
+    if (hipMalloc((void **)&e.d, b) != hipSuccess) return fail(AM_ENOMEM, "hipMalloc of bridge schedule failed");
+    HIP_TRY(hipMemcpy(e.d, e.seg.nodes.data(), b, hipMemcpyHostToDevice));
+    *out = &(st->sched[M] = std::move(e));
     return AM_OK;
+}
+
+// Point a generation launch at the schedule's segments and size its waves.
+// base: the device copy of S's nodes (all variants), or of variant `v` alone.
+void set_gen_shape(amq::GenArgs &ga, const SegSchedule &S, int v, const amq::GenNode *seg0, int num_cu)
+{
+    ga.sched = seg0;
+    ga.segs = 1 << v;
+    ga.seg_len = S.len[v];
+    const int64_t target_waves = (int64_t)num_cu * kGenWavesPerCU;
+    const int64_t R = (ga.nblocks * ga.segs + target_waves - 1) / target_waves;
+    ga.R = (int32_t)(R < 1 ? 1 : R);
+}
+
+void set_gen_shape(amq::GenArgs &ga, const DevState::DevSchedule &sc, int num_cu)
+{
+    const int v = ga.what == 0 ? gen_variant(ga.M, (ga.N + 63) / 64) : 0;
+    set_gen_shape(ga, sc.seg, v, sc.d + sc.seg.off[v], num_cu);
 }
 
 int groups_per_cu(DevState *st, int fp64, int laguerre, int wg, int ppt, int degree)
@@ -392,20 +485,21 @@ int prof_slot(ProfRec **out)
 }
 
 // Enqueue both kernels; result stays in the workspace.
-// noalloc_sched: the allocation-free entry point passes the schedule it
-// placed in its scratch memory; then nothing here allocates or creates a
+// noalloc_seg, noalloc_sched: the allocation-free entry point passes the
+// schedule and where in its scratch memory it placed the variant that this
+// launch takes; then nothing here allocates or creates a
 // HIP object (no schedule cache entry, no profiling events, the ordering
 // event made by am_init).
 int enqueue(DevState *st, const am_params *p, int64_t N, int32_t M, am_basis b, int32_t dtype,
             char *ws, const Layout &L, hipStream_t stream, int rep = -1, int n_rep = 0,
-            const amq::BridgeNode *noalloc_sched = nullptr)
+            const SegSchedule *noalloc_seg = nullptr, const amq::GenNode *noalloc_sched = nullptr)
 {
     const int fp64 = dtype == AM_FP64;
     Plan plan;
     int rc = choose_plan(st, N, fp64, b.kind == AM_BASIS_LAGUERRE, b.degree, &plan);
     if (rc) return rc;
-    const amq::BridgeNode *sched = noalloc_sched;
-    if (!sched) {
+    const DevState::DevSchedule *sched = nullptr;
+    if (!noalloc_sched) {
         rc = get_schedule(st, M, &sched);
         if (rc) return rc;
     }
@@ -414,16 +508,16 @@ int enqueue(DevState *st, const am_params *p, int64_t N, int32_t M, am_basis b, 
     memset(&ga, 0, sizeof ga);
     ga.S = ws + L.off_S;
     ga.V = st->d_V;
-    ga.sched = sched;
     ga.datec = (amq::DateConst *)(ws + L.off_datec);
     ga.sync = (uint32_t *)(ws + L.off_result + 64);
     ga.N = N; ga.ld = L.ld;
     ga.nblocks = L.ld / 64;
     ga.M = M;
-    const int64_t target_waves = (int64_t)st->num_cu * kGenWavesPerCU;
-    int64_t R = (ga.nblocks + target_waves - 1) / target_waves;
-    ga.R = (int32_t)(R < 1 ? 1 : R);
     ga.what = 0;
+    if (noalloc_sched)
+        set_gen_shape(ga, *noalloc_seg, gen_variant(M, (N + 63) / 64), noalloc_sched, st->num_cu);
+    else
+        set_gen_shape(ga, *sched, st->num_cu);
     ga.is_call = p->is_call;
     ga.S0 = p->S0; ga.K = p->K; ga.r = p->r; ga.sigma = p->sigma; ga.T = p->T;
     const double dt = p->T / (double)M;
@@ -659,31 +753,35 @@ int am_price_american_noalloc(const am_params *params, int64_t n_paths, int32_t 
     dtype = storage_of(n_paths, dtype);
     const Layout L = make_layout(n_paths, n_dates, dtype);
     // the bridge schedule follows the workspace regions (L.total is 256-aligned)
-    const size_t sched_bytes = sizeof(amq::BridgeNode) * (size_t)n_dates;
+    // (64 bytes a date: every variant's two nodes a date at most)
+    const size_t sched_bytes = 64 * (size_t)n_dates;
     const size_t need = L.total + sched_bytes;
     if (need > (size_t)AM_SCRATCH_BYTES)
         return fail(AM_EWORKSPACE, "%lld paths x %d dates need %zu bytes; the allocation-free entry point "
                     "has %zu", (long long)n_paths, n_dates, need, (size_t)AM_SCRATCH_BYTES);
     DevState *st = find_state();
     if (!st || !st->scratch) return fail(AM_EINVAL, "am_init has not run on this device");
-    const std::vector<amq::BridgeNode> *hs = nullptr;
+    const SegSchedule *hs = nullptr;
     {
         // host copies only (built once per date count, kept for the process)
         std::lock_guard<std::mutex> lk(st->mu);
         auto it = st->host_sched.find(n_dates);
         if (it == st->host_sched.end()) {
-            std::vector<amq::BridgeNode> h = make_schedule(n_dates);
-            if ((int)h.size() != n_dates || max_slot(h) >= amq::kAnchorSlot)
-                return fail(AM_EDIM, "bridge schedule for %d dates does not fit the register window", n_dates);
+            SegSchedule h;
+            rc = host_schedule(n_dates, &h);
+            if (rc) return rc;
             it = st->host_sched.emplace(n_dates, std::move(h)).first;
         }
         hs = &it->second;
     }
     hipStream_t stream = (hipStream_t)hip_stream;
     char *ws = st->scratch;
-    amq::BridgeNode *d_sched = (amq::BridgeNode *)(ws + L.total);
-    HIP_TRY(hipMemcpyAsync(d_sched, hs->data(), sched_bytes, hipMemcpyHostToDevice, stream));
-    rc = enqueue(st, params, n_paths, n_dates, basis, dtype, ws, L, stream, -1, 0, d_sched);
+    amq::GenNode *d_sched = (amq::GenNode *)(ws + L.total);
+    const int v = gen_variant(n_dates, (n_paths + 63) / 64);
+    const size_t vb = sizeof(amq::GenNode) * ((size_t)hs->len[v] << v);
+    if (vb > sched_bytes) return fail(AM_EDIM, "bridge schedule for %d dates does not fit the scratch memory", n_dates);
+    HIP_TRY(hipMemcpyAsync(d_sched, hs->nodes.data() + hs->off[v], vb, hipMemcpyHostToDevice, stream));
+    rc = enqueue(st, params, n_paths, n_dates, basis, dtype, ws, L, stream, -1, 0, hs, d_sched);
     if (rc) return rc;
     // result words and the barrier block's first line, into host stack memory
     double res[16];
@@ -746,7 +844,7 @@ struct BatchPlan {
     std::vector<int32_t> G, tile_base;
     size_t off_part = 0, off_res = 0, off_sync = 0, off_gsync = 0, off_desc = 0, off_tiles = 0,
            off_units = 0, total = 0;
-    int total_tiles = 0, max_M = 0;
+    int total_tiles = 0;
     int64_t total_blocks = 0, max_units = 0;
 };
 
@@ -774,11 +872,10 @@ int batch_plan(const am_option *opts, int32_t n, int32_t dtype, BatchPlan &P)
         P.offPV[i] = (int64_t)o; o = align256(o + (size_t)ld * s);
         P.tile_base[i] = tiles;
         P.total_blocks += ld / 64;
-        P.max_units += (ld / 64 + amq::kWaves - 1) / amq::kWaves;
-        if (opts[i].n_dates > P.max_M) P.max_M = opts[i].n_dates;
     }
     for (int q = 0; q < n; ++q) {
         const int i = P.order[q];
+        P.max_units += (P.ld[i] / 64 + amq::kWaves - 1) / amq::kWaves << gen_variant(opts[i].n_dates, P.total_blocks);
         P.offDatec[i] = o; o = align256(o + (size_t)(opts[i].n_dates + 1) * sizeof(amq::DateConst));
         P.offRec[i] = o;   o = align256(o + (size_t)(opts[i].n_dates + 1) * amq::kRec * 8);
     }
@@ -921,7 +1018,7 @@ int am_price_paper_estimator(const am_params *params, int64_t n_paths, int32_t n
     DevState *st = nullptr;
     rc = get_state(&st);
     if (rc) return rc;
-    const amq::BridgeNode *sched = nullptr;
+    const DevState::DevSchedule *sched = nullptr;
     rc = get_schedule(st, n_points, &sched);
     if (rc) return rc;
     char *ws = (char *)d_workspace;
@@ -932,14 +1029,11 @@ int am_price_paper_estimator(const am_params *params, int64_t n_paths, int32_t n
     memset(&ga, 0, sizeof ga);
     ga.S = ws + L.off_S;
     ga.V = st->d_V;
-    ga.sched = sched;
     ga.datec = (amq::DateConst *)(ws + L.off_datec);
     ga.sync = (uint32_t *)(ws + L.off_result + 64);
     ga.N = n_paths; ga.ld = L.ld; ga.nblocks = L.ld / 64; ga.M = n_points;
-    const int64_t target_waves = (int64_t)st->num_cu * kGenWavesPerCU;
-    int64_t R = (ga.nblocks + target_waves - 1) / target_waves;
-    ga.R = (int32_t)(R < 1 ? 1 : R);
     ga.what = 0;
+    set_gen_shape(ga, *sched, st->num_cu);
     ga.is_call = params->is_call;
     ga.S0 = params->S0; ga.K = params->K; ga.r = params->r; ga.sigma = params->sigma;
     ga.T = dt * (double)n_points;                       // horizon t_m = m dt
@@ -991,21 +1085,25 @@ int enqueue_batch(DevState *st, const am_option *opts, int32_t n_opts, am_basis 
     if (grid_cap > 0 && grid_cap < capacity) capacity = grid_cap;
 
     std::vector<amq::BatchOpt> desc(n_opts);
+    std::vector<int> variant(n_opts);
     std::vector<int32_t> tile_opt;
-    int max_G = 0;
+    int max_G = 0, max_len = 0;
     int tiles = 0;
     size_t rows_off = 0;
     for (int q = 0; q < n_opts; ++q) {
         const int i = P.order[q];
         const am_option &op = opts[i];
-        const amq::BridgeNode *sched = nullptr;
+        const DevState::DevSchedule *sched = nullptr;
         rc = get_schedule(st, op.n_dates, &sched);
         if (rc) return rc;
+        const int v = variant[i] = gen_variant(op.n_dates, P.total_blocks);
         amq::BatchOpt &d = desc[i];
         memset(&d, 0, sizeof d);
         d.S = ws + P.offS[i];
         d.pv = ws + P.offPV[i];
-        d.sched = sched;
+        d.sched = sched->d + sched->seg.off[v];
+        d.seg_len = sched->seg.len[v];
+        if (d.seg_len > max_len) max_len = d.seg_len;
         d.datec = (amq::DateConst *)(ws + P.offDatec[i]);
         d.rec = (double *)(ws + P.offRec[i]);
         d.result = (double *)(ws + P.off_res) + (size_t)i * 8;
@@ -1045,13 +1143,15 @@ int enqueue_batch(DevState *st, const am_option *opts, int32_t n_opts, am_basis 
     for (int q = 0; q < n_opts; ++q) {
         const int i = P.order[q];
         const int64_t nb = P.ld[i] / 64;
-        int64_t R = (wave_work + opts[i].n_dates / 2) / opts[i].n_dates;
+        const int32_t dates = desc[i].seg_len;   // a wave's
+        int64_t R = (wave_work + dates / 2) / dates;
         if (R < 1) R = 1;
-        for (int64_t b = 0; b < nb; b += amq::kWaves * R) {
-            amq::GenUnit u;
-            u.opt = i; u.pad = 0; u.b0 = b; u.b1 = b + amq::kWaves * R < nb ? b + amq::kWaves * R : nb;
-            units.push_back(u);
-        }
+        for (int64_t b = 0; b < nb; b += amq::kWaves * R)
+            for (int sg = 0; sg < 1 << variant[i]; ++sg) {
+                amq::GenUnit u;
+                u.opt = i; u.seg = sg; u.b0 = b; u.b1 = b + amq::kWaves * R < nb ? b + amq::kWaves * R : nb;
+                units.push_back(u);
+            }
     }
     if ((int64_t)units.size() > P.max_units) return fail(AM_EDEVICE, "unit table overflow");
     const size_t bd = desc.size() * sizeof(amq::BatchOpt), bt = tile_opt.size() * 4,
@@ -1077,7 +1177,7 @@ int enqueue_batch(DevState *st, const am_option *opts, int32_t n_opts, am_basis 
     }
     HIP_TRY(amq::launch_generate_batch((const amq::BatchOpt *)(ws + P.off_desc),
                                        (const amq::GenUnit *)(ws + P.off_units), (int)units.size(),
-                                       st->d_V, gsync, P.max_M, fp64, shifts != nullptr, stream));
+                                       st->d_V, gsync, max_len, fp64, shifts != nullptr, stream));
     if (pr) HIP_TRY(hipEventRecord(pr->e[1], stream));
     amq::BatchGlobal g;
     memset(&g, 0, sizeof g);
@@ -1403,7 +1503,7 @@ int am_batch_graph_create(const am_option *opts, int32_t n_opts, am_basis basis,
     rc = get_state(&st);
     if (rc) return rc;
     for (int i = 0; i < n_opts; ++i) {   // schedules are allocated outside the capture
-        const amq::BridgeNode *sc = nullptr;
+        const DevState::DevSchedule *sc = nullptr;
         rc = get_schedule(st, opts[i].n_dates, &sc);
         if (rc) return rc;
     }
@@ -1911,7 +2011,7 @@ int am_shutdown(void)
             // last single-option sweep on any stream
             if (st->stream) (void)hipStreamSynchronize(st->stream);
             if (st->persist_done) (void)hipEventSynchronize(st->persist_done);
-            for (auto &sc : st->sched) (void)hipFree(sc.second);
+            for (auto &sc : st->sched) (void)hipFree(sc.second.d);
             st->sched.clear();
             if (st->d_V) (void)hipFree(st->d_V);
             if (st->ws) (void)hipFree(st->ws);
@@ -1982,7 +2082,7 @@ int am_debug_generate(int32_t what, const am_params *params, int64_t n_paths, in
     DevState *st = nullptr;
     rc = get_state(&st);
     if (rc) return rc;
-    const amq::BridgeNode *sched = nullptr;
+    const DevState::DevSchedule *sched = nullptr;
     rc = get_schedule(st, n_dims, &sched);
     if (rc) return rc;
     const int fp64 = dtype == AM_FP64;
@@ -1997,14 +2097,11 @@ int am_debug_generate(int32_t what, const am_params *params, int64_t n_paths, in
     memset(&ga, 0, sizeof ga);
     ga.S = d;
     ga.V = st->d_V;
-    ga.sched = sched;
     ga.datec = (amq::DateConst *)(d + align256(out_b));
     ga.sync = (uint32_t *)(d + align256(out_b) + align256((size_t)(n_dims + 1) * sizeof(amq::DateConst)));
     ga.N = n_paths; ga.ld = ld; ga.nblocks = (n_paths + 63) / 64; ga.M = n_dims;
-    const int64_t target_waves = (int64_t)st->num_cu * kGenWavesPerCU;
-    int64_t R = (ga.nblocks + target_waves - 1) / target_waves;
-    ga.R = (int32_t)(R < 1 ? 1 : R);
     ga.what = what;
+    set_gen_shape(ga, *sched, st->num_cu);
     ga.S0 = p->S0; ga.K = p->K; ga.r = p->r; ga.sigma = p->sigma; ga.T = p->T;
     const double dt = p->T / (double)n_dims;
     ga.mu = (p->r - 0.5 * p->sigma * p->sigma) * dt;

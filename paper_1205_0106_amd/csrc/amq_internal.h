@@ -8,7 +8,7 @@ namespace amq {
 
 constexpr int kWG = 256;          // threads per workgroup (4 wave64)
 constexpr int kWaves = kWG / 64;
-constexpr int kMaxSlots = 16;     // bridge register window (tree depth + 2; depth <= 10 for 640 dates)
+constexpr int kMaxSlots = 13;     // bridge register window (tree depth + 2 and the anchor; depth <= 10 for 640 dates)
 constexpr int kAnchorSlot = kMaxSlots - 1;   // read by the first bridge node only
 constexpr int kMaxDates = 640;    // on-chip Sobol lane tables (<= 64 KiB of LDS) bound this
 constexpr int kRec = 40;          // doubles per date record
@@ -49,17 +49,29 @@ constexpr int64_t kLdAlign = 32768;
 // a + b t + c W(t): the generation kernels run it on the log-price
 // log S0 + (r - sigma^2/2) t + sigma W(t), with slot 0 = log S0, the anchor
 // = log S0 + (r - sigma^2/2) T and sigma sqrt(dt) z in place of z.
-// Both precisions are stored so each kernel reads one.
-struct alignas(64) BridgeNode {
+struct BridgeNode {
     int32_t m;      // date index 1..M
     int32_t dim;    // Sobol dimension, 0-based
     int32_t sl, sr, dst;
-    float fm;       // m as float
     double wl, wr, sd;
-    float fwl, fwr, fsd;
-    int32_t pad;
 };
-static_assert(sizeof(BridgeNode) == 64, "bridge node is one scalar cache line");
+
+// The node as the generation kernels read it (scalar loads, half a line).
+struct alignas(32) GenNode {
+    uint32_t md;     // m | dim << 16
+    uint32_t slots;  // sl | sr << 8 | dst << 16
+    double wl, wr, sd;
+};
+static_assert(sizeof(GenNode) == 32, "packed bridge node");
+static_assert(kMaxDates < 65536 && kMaxSlots <= 256, "bridge node packing");
+
+// A schedule of M dates in Q = 2^v segments of `len` nodes each, one after
+// another: segment s holds the ancestors of the s-th interval of tree level
+// v (recomputed by every segment below them, to bitwise the same values) and
+// then that interval's nodes in depth-first order; shorter segments repeat
+// their last node, which changes nothing.  A segment's nodes need no others,
+// so segments of one path block run in different waves.
+constexpr int kSegVariants = 4;    // Q = 1, 2, 4, 8
 
 // Per-date constants written by the generation kernel, read by the sweep.
 //   disc = exp(-r t_k); standardised abscissa xs = S * xa + xb with
@@ -72,11 +84,12 @@ struct DateConst {
 struct GenArgs {
     void *S;                  // [M][ld] T (what = 0) or debug output
     const uint32_t *V;        // [dims][32] direction numbers
-    const BridgeNode *sched;  // [M]
+    const GenNode *sched;     // [segs][seg_len]
     DateConst *datec;         // [M+1]
     uint32_t *sync;           // barrier words, zeroed here
     int64_t N, ld;
     int64_t nblocks;          // 64-path blocks to write: ld / 64 (padding included)
+    int32_t segs, seg_len;    // schedule segments and their nodes
     int32_t M, R;             // dates, 64-path blocks per wave
     int32_t what;             // 0 paths, 1 sobol ints, 2 normals (debug)
     int32_t pad;
@@ -122,7 +135,7 @@ struct PaperArgs {
 struct alignas(64) BatchOpt {
     void *S;                  // [M][ld] T
     void *pv;                 // [ld] T
-    const BridgeNode *sched;  // [M]
+    const GenNode *sched;     // [segments][seg_len]
     DateConst *datec;         // [M+1]
     double *rec;              // [M+1][kRec]
     double *result;           // [8]
@@ -132,13 +145,14 @@ struct alignas(64) BatchOpt {
     int64_t N, ld;
     int32_t M, G;             // dates, tiles
     int32_t tile_base;        // first partial slot / global tile index
-    int32_t is_call, allow_exercise, pad;
+    int32_t is_call, allow_exercise;
+    int32_t seg_len;          // nodes of one schedule segment
     double S0, K, r, sigma, T, mu, vol;
     const uint32_t *shift;    // [M] digital shift per dimension (randomised QMC), or null
 };
 
-struct GenUnit {              // one generation workgroup: blocks [b0, b1) of option opt
-    int32_t opt, pad;
+struct GenUnit {              // one generation workgroup: blocks [b0, b1) of option opt, schedule segment seg
+    int32_t opt, seg;
     int64_t b0, b1;
 };
 
@@ -159,10 +173,9 @@ hipError_t preload_generate();
 hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream_t s);
 // Workgroups of the sweep kernel that fit on one CU (0: no such kernel).
 int sweep_blocks_per_cu(int fp64, int laguerre, int wg, int ppt, int degree);
-__host__ __device__ size_t generate_lds_bytes(int M, int cap);
 hipError_t launch_paper(const PaperArgs &a, int fp64, hipStream_t s);
 hipError_t launch_generate_batch(const BatchOpt *opts, const GenUnit *units, int n_units,
-                                 const uint32_t *V, uint32_t *gsync, int max_dates, int fp64,
+                                 const uint32_t *V, uint32_t *gsync, int max_seg_len, int fp64,
                                  bool shifted, hipStream_t s);
 hipError_t launch_sweep_batch(const BatchOpt *opts, const int32_t *tile_opt, const BatchGlobal &g,
                               int grid, int fp64, int ppt, int degree, bool cooperative, hipStream_t s);

@@ -20,6 +20,9 @@
 
 namespace amq {
 
+// a schedule node through the scalar cache
+using GenNodeC = const __attribute__((address_space(4))) GenNode;
+
 // ---------------------------------------------------------------------------
 // Moro's inverse cumulative normal (Section III.D names it; coefficients from
 // Moro 1995, "The full Monte", Risk 8(2)).  Central region |u - 1/2| < 0.42:
@@ -103,69 +106,70 @@ __constant__ double kExpTab[64] = {
 template <typename Tab>
 __device__ __forceinline__ double exp_tab(double x, Tab tab)
 {
-    const double n = rint(x * 92.332482616893658);            // 64 / ln 2
+    // n = rint(64 x / ln 2) by adding 1.5 2^52: the integer is in the sum's low
+    // word (two's complement), no rounding and conversion instructions
+    const double r = fma3s(x, 92.332482616893658, 0x1.8p52);  // 64 / ln 2
+    const double n = r - 0x1.8p52;
+    const int ni = (int)(uint32_t)(uint64_t)__double_as_longlong(r);
     const double g = fma(-n, 3.6235106466348431e-19, fma(-n, 0.010830424696249145, x));
-    double p = fma3(1.0 / 120.0, g, kInvFact4);                 // 1/4! (see exp_poly)
-    p = fma3(p, g, 1.0 / 6.0);
+    double p = fma3s(1.0 / 120.0, g, kInvFact4);                // 1/4! (see exp_poly)
+    p = fma3s(p, g, 1.0 / 6.0);
     p = fma(p, g, 0.5);
     p = fma(p, g, 1.0);
-    const int ni = (int)n;
     const double t = tab((uint32_t)ni & 63u);
     return ldexp(fma(t, p * g, t), ni >> 6);
 }
 
-// logF: the table, from constant memory or from an LDS copy (the path
-// generator's: its loads then wait on LDS only, not on the generator's
-// pending stores); 1/F by the reciprocal's Newton refinement.
-template <typename LogF>
-__device__ __forceinline__ double log_tab(double v, LogF logF)
+// F of interval j.
+__device__ __forceinline__ double log_tab_centre(uint32_t j) { return fma((double)j, 0x1p-7, 0.5 + 0x1p-8); }
+
+// log(m 2^e), m in [1/2, 1).  tab(j): {1 / F, log F} (the path generator's LDS
+// table, 1 / F by the reciprocal's Newton refinement).  F itself is m with
+// the bits below the interval's replaced by its midpoint's.
+struct LogEntry { double rcp, log; };
+template <typename Tab>
+__device__ __forceinline__ double log_tab(double m, int e, Tab tab)
 {
-    const double m = __builtin_amdgcn_frexp_mant(v);
-    const int e = __builtin_amdgcn_frexp_exp(v);
-    const uint32_t j = (uint32_t)((uint64_t)__double_as_longlong(m) >> 46) & 63u;
-    const double F = fma((double)j, 0x1p-7, 0.5 + 0x1p-8);
-    const double u = (m - F) * rcp_f64(F);
-    double p = fma(u, 1.0 / 7.0, -1.0 / 6.0);
-    p = fma(p, u, 0.2);
-    p = fma(p, u, -0.25);
-    p = fma(p, u, 1.0 / 3.0);
+    const uint32_t hi = (uint32_t)((uint64_t)__double_as_longlong(m) >> 32);
+    const LogEntry t = tab((hi >> 14) & 63u);
+    const double F = __longlong_as_double((long long)((uint64_t)((hi & 0xFFFFC000u) | 0x2000u) << 32));
+    const double u = (m - F) * t.rcp;
+    double p = fma3s(1.0 / 7.0, u, -1.0 / 6.0);
+    p = fma3s(p, u, 0.2);
+    p = fma3s(p, u, -0.25);
+    p = fma3s(p, u, 1.0 / 3.0);
     p = fma(p, u, -0.5);
     const double l1p = fma(p, u * u, u);
     const double de = (double)e;
-    return fma(de, 0.69314718055994529, fma(de, 2.3190468138462996e-17, logF(j) + l1p));
+    return fma(de, 0.69314718055994529, fma(de, 2.3190468138462996e-17, t.log + l1p));
 }
 
-__device__ __forceinline__ double log_tab(double v)
-{
-    return log_tab(v, [](uint32_t j) { return kLogTab[j]; });
-}
-
-// The two branches separately: which branch a point takes, the central
-// rational function and the tail polynomial (its two logarithms by
-// log_tab).  inv_normal_f64 combines them; the path generator evaluates the
-// tails packed.
-template <typename T> struct MoroParts;
-
-template <> struct MoroParts<double> {
-    // d = x - 2^31 exactly (the sign bit flipped, read as a signed integer);
-    // y = u - 1/2 = d 2^-32.  The branch test and the central rational are
-    // taken on d with every constant scaled by a power of two, which leaves
-    // each rounded intermediate scaled by the same power: the values are
-    // bitwise those of the same steps on y (no under- or overflow here).
-    static __device__ __forceinline__ double centered(uint32_t x)
+// The inverse normal's two branches separately: which branch a point takes,
+// the central rational function and the tail polynomial (its two logarithms
+// by log_tab).  The path generator evaluates the tails packed.  MID: shifted
+// (randomised) points sit at cell midpoints u = (x + 1/2) 2^-32, so a shifted
+// integer 0 still maps to a finite normal.
+template <bool MID> struct Moro {
+    // Points come as xc = x ^ 2^31 (x - 2^31 as a signed integer).
+    // d = x - 2^31 (+ 1/2) exactly; y = u - 1/2 = d 2^-32.  The branch test and the central
+    // rational are taken on d with every constant scaled by a power of two,
+    // which leaves each rounded intermediate scaled by the same power: the
+    // values are bitwise those of the same steps on y (no under- or overflow
+    // here).
+    static __device__ __forceinline__ double centered(uint32_t xc)
     {
-        return (double)(int32_t)(x ^ 0x80000000u);
+        const double d = (double)(int32_t)xc;
+        return MID ? d + 0.5 : d;
     }
-    static __device__ __forceinline__ bool tail(uint32_t x)
+    static __device__ __forceinline__ bool tail(double d)
     {
-        return !(fabs(centered(x)) < 0.42 * 0x1p32);   // |y| >= 0.42
+        return !(fabs(d) < 0.42 * 0x1p32);   // |y| >= 0.42
     }
-    static __device__ __forceinline__ double central(uint32_t x)
+    static __device__ __forceinline__ double central(double d)
     {
         // y P(r) / Q(r), r = y^2 = D 2^-64: Horner in D with the k-th
         // coefficient of P scaled by 2^(-64k - 32) (the y factor's 2^-32
         // folded in) and of Q (beyond the constant 1) by 2^(-64(k + 1))
-        const double d = centered(x);
         const double D = d * d;
         const double num = d * fma3(fma3(fma3(AMQ_A3 * 0x1p-224, D, AMQ_A2 * 0x1p-160), D, AMQ_A1 * 0x1p-96),
                                     D, AMQ_A0 * 0x1p-32);
@@ -174,131 +178,53 @@ template <> struct MoroParts<double> {
                                D, 1.0);
         return num * rcp_f64(den);   // (a tail point's value is discarded)
     }
-    template <typename LogF>
-    static __device__ __forceinline__ double tail_value(uint32_t x, LogF logF)
+    template <typename Tab>
+    static __device__ __forceinline__ double tail_value(uint32_t xc, Tab tab)
     {
-        const double s = 0x1p-32;
-        const double y = ((double)x - 2147483648.0) * s;
-        const double q = y < 0.0 ? (double)x * s : (4294967296.0 - (double)x) * s;
-        const double t = log_tab(-log_tab(q, logF), logF);
-        // Horner steps as single fmas (three-address: the coefficients stay
-        // in registers of their own)
-        double v = AMQ_C8;
-        v = fma3(v, t, AMQ_C7);
-        v = fma3(v, t, AMQ_C6);
-        v = fma3(v, t, AMQ_C5);
-        v = fma3(v, t, AMQ_C4);
-        v = fma3(v, t, AMQ_C3);
-        v = fma3(v, t, AMQ_C2);
-        v = fma3(v, t, AMQ_C1);
-        v = fma3(v, t, AMQ_C0);
-        return y < 0.0 ? -v : v;
-    }
-    static __device__ __forceinline__ double tail_value(uint32_t x)
-    {
-        return tail_value(x, [](uint32_t j) { return kLogTab[j]; });
+        const uint32_t x = xc ^ 0x80000000u;
+        // 2^32 q: the distance from the nearer end, an exact integer (+ 1/2);
+        // the first logarithm takes the 2^-32 off the exponent
+        const uint32_t k = min(x, MID ? ~x : 0u - x);
+        double qd = (double)k;
+        if (MID) qd += 0.5;
+        const double l = -log_tab(__builtin_amdgcn_frexp_mant(qd), __builtin_amdgcn_frexp_exp(qd) - 32, tab);
+        const double t = log_tab(__builtin_amdgcn_frexp_mant(l), __builtin_amdgcn_frexp_exp(l), tab);
+        double v = fma3s(AMQ_C8, t, AMQ_C7);
+        v = fma3s(v, t, AMQ_C6);
+        v = fma3s(v, t, AMQ_C5);
+        v = fma3s(v, t, AMQ_C4);
+        v = fma3s(v, t, AMQ_C3);
+        v = fma3s(v, t, AMQ_C2);
+        v = fma3s(v, t, AMQ_C1);
+        v = fma3s(v, t, AMQ_C0);
+        // v > 0; the lower tail (x < 2^31) is its negative
+        const uint64_t b = (uint64_t)__double_as_longlong(v);
+        return __longlong_as_double((long long)(b ^ ((uint64_t)(~x & 0x80000000u) << 32)));
     }
 };
-
-// binary64: u, u - 1/2 and 1 - u are exact for u = x 2^-32.
-__device__ __forceinline__ double inv_normal_f64(uint32_t x)
-{
-    return MoroParts<double>::tail(x) ? MoroParts<double>::tail_value(x) : MoroParts<double>::central(x);
-}
-
-// Shifted (randomised) points sit at cell midpoints u = (x + 1/2) 2^-32, so a
-// shifted integer 0 still maps to a finite normal.
-__device__ __forceinline__ double inv_normal_mid_f64(uint32_t x)
-{
-    const double s = 0x1p-32;
-    const double y = ((double)x + 0.5 - 2147483648.0) * s;
-    if (fabs(y) < 0.42) {
-        const double r = y * y;
-        const double num = y * (((AMQ_A3 * r + AMQ_A2) * r + AMQ_A1) * r + AMQ_A0);
-        const double den = (((AMQ_B3 * r + AMQ_B2) * r + AMQ_B1) * r + AMQ_B0) * r + 1.0;
-        return num / den;
-    }
-    const double q = y < 0.0 ? ((double)x + 0.5) * s : (4294967296.0 - (double)x - 0.5) * s;
-    const double t = log_tab(-log_tab(q));
-    double v = AMQ_C8;
-    v = v * t + AMQ_C7;
-    v = v * t + AMQ_C6;
-    v = v * t + AMQ_C5;
-    v = v * t + AMQ_C4;
-    v = v * t + AMQ_C3;
-    v = v * t + AMQ_C2;
-    v = v * t + AMQ_C1;
-    v = v * t + AMQ_C0;
-    return y < 0.0 ? -v : v;
-}
-
-template <bool MID> __device__ __forceinline__ double inv_normal(uint32_t x)
-{
-    return MID ? inv_normal_mid_f64(x) : inv_normal_f64(x);
-}
-
-// A bridge node as the batch generator keeps it in LDS: 32 bytes (date and
-// dimension in one word, the three window slots in another), so that the
-// schedule of 256 dates and the generator's tables leave room for four
-// groups per CU.
-struct LdsNode {
-    uint32_t md;    // m | dim << 16
-    uint32_t slots; // sl | sr << 8 | dst << 16
-    double wl, wr, sd;
-};
-static_assert(sizeof(LdsNode) == 32, "LDS bridge node");
-static_assert(kMaxDates < 65536 && kMaxSlots <= 256, "LDS bridge node packing");
-
-// A node's integer fields, wave-uniform (scalar registers).
-struct NodeIdx { int m, dim, sl, sr, dst; };
-__device__ __forceinline__ NodeIdx node_idx(const BridgeNode &n)
-{
-    return {__builtin_amdgcn_readfirstlane(n.m), __builtin_amdgcn_readfirstlane(n.dim),
-            __builtin_amdgcn_readfirstlane(n.sl), __builtin_amdgcn_readfirstlane(n.sr),
-            __builtin_amdgcn_readfirstlane(n.dst)};
-}
-__device__ __forceinline__ NodeIdx node_idx(const LdsNode &n)
-{
-    const uint32_t md = (uint32_t)__builtin_amdgcn_readfirstlane((int)n.md);
-    const uint32_t sv = (uint32_t)__builtin_amdgcn_readfirstlane((int)n.slots);
-    return {(int)(md & 0xFFFFu), (int)(md >> 16), (int)(sv & 0xFFu), (int)((sv >> 8) & 0xFFu), (int)(sv >> 16)};
-}
 
 // Nodes whose tail normals are evaluated together (binary64 paths): a
 // 64-point Sobol block puts about 10 of its 64 points of each dimension in
 // the tails (|u - 1/2| >= 0.42), so the tails of 5 nodes mostly fill one wave.
-constexpr int kTailChunk = 5;
-// Tail points staged per wave and chunk: every lane of every node
-// (kTailFull), or kTailSmall.  An aligned block of 64 Sobol points has
-// exactly one point in each interval [k/64, (k+1)/64) of every dimension (the
-// generator matrix's leading 6 x 6 block is triangular with unit diagonal),
-// and the tails meet 12 such intervals; a wave's lanes hold 63 points of one
-// aligned block and the first of the next, so a node has at most 13 tail
-// points and a chunk at most 65 <= kTailSmall.  The smaller staging lets
-// four groups per CU hold their tables at 256 dates and more; its slots are
-// masked to the staging, so no point set could write outside it.
-constexpr int kTailFull = kTailChunk * 64, kTailSmall = 128;
-static_assert((kTailSmall & (kTailSmall - 1)) == 0 && kTailSmall >= 13 * kTailChunk, "tail staging");
+constexpr int kTailChunk = 6;
+// Tail points staged per wave and chunk.  An aligned block of 64 Sobol points
+// has exactly one point in each interval [k/64, (k+1)/64) of every dimension
+// (the generator matrix's leading 6 x 6 block is triangular with unit
+// diagonal; a digital shift permutes the intervals), and the tails meet 12
+// such intervals; a wave's lanes hold 63 points of one aligned block and the
+// first of the next, so a node has at most 13 tail points and a chunk at most
+// 65.  The staging holds every lane of every node all the same, so no point
+// set could write outside it; a point's word becomes its normal in place.
+constexpr int kTailCap = kTailChunk * 64;
 
-__host__ __device__ size_t generate_lds_bytes(int M, int cap)
-{
-    // lane tables [M][16], per-wave block words [kWaves][M][2], per-wave tail
-    // staging: points [cap] u32 and normals [cap] f64 (both storage types:
-    // the normals are binary64), the logarithm's table [64] f64, the
-    // exponential's table [64] f64
-    return (size_t)M * 16 * sizeof(uint32_t) + (size_t)kWaves * M * 2 * sizeof(uint32_t) +
-           (size_t)kWaves * cap * (sizeof(uint32_t) + sizeof(double)) + 8 + (64 + 64) * sizeof(double);
-}
-
-// The single-option generator's staging: the full one while the four groups
-// per CU that the kernel's registers allow still fit in LDS with it, else
-// the smaller.
-int gen_tail_cap(int M, int fp64)
-{
-    (void)fp64;
-    const size_t share = (size_t)160 * 1024 / 4;
-    return generate_lds_bytes(M, kTailFull) <= share ? kTailFull : kTailSmall;
-}
+// Dynamic LDS of a generation workgroup (bytes): the exponential's table [64]
+// f64 and the logarithm's [64] {1/F, log F} at fixed offsets (their addresses
+// are then immediates), the per-wave tail staging ([kTailCap] points, then
+// normals, and 64 spare words), then per schedule node the lane tables [16]
+// u32, every wave's block words [2] u32 and the node's dimension.
+constexpr size_t kLdsLog = 64 * 8, kLdsTz = kLdsLog + 64 * 16, kLdsSpare = kLdsTz + (size_t)kWaves * kTailCap * 8,
+                 kLdsNodes = kLdsSpare + (size_t)kWaves * 64 * 4, kLdsPerNode = 64 + kWaves * 8 + 4;
+static size_t gen_lds_bytes(int len) { return kLdsNodes + (size_t)len * kLdsPerNode; }
 
 // ---------------------------------------------------------------------------
 // Generation.  One wave owns 64 consecutive paths i = 64w + lane (Sobol index
@@ -308,7 +234,9 @@ int gen_tail_cap(int M, int fp64)
 // X_j(h) is wave-uniform (kept per wave in LDS as the pair for h = 64w and
 // h = 64(w+1), because lane 63 has n = 64(w+1)); x^lo comes from two 8-entry
 // lane tables per dimension (bits 0-2 and 3-5 of gray(l)).  Moving to the
-// next block: X(64(w+1)) = X(64w) ^ V[5] ^ V[6 + ctz(w+1)].
+// next block: X(64(w+1)) = X(64w) ^ V[5] ^ V[6 + ctz(w+1)].  The tables are
+// laid out in schedule order, so a chunk's reads are one running address and
+// immediate offsets and wait for no node field.
 //
 // The bridge runs in depth-first order over a register window of ancestor
 // values (slots chosen on the host), so a path never needs more than
@@ -318,13 +246,13 @@ int gen_tail_cap(int M, int fp64)
 // One workgroup's share: `init` (the group holding the option's first block)
 // writes the option's date constants and clears its barrier words; wave
 // blocks [w0, w1) are generated.
-template <typename T, int WHAT, bool MID, int CAP, typename Node>
+template <typename T, int WHAT, bool MID>
 __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__restrict__ V,
-                                         const Node *__restrict__ sched,
+                                         const GenNode *__restrict__ sched, int len,
                                          const uint32_t *__restrict__ shift, bool init, int64_t w0,
                                          int64_t w1)
 {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) char lds[];
     const int M = a.M;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // the wave's block range in scalar registers (it is the same in every
@@ -337,21 +265,20 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
     };
     w0 = uniform_i64(w0);
     w1 = uniform_i64(w1);
-    uint32_t *ttab = lds;                                   // [M][16]
-    uint32_t *xw = lds + (size_t)M * 16 + (size_t)wave * M * 2;   // [M][2]
-    // this wave's tail staging (see kTailChunk)
-    uint32_t *tx = lds + (size_t)M * 16 + (size_t)kWaves * M * 2 + (size_t)wave * CAP;
-    double *tz0 = reinterpret_cast<double *>(reinterpret_cast<char *>(lds) +
-                                  (((size_t)M * 16 + (size_t)kWaves * M * 2 + (size_t)kWaves * CAP) *
-                                       sizeof(uint32_t) + 7) / 8 * 8);
-    double *tz = tz0 + (size_t)wave * CAP;
-    // the logarithm's table, for the packed tails
-    double *ltab = tz0 + (size_t)kWaves * CAP;
-    for (int j = tid; j < 64; j += kWG) ltab[j] = kLogTab[j];
-    // the exponential's table
-    double *etab = ltab + 64;
-    for (int j = tid; j < 64; j += kWG) etab[j] = kExpTab[j];
+    double *etab = reinterpret_cast<double *>(lds);
+    LogEntry *ltab = reinterpret_cast<LogEntry *>(lds + kLdsLog);
+    double *tz = reinterpret_cast<double *>(lds + kLdsTz) + (size_t)wave * kTailCap;
+    uint32_t *spare = reinterpret_cast<uint32_t *>(lds + kLdsSpare) + tid;
+    uint32_t *ttab = reinterpret_cast<uint32_t *>(lds + kLdsNodes);              // [len][16]
+    uint32_t *xw = ttab + (size_t)len * 16 + (size_t)wave * len * 2;             // [len][2]
+    uint32_t *dims = ttab + (size_t)len * (16 + kWaves * 2);                     // [len]
+    for (int j = tid; j < 64; j += kWG) {
+        etab[j] = kExpTab[j];
+        ltab[j].rcp = rcp_f64(log_tab_centre((uint32_t)j));
+        ltab[j].log = kLogTab[j];
+    }
     const auto etab_at = [=](uint32_t j) { return etab[j]; };
+    const auto ltab_at = [=](uint32_t j) { return ltab[j]; };
 
     if (init && WHAT == 0) {
         for (int q = tid; q < kSyncWords; q += kWG) a.sync[q] = 0u;
@@ -391,35 +318,37 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
         }
     }
 
-    for (int e = tid; e < M * 16; e += kWG) {
-        const int j = e >> 4, h = (e >> 3) & 1, idx = e & 7;
-        const uint32_t *v = V + (size_t)j * 32 + 3 * h;
-        uint32_t t = 0u;
-        if (idx & 1) t ^= v[0];
-        if (idx & 2) t ^= v[1];
-        if (idx & 4) t ^= v[2];
-        ttab[e] = t;
+    for (int q = tid; q < len; q += kWG) dims[q] = sched[q].md >> 16;
+    __syncthreads();
+    for (int e = tid; e < len * 16; e += kWG) {
+        const int h = (e >> 3) & 1, idx = e & 7;
+        const uint32_t *v = V + (size_t)dims[e >> 4] * 32 + 3 * h;
+        const uint32_t v0 = v[0], v1 = v[1], v2 = v[2];
+        ttab[e] = (idx & 1 ? v0 : 0u) ^ (idx & 2 ? v1 : 0u) ^ (idx & 4 ? v2 : 0u);
     }
 
     if (w0 < w1) {
         const uint64_t n0 = (uint64_t)w0 << 6;
         const uint64_t g0 = n0 ^ (n0 >> 1);
         const int c = min(__builtin_ctzll((uint64_t)w0 + 1u) + 6, 31);
-        for (int j = lane; j < M; j += 64) {
+        for (int q = lane; q < len; q += 64) {
+            const uint32_t j = dims[q];
             const uint32_t *v = V + (size_t)j * 32;
-            uint32_t xa = 0u;
+            // the block words carry the flipped sign bit (see Moro) and a
+            // shifted point's shift
+            uint32_t xa = (WHAT == 1 ? 0u : 0x80000000u) ^ (MID ? shift[j] : 0u);
             for (int b = 5; b < 32; ++b)
                 if ((g0 >> b) & 1u) xa ^= v[b];
-            xw[2 * j] = xa;
-            xw[2 * j + 1] = xa ^ v[5] ^ v[c];
+            xw[2 * q] = xa;
+            xw[2 * q + 1] = xa ^ v[5] ^ v[c];
         }
     }
     __syncthreads();
 
     const int lo = lane < 63 ? lane + 1 : 0;
     const int gl = lo ^ (lo >> 1);
-    const int offL = gl & 7, offH = 8 + (gl >> 3);
-    const int xsel = lane == 63 ? 1 : 0;
+    const uint32_t *tL = ttab + (gl & 7), *tH = ttab + 8 + (gl >> 3);
+    const uint32_t *tX = xw + (lane == 63 ? 1 : 0);
 
     // The inverse normal, the bridge and the exponent run in binary64 for
     // both storage types, so binary32 storage holds each path value rounded
@@ -452,107 +381,116 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
         const bool valid = i < a.N;
         if (WHAT == 0 && (w << 6) >= a.N) {
             // padding block: out of the money on every date
-            for (int m = 0; m < M; ++m) ((T *)a.S)[(size_t)m * a.ld + i] = Kp;
+            for (int s = 0; s < len; ++s) ((T *)a.S)[(size_t)((sched[s].md & 0xFFFFu) - 1u) * a.ld + i] = Kp;
             continue;
         }
-        if constexpr (WHAT == 0 && !MID) {
-            // the inverse normal's two branches evaluated apart (the tail's
+        if constexpr (WHAT == 0) {
+            // The inverse normal's two branches evaluated apart (the tail's
             // two logarithms dominate).  Every lane evaluates the (cheap)
-            // central branch of kTailChunk nodes up front (independent of one
-            // another and of the bridge, so their latencies overlap); the
-            // points in the tails are packed into this wave's LDS staging
-            // (ballot and lane rank), their tail values evaluated together,
-            // one point per lane, and read back by their owners.  The values
-            // are exactly those of inv_normal.
-            for (int s0 = 0; s0 < M; s0 += kTailChunk) {
-                uint32_t slot[kTailChunk];
-                double zcq[kTailChunk];   // central values, computed with the tail test
+            // central branch of a chunk's nodes up front (independent of one
+            // another and of the bridge); the points in the tails are packed
+            // into this wave's LDS staging (ballot and lane rank), their tail
+            // values evaluated together, one point per lane, and read back by
+            // their owners.  A whole chunk runs without branches or masked
+            // regions (a point outside the tails writes to a spare word), so
+            // the nodes' LDS reads are in flight together and their chains
+            // interleave: with a branch per node every node waited for its
+            // own node fields and table words in turn.
+            char *const blk = (char *)a.S + (size_t)(w << 6) * sizeof(T);
+            const uint64_t ldb = (uint64_t)a.ld * sizeof(T);
+            const uint32_t lane_b = (uint32_t)lane * (uint32_t)sizeof(T);
+            const auto chunk = [&](int s0, auto whole) {
+                constexpr bool FULL = decltype(whole)::value;
+                const auto has = [&](int q) { return FULL || s0 + q < len; };
+                uint32_t nmd[kTailChunk], nsl[kTailChunk];
+                double nwl[kTailChunk], nwr[kTailChunk], nsd[kTailChunk];
+#pragma unroll
+                for (int q = 0; q < kTailChunk; ++q) {
+                    GenNodeC *nd = (GenNodeC *)(sched + (has(q) ? s0 + q : s0));
+                    nmd[q] = nd->md; nsl[q] = nd->slots; nwl[q] = nd->wl; nwr[q] = nd->wr; nsd[q] = nd->sd;
+                }
+                const uint32_t *pL = tL + s0 * 16, *pH = tH + s0 * 16, *pX = tX + s0 * 2;
+                uint32_t x[kTailChunk];
+                double *slot[kTailChunk];
+                double zc[kTailChunk];
                 bool tl[kTailChunk];
                 uint32_t ntail = 0;   // wave-uniform
 #pragma unroll
-                for (int q = 0; q < kTailChunk; ++q) {
-                    tl[q] = false;
-                    if (s0 + q < M) {
-                        const int j = node_idx(sched[s0 + q]).dim;
-                        const uint32_t x = xw[2 * j + xsel] ^ ttab[j * 16 + offL] ^ ttab[j * 16 + offH];
-                        zcq[q] = MoroParts<double>::central(x);
-                        tl[q] = MoroParts<double>::tail(x);
-                        const uint64_t m = __builtin_amdgcn_ballot_w64(tl[q]);
-                        slot[q] = ntail + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                        if constexpr (CAP < kTailFull) slot[q] &= (uint32_t)(CAP - 1);
-                        if (tl[q]) tx[slot[q]] = x;
-                        ntail += (uint32_t)__builtin_popcountll(m);
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const uint32_t nstaged = min(ntail, (uint32_t)CAP);
-                for (uint32_t t0 = 0; t0 < nstaged; t0 += 64) {
-                    const uint32_t t = t0 + (uint32_t)lane;
-                    if (t < nstaged)
-                        tz[t] = MoroParts<double>::tail_value(tx[t], [=](uint32_t j) { return ltab[j]; });
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                for (int q = 0; q < kTailChunk; ++q) x[q] = has(q) ? pX[2 * q] ^ pL[16 * q] ^ pH[16 * q] : 0u;
 #pragma unroll
                 for (int q = 0; q < kTailChunk; ++q) {
-                    if (s0 + q < M) {
-                        const Node &nd = sched[s0 + q];
-                        const NodeIdx ni = node_idx(nd);
-                        const int n_m = ni.m, n_sl = ni.sl, n_sr = ni.sr, n_dst = ni.dst;
-                        const double n_wl = uniform_f64(nd.wl), n_wr = uniform_f64(nd.wr),
-                                     n_sd = uniform_f64(nd.sd);
-                        const double z = tl[q] ? tz[slot[q]] : zcq[q];
-                        const double xv = n_wl * X[n_sl] + n_wr * X[n_sr] + n_sd * (vol * z);
-                        X[n_dst] = xv;
-                        const T Sv = (T)exp_tab(xv, etab_at);
-                        ((T *)a.S + ((size_t)(n_m - 1) * a.ld + ((size_t)w << 6)))[(uint32_t)lane] = valid ? Sv : Kp;
-                    }
+                    const double d = Moro<MID>::centered(x[q]);
+                    zc[q] = Moro<MID>::central(d);
+                    tl[q] = Moro<MID>::tail(d);
+                    const uint64_t m = __builtin_amdgcn_ballot_w64(tl[q]);
+                    slot[q] = tz + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, ntail));
+                    *(tl[q] ? reinterpret_cast<uint32_t *>(slot[q]) : spare) = x[q];
+                    ntail += (uint32_t)__builtin_popcountll(m);
+                }
+                wave_lds_fence();
+                for (uint32_t t0 = 0; t0 < ntail; t0 += 64) {
+                    // lanes past the last point evaluate what the staging
+                    // holds (kept out of every result)
+                    double *t = tz + t0 + lane;
+                    *t = Moro<MID>::tail_value(*reinterpret_cast<uint32_t *>(t), ltab_at);
+                }
+                wave_lds_fence();
+                double zt[kTailChunk];
+#pragma unroll
+                for (int q = 0; q < kTailChunk; ++q) zt[q] = *slot[q];
+#pragma unroll
+                for (int q = 0; q < kTailChunk; ++q) {
+                    asm volatile("" : "+v"(zt[q]));   // (read by every lane: no masked regions)
+                    zc[q] = vol * (tl[q] ? zt[q] : zc[q]);
+                }
+#pragma unroll
+                for (int q = 0; q < kTailChunk; ++q) {
+                    if (!has(q)) break;
+                    const uint32_t sv = nsl[q], mq = nmd[q] & 0xFFFFu;
+                    const double xv = fma(nsd[q], zc[q], fma(nwl[q], X[sv & 0xFFu], nwr[q] * X[(sv >> 8) & 0xFFu]));
+                    X[sv >> 16] = xv;
+                    const T Sv = (T)exp_tab(xv, etab_at);
+                    using RowPtr = __attribute__((address_space(1))) char *;
+                    RowPtr row = (RowPtr)blk + (uint64_t)(mq - 1u) * ldb;
+                    // a scalar row base and the lane's 32-bit offset
+                    uint32_t off = lane_b;
+                    asm volatile("" : "+s"(row), "+v"(off));
+                    *(__attribute__((address_space(1))) T *)(row + off) = Sv;
                 }
                 // the next chunk rewrites the staging only after every lane
                 // has read its values back
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
+                wave_lds_fence();
+            };
+            int s0 = 0;
+            for (; s0 + kTailChunk <= len; s0 += kTailChunk) chunk(s0, std::true_type{});
+            if (s0 < len) chunk(s0, std::false_type{});
+            // the one block that straddles N: its padding paths over what the
+            // chunks stored there (a wave's stores to one address stay in order)
+            if (((w + 1) << 6) > a.N && !valid)
+                for (int s = 0; s < len; ++s) ((T *)a.S)[(size_t)((sched[s].md & 0xFFFFu) - 1u) * a.ld + i] = Kp;
         } else
-        for (int s = 0; s < M; ++s) {
-            // node fields moved to scalar registers: the batch kernel reaches
-            // the schedule through a loaded descriptor, and a window index the
-            // compiler cannot prove uniform turns every slot access into a
-            // compare-and-select chain
-            const Node &nd = sched[s];
-            const NodeIdx ni = node_idx(nd);
-            const int j = ni.dim, n_m = ni.m, n_sl = ni.sl, n_sr = ni.sr, n_dst = ni.dst;
-            const double n_wl = uniform_f64(nd.wl), n_wr = uniform_f64(nd.wr), n_sd = uniform_f64(nd.sd);
-            uint32_t x = xw[2 * j + xsel] ^ ttab[j * 16 + offL] ^ ttab[j * 16 + offH];
-            if (MID) x ^= shift[j];
+        for (int s = 0; s < len; ++s) {
+            const int j = (int)dims[s];
+            const uint32_t x = tX[2 * s] ^ tL[16 * s] ^ tH[16 * s];
             if (WHAT == 1) {
                 if (valid) ((uint32_t *)a.S)[(size_t)j * a.ld + i] = x;
                 continue;
             }
-            const double z = inv_normal<MID>(x);
-            if (WHAT == 2) {
-                if (valid) ((double *)a.S)[(size_t)j * a.ld + i] = z;
-                continue;
-            }
-            const double xv = n_wl * X[n_sl] + n_wr * X[n_sr] + n_sd * (vol * z);
-            X[n_dst] = xv;
-            const T Sv = (T)exp_tab(xv, etab_at);
-            ((T *)a.S + ((size_t)(n_m - 1) * a.ld + ((size_t)w << 6)))[(uint32_t)lane] = valid ? Sv : Kp;
+            const double d = Moro<MID>::centered(x);
+            const double z = Moro<MID>::tail(d) ? Moro<MID>::tail_value(x, ltab_at) : Moro<MID>::central(d);
+            if (valid) ((double *)a.S)[(size_t)j * a.ld + i] = z;
         }
         if (w + 1 < w1) {
             const int c = min(__builtin_ctzll((uint64_t)w + 2u) + 6, 31);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            for (int j = lane; j < M; j += 64) {
-                const uint32_t xb = xw[2 * j + 1];
-                xw[2 * j] = xb;
-                xw[2 * j + 1] = xb ^ V[(size_t)j * 32 + 5] ^ V[(size_t)j * 32 + c];
+            for (int q = lane; q < len; q += 64) {
+                const uint32_t *v = V + (size_t)dims[q] * 32;
+                const uint32_t xb = xw[2 * q + 1];
+                xw[2 * q] = xb;
+                xw[2 * q + 1] = xb ^ v[5] ^ v[c];
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -561,49 +499,53 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
     }
 }
 
-// four waves per SIMD (128 registers; with five the node loop spills):
-// latency hiding for the per-lane dependency chain of each path through the
-// dates
-template <typename T, int WHAT, bool MID, int CAP>
+// Bound by binary64 issue at the clock that its power allows (2.07 GHz
+// counted): 38 binary64 and 30 other vector instructions per path-step, the
+// LDS busy for 28 %.  Four waves per SIMD (128 registers) hide the per-lane
+// dependency chain of each path through the dates.  Whole calls, before and
+// after the branch-free chunks, the {1/F, log F} table, six nodes a chunk and
+// the segments: 2^24 x 252 binary32 16.59 -> 15.49 ms, 2^20 x 100 binary64 890
+// -> 823 us, 30011 x 365 1340 -> 1161 us (8 segments; one wave walked all 365
+// dates, 226 us of generation), 8 x 2^17 x 100 shifted 1191 -> 956 us (both
+// branches of every point, with divisions).  blockIdx.y: the schedule segment.
+template <typename T, int WHAT, bool MID>
 __global__ void __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4)))
-gen_kernel(GenArgs a, const uint32_t *__restrict__ V, const BridgeNode *__restrict__ sched,
+gen_kernel(GenArgs a, const uint32_t *__restrict__ V, const GenNode *__restrict__ sched,
            const uint32_t *__restrict__ shift)
 {
     const int64_t gw = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
     const int64_t w0 = gw * a.R;
     const int64_t w1 = min(w0 + (int64_t)a.R, a.nblocks);
     // the sweep's partial-sum rows start each launch at tag 0
-    if (WHAT == 0)
+    if (WHAT == 0 && blockIdx.y == 0)
         for (int64_t q = (int64_t)blockIdx.x * kWG + threadIdx.x; q < a.rows_n; q += (int64_t)gridDim.x * kWG)
             a.rows[q] = 0ull;
-    gen_body<T, WHAT, MID, CAP, BridgeNode>(a, V, sched, shift, blockIdx.x == 0, w0, w1);
+    // (the last group of a segment holds the fewest paths: it writes the date
+    // constants beside them)
+    gen_body<T, WHAT, MID>(a, V, sched + (size_t)blockIdx.y * a.seg_len, a.seg_len, shift,
+                           blockIdx.x == gridDim.x - 1 && blockIdx.y == 0, w0, w1);
 }
 
 hipError_t launch_generate(const GenArgs &a, int fp64, hipStream_t s)
 {
     const int64_t waves = (a.nblocks + a.R - 1) / a.R;
     const int64_t grid = (waves + kWaves - 1) / kWaves;
-    const dim3 g((unsigned)grid), b(kWG);
+    const dim3 g((unsigned)grid, (unsigned)a.segs), b(kWG);
     const bool mid = a.shift != nullptr;
-    // only the packed tails (unshifted points, paths) use the staging
-    const int cap = (a.what == 0 && !mid) ? gen_tail_cap(a.M, fp64) : kTailSmall;
-    const size_t lds = generate_lds_bytes(a.M, cap);
-    const bool full = cap == kTailFull;
+    const size_t lds = gen_lds_bytes(a.seg_len);
     if (a.what == 0) {
         if (fp64) {
-            if (mid)       hipLaunchKernelGGL((gen_kernel<double, 0, true, kTailSmall>), g, b, lds, s, a, a.V, a.sched, a.shift);
-            else if (full) hipLaunchKernelGGL((gen_kernel<double, 0, false, kTailFull>), g, b, lds, s, a, a.V, a.sched, a.shift);
-            else           hipLaunchKernelGGL((gen_kernel<double, 0, false, kTailSmall>), g, b, lds, s, a, a.V, a.sched, a.shift);
+            if (mid) hipLaunchKernelGGL((gen_kernel<double, 0, true>), g, b, lds, s, a, a.V, a.sched, a.shift);
+            else     hipLaunchKernelGGL((gen_kernel<double, 0, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
         } else {
-            if (mid)       hipLaunchKernelGGL((gen_kernel<float, 0, true, kTailSmall>), g, b, lds, s, a, a.V, a.sched, a.shift);
-            else if (full) hipLaunchKernelGGL((gen_kernel<float, 0, false, kTailFull>), g, b, lds, s, a, a.V, a.sched, a.shift);
-            else           hipLaunchKernelGGL((gen_kernel<float, 0, false, kTailSmall>), g, b, lds, s, a, a.V, a.sched, a.shift);
+            if (mid) hipLaunchKernelGGL((gen_kernel<float, 0, true>), g, b, lds, s, a, a.V, a.sched, a.shift);
+            else     hipLaunchKernelGGL((gen_kernel<float, 0, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
         }
     } else if (a.what == 1) {
-        hipLaunchKernelGGL((gen_kernel<float, 1, false, kTailSmall>), g, b, lds, s, a, a.V, a.sched, a.shift);
+        hipLaunchKernelGGL((gen_kernel<float, 1, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
     } else {
         // the normals are binary64 for both storage types
-        hipLaunchKernelGGL((gen_kernel<double, 2, false, kTailSmall>), g, b, lds, s, a, a.V, a.sched, a.shift);
+        hipLaunchKernelGGL((gen_kernel<double, 2, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
     }
     return hipGetLastError();
 }
@@ -614,8 +556,8 @@ hipError_t launch_generate(const GenArgs &a, int fp64, hipStream_t s)
 hipError_t preload_generate()
 {
     hipFuncAttributes fa;
-    hipError_t e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<float, 0, false, kTailFull>));
-    if (e == hipSuccess) e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<double, 0, false, kTailFull>));
+    hipError_t e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<float, 0, false>));
+    if (e == hipSuccess) e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<double, 0, false>));
     return e;
 }
 
@@ -722,6 +664,7 @@ __device__ __forceinline__ GenArgs gen_args_of(const BatchOpt &o, const uint32_t
     a.ld = o.ld;
     a.nblocks = o.ld / 64;
     a.M = o.M;
+    a.segs = 1; a.seg_len = o.seg_len;
     a.R = 1;
     a.what = 0;
     a.pad = 0;
@@ -743,34 +686,20 @@ gen_batch_kernel(const BatchOpt *__restrict__ opts, const GenUnit *__restrict__ 
     const BatchOpt o = opts[u.opt];
     if (blockIdx.x == 0 && threadIdx.x < 16) gsync[threadIdx.x] = 0u;
     const GenArgs a = gen_args_of(o, V);
-    if (u.b0 == 0)   // the option's first unit clears its partial-sum rows
+    if (u.b0 == 0 && u.seg == 0)   // the option's first unit clears its partial-sum rows
         for (int64_t q = threadIdx.x; q < o.rows_n; q += kWG) o.rows[q] = 0ull;
     const int64_t per = (u.b1 - u.b0 + kWaves - 1) / kWaves;
     const int64_t w0 = u.b0 + (int64_t)(threadIdx.x >> 6) * per;
     const int64_t w1 = min(w0 + per, u.b1);
-    // the option's bridge schedule copied into LDS past gen_body's regions
-    // (read by gen_body after its first barrier): co-resident groups of
-    // different options would otherwise each walk their own schedule through
-    // the shared scalar cache, one miss per date
-    extern __shared__ uint32_t lds[];
-    LdsNode *nodes = reinterpret_cast<LdsNode *>(reinterpret_cast<char *>(lds) +
-                                                 (generate_lds_bytes(o.M, kTailSmall) + 15) / 16 * 16);
-    for (int q = threadIdx.x; q < o.M; q += kWG) {
-        const BridgeNode &b = o.sched[q];
-        LdsNode n;
-        n.md = (uint32_t)b.m | (uint32_t)b.dim << 16;
-        n.slots = (uint32_t)b.sl | (uint32_t)b.sr << 8 | (uint32_t)b.dst << 16;
-        n.wl = b.wl; n.wr = b.wr; n.sd = b.sd;
-        nodes[q] = n;
-    }
-    gen_body<T, 0, MID, kTailSmall, LdsNode>(a, V, nodes, MID ? o.shift : nullptr, u.b0 == 0, w0, w1);
+    gen_body<T, 0, MID>(a, V, o.sched + (size_t)u.seg * o.seg_len, o.seg_len, MID ? o.shift : nullptr,
+                        u.b0 == 0 && u.seg == 0, w0, w1);
 }
 
 hipError_t launch_generate_batch(const BatchOpt *opts, const GenUnit *units, int n_units,
-                                 const uint32_t *V, uint32_t *gsync, int max_dates, int fp64,
+                                 const uint32_t *V, uint32_t *gsync, int max_seg_len, int fp64,
                                  bool shifted, hipStream_t s)
 {
-    const size_t lds = (generate_lds_bytes(max_dates, kTailSmall) + 15) / 16 * 16 + (size_t)max_dates * sizeof(LdsNode);
+    const size_t lds = gen_lds_bytes(max_seg_len);
     const dim3 g(n_units), b(kWG);
     if (shifted) {
         // randomised QMC: every option of the batch carries its digital shift

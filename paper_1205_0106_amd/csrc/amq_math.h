@@ -17,6 +17,15 @@ __device__ __forceinline__ double fma3(double p, double g, double c)
     return r;
 }
 
+// The same with the coefficient in scalar registers (one scalar operand is
+// free), where vector registers are the scarcer.
+__device__ __forceinline__ double fma3s(double p, double g, double c)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(p), "v"(g), "s"(c));
+    return r;
+}
+
 // exp(x) in binary64: n = rint(x log2(e)), g = x - n ln 2 (Cody-Waite: ln 2
 // split into a 53-bit head and its tail, each product taken exactly inside
 // an fma), |g| <= 0.3466; exp(x) = 2^n e^g with e^g from its Taylor series to

@@ -1,0 +1,45 @@
+"""Path generation in schedule segments (few path blocks) against whole
+schedules (many): the same paths bit for bit, plain and digitally shifted."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+KW = dict(S0=100.0, K=105.0, r=0.03, sigma=0.35, T=1.5)
+MANY = 4096 * 64 + 37   # enough blocks that schedules up to 280 dates stay whole
+
+
+@pytest.fixture(scope="module")
+def pricer():
+    import torch
+    import paper_1205_0106_amd as amq
+    assert torch.cuda.is_available()
+    return amq.Pricer(0)
+
+
+# below, at and past the date counts where 2, 4 and 8 segments begin; chunk
+# remainders of every size; more dates than one segment's tables hold
+@pytest.mark.parametrize("M", [1, 2, 7, 15, 16, 17, 31, 32, 33, 63, 64, 65, 67, 100, 280, 281, 365, 640])
+@pytest.mark.parametrize("dtype", ["fp64", "fp32"])
+def test_segments_give_the_same_paths(pricer, M, dtype):
+    import paper_1205_0106_amd as amq
+    few = 16384 + 5 if dtype == "fp32" else 1000 + 5
+    b, p = amq.make_basis("monomial", 2), amq.make_params(**KW)
+    print(f"  segments: M={M} {dtype} N={few} and {MANY}", flush=True)
+    pricer.price(p, few, M, b, dtype)
+    got = pricer.views(few, M, b, dtype)["S"].clone()
+    pricer.price(p, MANY, M, b, dtype)
+    want = pricer.views(MANY, M, b, dtype)["S"][:, :few]
+    assert np.array_equal(got.cpu().numpy(), want.cpu().numpy())
+
+
+def test_batch_segments_equal_the_option_in_a_large_book(pricer):
+    # a few options price in segments, the same ones among many in whole schedules
+    import paper_1205_0106_amd as amq
+    opt = dict(S0=100.0, K=97.0, r=0.04, sigma=0.3, T=1.0, is_call=True, n_paths=17000, n_dates=75)
+    big = [dict(opt, n_paths=30000 + q, n_dates=20) for q in range(12)]
+    b = amq.make_basis("monomial", 2)
+    for dtype in ("fp32", "fp64"):
+        alone = pricer.price_batch(amq.make_options([opt]), b, dtype)
+        mixed = pricer.price_batch(amq.make_options(big + [opt]), b, dtype)
+        assert np.array_equal(np.asarray(alone)[0], np.asarray(mixed)[-1])
