@@ -362,9 +362,10 @@ int groups_per_cu(DevState *st, int fp64, int laguerre, int wg, int ppt, int deg
 // tile size (binary32 streamed tiles too: one group of two waves per SIMD
 // instead of two groups, half the groups in the device-wide sum).
 struct TileShape { int wg, ppt; };
+constexpr double kSlabOps = 40.0;   // lane operations per path and date of a slab tile's group
 const TileShape kTiles32[] = {{512, 4}, {256, 4}, {512, 8}, {256, 16}, {512, 64}, {256, 64}, {512, 128}, {256, 128}};
-const TileShape kTiles64[] = {{512, 2}, {256, 2}, {512, 4}, {256, 8}, {512, 8}, {256, 16}, {256, 64}};
-const int kNTiles32 = 8, kNTiles64 = 7;
+const TileShape kTiles64[] = {{512, 2}, {256, 2}, {512, 4}, {256, 8}, {512, 8}, {512, 32}, {256, 16}, {256, 64}};
+const int kNTiles32 = 8, kNTiles64 = 8;
 thread_local int32_t g_sweep_wide = 1;   // 0: single-option sweeps use 256-thread groups only
 thread_local int32_t g_tile_wg = 0, g_tile_ppt = 0;   // a forced single-option tile (0: the cost model's)
 
@@ -380,7 +381,13 @@ thread_local int32_t g_tile_wg = 0, g_tile_ppt = 0;   // a forced single-option 
 //    size (two waves per SIMD hide the pass's latency) by 5-14 % below 2^16
 //    paths and up to 13 % at 2^18 - 2^19;
 //  - larger N: the work spread over min(G, CUs) compute units at ~40 lane
-//    operations per path (binary64: ~2x), against 4.5 us + 13 ns per group.
+//    operations per path (binary64: ~2x; binary32 tiles that read their slab
+//    twice 55, the slab-resident one 33), against 4.5 us + 13 ns per group; a
+//    slab tile's group has the paths of its units at 40.  Fitted at 2^20 ..
+//    10^7 paths x 20 dates, monomials of degree 2 and 4: per call the chosen
+//    tile is the fastest timed or within 3 % of it (3 10^6 paths, binary64,
+//    degree 2: slab 410 us, 256 x 64 415, 256 x 16 417; 5 10^6, binary32: 487,
+//    531 and, 256 x 128, 520; 10^7: 512 x 128 870 against 256 x 128 932).
 // Among the tiles whose grid is co-resident, the least modelled time per
 // date, small tiles first.
 int choose_plan(DevState *st, int64_t N, int fp64, int laguerre, int degree, Plan *p)
@@ -409,7 +416,18 @@ int choose_plan(DevState *st, int64_t N, int fp64, int laguerre, int degree, Pla
             // divide the padded row length
             const int64_t ld = (N + amq::kLdAlign - 1) / amq::kLdAlign * amq::kLdAlign;
             if (ld % tile != 0) continue;
-            const int64_t G = (N + tile - 1) / tile;
+            int64_t G = (N + tile - 1) / tile;
+            // slab tiles (512 threads, 256 bytes of path values a thread) take
+            // one to four quarter tiles a group: as few as fill the CUs
+            const bool slab = !laguerre && wg == 512 && ppt * (fp64 ? 8 : 4) == 256;
+            int64_t paths_cu = 0;
+            if (slab) {
+                const int64_t U = (N + tile / 4 - 1) / (tile / 4);
+                const int64_t nu = (U + gmax - 1) / gmax;
+                if (nu > 4) continue;
+                G = (U + nu - 1) / nu;
+                paths_cu = nu * (tile / 4);
+            }
             if (G > gmax) continue;
             double t;
             if (pass == 0) {
@@ -417,8 +435,10 @@ int choose_plan(DevState *st, int64_t N, int fp64, int laguerre, int degree, Pla
             } else {
                 // per-date work at 64 lanes x 4 SIMDs x 2.4 GHz per CU
                 const double cus = (double)(G < st->num_cu ? G : st->num_cu);
-                const double work_us = (double)N * (fp64 ? 80.0 : 40.0) / (cus * 4.0 * 16.0 * 2.4e3);
-                t = 4.5 + 0.013 * (double)G + work_us;
+                const bool keep = ppt * (fp64 ? 8 : 4) <= 64, resident = !laguerre && !fp64 && wg == 512 && ppt == 128;
+                const double ops = fp64 ? 80.0 : resident ? 33.0 : keep ? 40.0 : 55.0;
+                const double work_us = (double)N * ops / (cus * 4.0 * 16.0 * 2.4e3);
+                t = 4.5 + 0.013 * (double)G + (slab ? (double)paths_cu * kSlabOps / (4.0 * 16.0 * 2.4e3) : work_us);
             }
             if (!found || t < best) { best = t; p->wg = wg; p->ppt = ppt; p->G = (int)G; found = true; }
         }

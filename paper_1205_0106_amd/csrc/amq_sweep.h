@@ -107,15 +107,27 @@ struct SweepShape {
     static constexpr int waves() { return (sizeof(T) * PPT <= 16 && !LAG && D <= 2) ? 4 : 2; }
 };
 
+// Slab tiles (monomial basis, 256 bytes of path values per thread: 64
+// binary32 or 32 binary64 paths, four units of four 16-byte vectors): a
+// date's slab stays in LDS between the moment pass and the update, 128 KiB of
+// it per CU (two groups of 256 threads, or one of 512), and the next date's
+// is loaded there behind the update.  A group takes one to four units, so
+// that any path count spreads evenly over the groups.
+template <typename T, int PPT, bool LAG>
+struct Slab {
+    static constexpr bool on = !LAG && sizeof(T) * PPT == 256;
+    static constexpr int VW = 16 / sizeof(T), NU = 4, UV = 4;   // units per group at most, vectors per unit
+};
+
 // Slab-resident tiles (binary32 path values, monomial basis, one group of
-// 512 threads per CU, 64 or 128 paths per thread): a date's slab stays on
+// 512 threads per CU, 128 paths per thread): a date's slab stays on
 // chip between the moment pass and the exercise update, the first NKL
 // vectors of each thread in LDS and the next NKR in registers; the last NRR
 // (what neither holds next to the resident cashflows) are read again for the
 // update.
 template <typename T, int PPT, int WG, bool LAG>
 struct Resident {
-    static constexpr bool on = sizeof(T) == 4 && WG == 512 && !LAG && (PPT == 64 || PPT == 128);
+    static constexpr bool on = sizeof(T) == 4 && WG == 512 && !LAG && PPT == 128;
     static constexpr int NVEC = PPT * (int)sizeof(T) / 16;
     static constexpr int NKL = NVEC < 19 ? NVEC : 19;   // at most 19 x 512 x 16 B = 152 KiB of LDS
     static constexpr int NKR = NVEC - NKL < 8 ? NVEC - NKL : 8;
@@ -129,7 +141,7 @@ template <typename T, int PPT, int WG, bool LAG = false>
 constexpr int stream_keep_vecs()
 {
     if (SweepShape<T, PPT>::KEEP || WG != 512) return 0;
-    if (Resident<T, PPT, WG, LAG>::on) return 0;   // their LDS slots are arrays of their own
+    if (Resident<T, PPT, WG, LAG>::on || Slab<T, PPT, LAG>::on) return 0;   // their LDS slots are arrays of their own
     constexpr int cap = (128 * 1024) / (WG * 16);
     return SweepShape<T, PPT>::NVEC < cap ? SweepShape<T, PPT>::NVEC : cap;
 }
@@ -1102,6 +1114,7 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
                                               }
                                           })) {
             alive = false;
+            wait_vmcnt<0>();   // no request may land in LDS that the group has given back
             return;
         }
         if (gid == 0 && wave == WG / 64 - 1) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
@@ -1150,6 +1163,249 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
         // (s_beta and s_tot are next written after the next date's in-group
         // sum, as in sweep_keep)
     }
+    wait_vmcnt<0>();   // the last requests, unused
+}
+
+// The four vectors of a slab tile's unit under one LDS wait, complete on
+// return.  STRIDE: bytes between a thread's vectors.
+template <int STRIDE>
+__device__ __forceinline__ void read_unit(uint32_t addr, Vec<float> (&v)[4])
+{
+    using V4 = float __attribute__((ext_vector_type(4)));
+    static_assert(3 * STRIDE <= 65535, "LDS offset field");
+    V4 r0, r1, r2, r3;
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%5\n\tds_read_b128 %2, %4 offset:%6\n\t"
+                 "ds_read_b128 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
+                 : "v"(addr), "n"(STRIDE), "n"(2 * STRIDE), "n"(3 * STRIDE));
+    const V4 r[4] = {r0, r1, r2, r3};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = __builtin_bit_cast(Vec<float>, r[q]);
+}
+
+template <int WG>
+__device__ __forceinline__ Vec<float> *slab_array()
+{
+    __shared__ Vec<float> s[16 * WG];
+    return s;
+}
+
+// A path value's in-the-money test by one compare: s > K (call) or -s > -K
+// (put), the sign bit flipped with the side; for binary32 values K rounded
+// toward the side (see strike_threshold_f32).
+template <typename T> struct ItmTest;
+template <> struct ItmTest<float> {
+    uint32_t flip;
+    float thr;
+    __device__ ItmTest(bool call, double K)
+        : flip(call ? 0u : 0x80000000u), thr(call ? strike_threshold_f32<true>(K) : -strike_threshold_f32<false>(K))
+    {
+    }
+    __device__ __forceinline__ bool operator()(float s) const
+    {
+        return __int_as_float((int)((uint32_t)__float_as_int(s) ^ flip)) > thr;
+    }
+};
+template <> struct ItmTest<double> {
+    uint64_t flip;
+    double thr;
+    __device__ ItmTest(bool call, double K) : flip(call ? 0ull : 1ull << 63), thr(call ? K : -K) {}
+    __device__ __forceinline__ bool operator()(double s) const
+    {
+        return __longlong_as_double((long long)((uint64_t)__double_as_longlong(s) ^ flip)) > thr;
+    }
+};
+
+// The units of a slab tile's group: units [u0, u0 + nu) of the option's
+// ceil(N / unit), split as evenly as whole units allow.
+struct SlabRange { uint32_t u0; int nu; };
+template <int UNIT>
+__device__ __forceinline__ SlabRange slab_range(int64_t N, uint32_t gid, uint32_t G)
+{
+    const uint32_t U = (uint32_t)((N + UNIT - 1) / UNIT);
+    const uint32_t a = (uint32_t)((uint64_t)gid * U / G), b = (uint32_t)((uint64_t)(gid + 1) * U / G);
+    SlabRange r;
+    r.u0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
+    r.nu = __builtin_amdgcn_readfirstlane((int)(b - a));
+    return r;
+}
+
+// Slab tile: per date, a moment pass over the slab in LDS, the device-wide
+// sum and solve, then the update over the same values, each unit's next date
+// requested (memory straight to LDS) as soon as the update has read it.  Both
+// passes take the units from the last to the first, so before unit p the
+// moment pass waits until the 4 p requests made after unit p's are all that
+// is outstanding (vector memory operations complete in issue order; later
+// ones only make the wait stricter).  A wave reads and fills only its own
+// lanes' words: no barriers.  Bound by the slab's arrival from memory and, in
+// books, by vector issue (23 operations per path-date for degree 2).  A date's
+// slab was read from memory twice through a register ring, with 30: 1024
+// options in binary32 45.4 -> 41.0 ms per call, 96 in binary64 5.74 -> 5.61 ms,
+// 3 10^6 paths x 60 dates in binary64 1167 -> 1144 us.
+template <typename T, int PPT, int D, int WG>
+__device__ __forceinline__ void sweep_slab(const SweepArgs &a, const T *__restrict__ S, uint32_t gid,
+                                           const SlabRange &rg, T (&pv)[PPT], uint32_t &epoch, bool &alive,
+                                           double (*s_red)[32], double *s_tot, double *s_beta, double (*s_L)[8],
+                                           double *s_w, int *s_flag, uint64_t *s_clk, uint32_t &skipped)
+{
+    using SL = Slab<T, PPT, false>;
+    constexpr int VW = SL::VW, NU = SL::NU, UV = SL::UV;
+    constexpr int NA = 2 * D + 1, NB = D + 1, P = D + 1;
+    constexpr int NV = NA + NB + 1;
+    constexpr int RW = row_words(D);
+    constexpr uint32_t JB = WG * 16;             // bytes between a thread's vectors
+    constexpr uint32_t UNIT = UV * WG * VW;      // paths per unit
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int M = a.M, nu = rg.nu;
+    const int64_t ld = a.ld, tile0 = (int64_t)rg.u0 * UNIT;
+    const uint32_t G = (uint32_t)a.G;
+    const uint32_t voff = (uint32_t)tid * 16u;
+
+    // discounted terminal cashflows (date M)
+    {
+        const T *row = S + (size_t)(M - 1) * ld + tile0;
+        const double K = a.K, dM = a.datec[M].disc;
+        const bool call = a.is_call != 0;
+        static_for<0, NU>([&](auto pc) {
+            constexpr int p = decltype(pc)::value;
+            if (p < nu) {
+                Vec<T> v[UV];
+#pragma unroll
+                for (int q = 0; q < UV; ++q)
+                    v[q] = load_vec<T>(row, (uint32_t)(p * UV + q) * (WG * VW) + (uint32_t)tid * VW);
+#pragma unroll
+                for (int q = 0; q < UV * VW; ++q) {
+                    const double sv = (double)v[q / VW].v[q % VW];
+                    const double h = call ? sv - K : K - sv;
+                    pv[p * UV * VW + q] = h > 0.0 ? (T)(dM * h) : T(0);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < UV * VW; ++q) pv[p * UV * VW + q] = T(0);
+            }
+        });
+    }
+    if (!(a.allow_exercise && M >= 2)) return;
+
+    const double sg = a.is_call ? 1.0 : -1.0, nsk = -sg * a.K;
+    const ItmTest<T> itm_of(a.is_call != 0, a.K);
+    const __attribute__((address_space(4))) DateConst *dcs =
+        (const __attribute__((address_space(4))) DateConst *)a.datec;
+    struct DC { double disc, xa, xb; };
+    auto dconst = [&](int k) {
+        DC d;
+        d.disc = dcs[k].disc;
+        d.xa = dcs[k].xa;
+        d.xb = dcs[k].xb;
+        return d;
+    };
+    Vec<float> *const slab = slab_array<WG>();
+    const uint32_t lane_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)slab + voff;
+    uint32_t wave_el = (uint32_t)wave * 64u;
+    auto request = [&](const T *row, auto pc) {
+        constexpr int p = decltype(pc)::value;
+        __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(row + tile0), (short)0, (int)(NU * UV * JB), 0x00020000);
+#pragma unroll
+        for (int q = 0; q < UV; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (__attribute__((address_space(3))) void *)(slab + (p * UV + q) * WG + wave_el), 16, voff,
+                (uint32_t)(p * UV + q) * JB, 0, 0);
+    };
+    // f on the group's units, last to first
+    auto units = [&](auto &&f) {
+        static_for<0, NU>([&](auto qc) {
+            constexpr int p = NU - 1 - decltype(qc)::value;
+            if (p < nu) f(Ic<p>{});
+        });
+    };
+
+    DC dcc = dconst(M - 1);
+    {
+        const T *row = S + (size_t)(M - 2) * ld;
+        units([&](auto pc) { request(row, pc); });
+    }
+    for (int k = M - 1; k >= 1; --k) {
+        asm volatile("" : "+s"(wave_el));
+        const double xa = dcc.xa, dk = dcc.disc;
+        double xb = dcc.xb;
+        asm volatile("" : "+v"(xb));   // (an fma takes one scalar operand: xa)
+        const DC dcn = dconst(k >= 2 ? k - 1 : 1);
+        uint64_t stamp[3];
+        stamp[2] = record_clock(gid);
+
+        double tv[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) tv[q] = 0.0;
+        uint32_t cnt = 0;
+        units([&](auto pc) {
+            constexpr int p = decltype(pc)::value;
+            Vec<float> raw[UV];
+            wait_vmcnt<UV * p>();
+            read_unit<JB>(lane_addr + (uint32_t)p * UV * JB, raw);
+#pragma unroll
+            for (int q = 0; q < UV * VW; ++q) {
+                const T s = __builtin_bit_cast(Vec<T>, raw[q / VW]).v[q % VW];
+                const bool itm = itm_of(s);
+                cnt += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(itm));
+                asm volatile("" : "+s"(cnt));
+                resident_moments<D>(tv + 1, tv + NA, (double)s, (double)pv[p * UV * VW + q], itm, xa, xb);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        tv[NV - 1] = (double)cnt;   // wave-uniform: summed over the waves only
+        // word 0 of the row is the count too (the Gram sum of q = 0)
+        const double at = group_sum<NV, 1, WG>(tv, s_red, tid == 0 ? (uint32_t)NV - 1u : (uint32_t)tid);
+        ++epoch;
+        stamp[0] = stamp[1] = record_clock(gid);
+        if (!allreduce_publish<NV, RW, WG>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+                                           s_flag) ||
+            !gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+                                          [&]() {
+                                              const uint64_t c0 = record_clock(gid);
+                                              if (tid == 0) {
+                                                  solve_thread<D, 1>(s_tot, s_beta, s_L, s_w);
+                                                  if (gid == 0) {
+                                                      s_clk[0] = c0;
+                                                      s_clk[1] = __builtin_amdgcn_s_memrealtime();
+                                                  }
+                                              }
+                                          })) {
+            alive = false;
+            wait_vmcnt<0>();   // no request may land in LDS that the group has given back
+            return;
+        }
+        if (gid == 0 && wave == WG / 64 - 1) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
+
+        const bool solved = s_beta[8] != 0.0;
+        skipped += solved ? 0u : 1u;
+        const T *nrow = S + (size_t)(k >= 2 ? k - 2 : 0) * ld;   // (the last date requests date 1 again, unused)
+        if (solved) {
+            double gam[P];
+#pragma unroll
+            for (int q = 0; q < P; ++q) gam[q] = uniform_f64(s_beta[q]);
+            units([&](auto pc) {
+                constexpr int p = decltype(pc)::value;
+                Vec<float> raw[UV];
+                read_unit<JB>(lane_addr + (uint32_t)p * UV * JB, raw);
+                request(nrow, pc);
+#pragma unroll
+                for (int q = 0; q < UV * VW; ++q) {
+                    T &c = pv[p * UV * VW + q];
+                    c = exercise_update<T, D, false>(__builtin_bit_cast(Vec<T>, raw[q / VW]).v[q % VW], c, sg, nsk, xa,
+                                                     xb, dk, gam, 0.0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        } else {
+            units([&](auto pc) { request(nrow, pc); });
+        }
+        dcc = dcn;
+        // (s_beta and s_tot are next written after the next date's in-group
+        // sum, as in sweep_keep)
+    }
+    wait_vmcnt<0>();   // the last requests land before the LDS is used again or given back
 }
 
 // LDS of one sweep workgroup.
@@ -1167,7 +1423,7 @@ struct SweepLds {
     // component-major partials of the LDS group sums (512-thread groups):
     // [8][WG]; consecutive sums are separated by barriers
     double x[KEEP && WG == 512 ? 8 * WG : 1];
-    DateConst dc[(KEEP || Resident<T, PPT, WG, LAG>::on) ? 1 : kMaxDates + 1];
+    DateConst dc[(KEEP || Resident<T, PPT, WG, LAG>::on || Slab<T, PPT, LAG>::on) ? 1 : kMaxDates + 1];
     // streamed tiles: the first vectors of each thread's slab, kept from the
     // moment pass for the update ([vector][thread])
     Vec<T> keep[stream_keep_vecs<T, PPT, WG, LAG>() > 0 ? stream_keep_vecs<T, PPT, WG, LAG>() * WG : 1];
@@ -1183,10 +1439,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const T *__restri
                                            uint32_t &skipped, SweepLds<T, PPT, LAG, WG> &L)
 {
     const TileIO<T, PPT, WG> io(gid, e0);
-    sweep_terminal<T, PPT, WG>(a, S, io, pv);
+    if constexpr (!Slab<T, PPT, LAG>::on) sweep_terminal<T, PPT, WG>(a, S, io, pv);
     if constexpr (SweepShape<T, PPT>::KEEP) {
         sweep_keep<T, PPT, D, LAG, WG>(a, S, gid, io, pv, epoch, alive, L.red, L.red2, L.tot, L.beta, L.wl, L.x,
                                        L.flag, L.clk, skipped);
+    } else if constexpr (Slab<T, PPT, LAG>::on) {
+        sweep_slab<T, PPT, D, WG>(a, S, gid, slab_range<PPT * WG / 4>(a.N, gid, (uint32_t)a.G), pv, epoch, alive, L.red,
+                                  L.tot, L.beta, L.L, L.w, L.flag, L.clk, skipped);
     } else if constexpr (Resident<T, PPT, WG, LAG>::on) {
         static_assert(SIDE == 1 || SIDE == 2, "slab-resident tiles are compiled per payoff side");
         sweep_resident<PPT, D, SIDE == 1>(a, S, gid, io, pv, epoch, alive, L.red, L.tot, L.beta, L.L, L.flag, L.clk, skipped);
@@ -1208,30 +1467,39 @@ __device__ __forceinline__ double moment_shift(const SweepArgs &a)
     return h0 > 0.0 ? h0 : 0.0;
 }
 
-template <typename T, int PPT, int D, int WG>
+template <typename T, int PPT, int D, bool LAG, int WG>
 __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, uint32_t e0,
                                             const T (&pv)[PPT], uint32_t epoch, uint32_t skipped,
                                             double (*s_red)[32], double *s_tot, int *s_flag)
 {
     constexpr int VW = 16 / sizeof(T), NVEC = PPT / VW;
-    constexpr uint32_t JS = 64 * VW;
+    constexpr bool SLAB = Slab<T, PPT, LAG>::on;
+    constexpr uint32_t JS = (SLAB ? WG : 64) * VW;
     const int tid = threadIdx.x;
     const int64_t N = a.N;
+    int nvec = NVEC;
+    if constexpr (SLAB) {
+        const SlabRange rg = slab_range<PPT * WG / 4>(N, gid, (uint32_t)a.G);
+        e0 = rg.u0 * (PPT * WG / 4) + (uint32_t)tid * VW;
+        nvec = rg.nu * Slab<T, PPT, LAG>::UV;
+    }
     const double c = moment_shift(a);
     double fin[2] = {0.0, 0.0};
     T *pvo = (T *)a.pv_out;
 #pragma unroll
     for (int jj = 0; jj < NVEC; ++jj) {
-        Vec<T> o;
+        if (!SLAB || jj < nvec) {
+            Vec<T> o;
 #pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            const T v = pv[jj * VW + e];   // padded paths hold 0
-            o.v[e] = v;
-            const double d = (int64_t)(e0 + (uint32_t)jj * JS + (uint32_t)e) < N ? (double)v - c : 0.0;
-            fin[0] += d;
-            fin[1] += d * d;
+            for (int e = 0; e < VW; ++e) {
+                const T v = pv[jj * VW + e];   // padded paths hold 0
+                o.v[e] = v;
+                const double d = (int64_t)(e0 + (uint32_t)jj * JS + (uint32_t)e) < N ? (double)v - c : 0.0;
+                fin[0] += d;
+                fin[1] += d * d;
+            }
+            *reinterpret_cast<Vec<T> *>(pvo + e0 + (uint32_t)jj * JS) = o;
         }
-        *reinterpret_cast<Vec<T> *>(pvo + e0 + (uint32_t)jj * JS) = o;
     }
     const double ft = group_sum<2, 0, WG>(fin, s_red, (uint32_t)tid);
     ++epoch;
@@ -1303,7 +1571,7 @@ sweep_kernel(SweepArgs a, const T *__restrict__ S)
     bool alive = true;
     sweep_body<T, PPT, D, LAG, WG, SIDE>(a, S, gid, e0, pv, epoch, alive, skipped, L);
     if (!alive) return;
-    sweep_final<T, PPT, D, WG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
+    sweep_final<T, PPT, D, LAG, WG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
 }
 
 template <typename T, int PPT, int D, bool LAG>
@@ -1351,7 +1619,7 @@ sweep_batch_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
         bool alive = true;
         sweep_body<T, PPT, D, LAG, kWG>(a, (const T *)o.S, gid, e0, pv, epoch, alive, skipped, L);
         if (!alive) return;
-        sweep_final<T, PPT, D, kWG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
+        sweep_final<T, PPT, D, LAG, kWG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
     }
 }
 
@@ -1392,7 +1660,7 @@ inline const void *sweep_entry(int degree)
 
 // Paths per thread built.  binary32: 4, 16, 64, 128 (256-thread groups),
 // 4, 8, 64, 128 (512-thread groups), batch 16, 64.  binary64: 2, 8, 16, 64 (256), 2, 4,
-// 8 (512), batch 8, 32.
+// 8, 32 (512; 32 monomial only), batch 8, 32.
 template <typename T, bool LAG>
 inline const void *sweep_table(int ppt, int degree, int kind)
 {
@@ -1410,6 +1678,9 @@ inline const void *sweep_table(int ppt, int degree, int kind)
             case 2: return sweep_entry<T, 2, LAG, 2>(degree);
             case 4: return sweep_entry<T, 4, LAG, 2>(degree);
             case 8: return sweep_entry<T, 8, LAG, 2>(degree);
+            case 32:
+                if constexpr (!LAG) return sweep_entry<T, 32, LAG, 2>(degree);
+                else return nullptr;
             default: return nullptr;
             }
         }
@@ -1438,11 +1709,7 @@ inline const void *sweep_table(int ppt, int degree, int kind)
             }
         }
         if (kind == 3) {
-            switch (ppt) {
-            case 64: return sweep_entry<T, 64, LAG, 3>(degree);
-            case 128: return sweep_entry<T, 128, LAG, 3>(degree);
-            default: return nullptr;
-            }
+            return ppt == 128 ? sweep_entry<T, 128, LAG, 3>(degree) : nullptr;
         }
         switch (ppt) {
         case 4: return sweep_entry<T, 4, LAG, 0>(degree);
