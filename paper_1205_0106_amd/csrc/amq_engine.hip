@@ -362,6 +362,10 @@ int groups_per_cu(DevState *st, int fp64, int laguerre, int wg, int ppt, int deg
 // tile size (binary32 streamed tiles too: one group of two waves per SIMD
 // instead of two groups, half the groups in the device-wide sum).
 struct TileShape { int wg, ppt; };
+// us per date that groups few enough to exchange within one XCD save (binary64,
+// degree 2, 40000 paths x 50 dates: 20 groups of 4 paths a thread 180 us per
+// call, 40 of 2 189; at 64000 181 and 194)
+constexpr double kOneXcdGain = 0.2;
 constexpr double kSlabOps = 40.0;   // lane operations per path and date of a slab tile's group
 const TileShape kTiles32[] = {{512, 4}, {256, 4}, {512, 8}, {256, 16}, {512, 64}, {256, 64}, {512, 128}, {256, 128}};
 const TileShape kTiles64[] = {{512, 2}, {256, 2}, {512, 4}, {256, 8}, {512, 8}, {512, 32}, {256, 16}, {256, 64}};
@@ -431,7 +435,8 @@ int choose_plan(DevState *st, int64_t N, int fp64, int laguerre, int degree, Pla
             if (G > gmax) continue;
             double t;
             if (pass == 0) {
-                t = 0.005 * (double)G + 0.0125 * sums * (double)ppt;
+                t = 0.005 * (double)G + 0.0125 * sums * (double)ppt -
+                    (G * amq::row_words(degree) <= 512 ? kOneXcdGain : 0.0);
             } else {
                 // per-date work at 64 lanes x 4 SIMDs x 2.4 GHz per CU
                 const double cus = (double)(G < st->num_cu ? G : st->num_cu);

@@ -556,6 +556,8 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
     prefetch(M - 2);
     double xa = uniform_f64(dcc[1]), xb = uniform_f64(dcc[2]), dk = uniform_f64(dcc[0]);
     double gt = gram_pass(sc, xa, xb, wbuf(M - 1));
+    // (the first wave publishes; the announcements have had the first pass to arrive)
+    const bool local = a.xcd_stride > 1 && tid < 64 && xcd_local<RW>(a.rows, G, a.err, a.spin_limit);
 
     for (int k = M - 1; k >= 1; --k) {
         uint64_t stamp[3];
@@ -603,7 +605,7 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         ++epoch;
         stamp[0] = record_clock(gid);
         if (!allreduce_publish<NV, RW, WG>(cr < (uint32_t)NB ? rt : gt, gid, G, a.rows, a.sync, a.err, epoch,
-                                           a.spin_limit, s_tot, s_red, s_flag)) {
+                                           a.spin_limit, s_tot, s_red, s_flag, local)) {
             alive = false;
             return;
         }
@@ -1564,7 +1566,9 @@ sweep_kernel(SweepArgs a, const T *__restrict__ S)
     static_assert(PPT % (16 / sizeof(T)) == 0, "PPT must be a multiple of the vector width");
     __shared__ SweepLds<T, PPT, LAG, WG> L;
 
-    const uint32_t gid = blockIdx.x;
+    if (a.xcd_stride > 1 && blockIdx.x % (uint32_t)a.xcd_stride != 0) return;   // (another XCD's group)
+    const uint32_t gid = blockIdx.x / (uint32_t)a.xcd_stride;
+    if (a.xcd_stride > 1) xcd_announce<row_words(D)>(a.rows, gid, (uint32_t)a.G);
     const uint32_t e0 = tile_e0<T, PPT, WG>(gid);
     T pv[PPT];
     uint32_t epoch = 0, skipped = 0;
@@ -1610,7 +1614,7 @@ sweep_batch_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
         a.laguerre = LAG; a.degree = D;
         a.S0 = o.S0; a.K = o.K;
         a.spin_limit = g.spin_limit;
-        a.pad = 0;
+        a.xcd_stride = 1;
         a.rep_out = nullptr; a.rep = 0; a.n_rep = 0;
         const uint32_t gid = (uint32_t)(t - o.tile_base);
         const uint32_t e0 = tile_e0<T, PPT, kWG>(gid);
