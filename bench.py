@@ -34,7 +34,7 @@ PEAK_HBM_GBS = 8000.0   # MI355X HBM3E, GB/s
 CSRC = os.path.join(ROOT, "paper_1205_0106_amd", "csrc")
 KERNEL_SOURCES = ("amq_internal.h", "amq_math.h", "amq_sync.h", "amq_sweep.h", "amq_kernels.hip",
                   "amq_sweep_f32_mono.hip", "amq_sweep_f32_lag.hip", "amq_sweep_f64_mono.hip",
-                  "amq_sweep_f64_lag.hip")
+                  "amq_sweep_f64_lag.hip", "amq_sweep_mixed.hip")
 
 
 def kernel_source_hash() -> str:

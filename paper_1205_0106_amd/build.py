@@ -28,7 +28,7 @@ HIP_FLAGS = [
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 SOURCES = ["amq_kernels.hip", "amq_engine.hip", "amq_sweep_f32_mono.hip", "amq_sweep_f32_lag.hip",
-           "amq_sweep_f64_mono.hip", "amq_sweep_f64_lag.hip"]
+           "amq_sweep_f64_mono.hip", "amq_sweep_f64_lag.hip", "amq_sweep_mixed.hip"]
 
 
 def _table_object() -> str:

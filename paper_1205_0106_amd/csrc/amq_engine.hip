@@ -1090,45 +1090,37 @@ size_t am_batch_workspace_bytes(const am_option *opts, int32_t n_opts, am_basis 
 
 namespace {
 
-// Enqueue one batch (generation + persistent sweep) on `stream`.  grid_cap
-// bounds the persistent grid (a fraction of the device when several batches
-// run side by side); cooperative selects hipLaunchCooperativeKernel.
-// staging (optional, pinned, staging_bytes) holds the uploaded tables.
-// shifts (nullable): per option, the device address of its digital shift
-// ([n_dates] words; randomised QMC); all options of the batch or none.
-int enqueue_batch(DevState *st, const am_option *opts, int32_t n_opts, am_basis basis, int32_t dtype,
-                  char *ws, const BatchPlan &P, hipStream_t stream, int grid_cap, bool cooperative,
-                  char *staging, size_t staging_bytes, int ppt, const uint32_t *const *shifts = nullptr)
+// One part of a batch (options of one storage type), as launched.
+struct BatchPart {
+    std::vector<amq::BatchOpt> desc;      // tile_base set once the claim order is known
+    std::vector<amq::GenUnit> units;
+    int max_len = 0, max_G = 0, tiles = 0;
+};
+
+// The descriptors and generation units of one part (options of one storage
+// type) at its place in the workspace.
+int build_part(DevState *st, const am_option *opts, int32_t n_opts, am_basis basis, char *ws, const BatchPlan &P,
+               int ppt, const uint32_t *const *shifts, BatchPart &B)
 {
-    int rc = AM_OK;
-    const int fp64 = dtype == AM_FP64;
     const int64_t tile = (int64_t)amq::kWG * ppt;
     if (kBatchTileAlign % tile != 0) return fail(AM_EINVAL, "batch tile %lld does not divide the row padding", (long long)tile);
-    const int per_cu = amq::sweep_batch_blocks_per_cu(fp64, basis.kind == AM_BASIS_LAGUERRE, ppt, basis.degree);
-    if (per_cu <= 0) return fail(AM_EDEVICE, "no batch sweep kernel for ppt %d degree %d", ppt, basis.degree);
-    int capacity = per_cu * st->num_cu;
-    if (grid_cap > 0 && grid_cap < capacity) capacity = grid_cap;
-
-    std::vector<amq::BatchOpt> desc(n_opts);
+    B.desc.resize(n_opts);
     std::vector<int> variant(n_opts);
-    std::vector<int32_t> tile_opt;
-    int max_G = 0, max_len = 0;
-    int tiles = 0;
     size_t rows_off = 0;
     for (int q = 0; q < n_opts; ++q) {
         const int i = P.order[q];
         const am_option &op = opts[i];
         const DevState::DevSchedule *sched = nullptr;
-        rc = get_schedule(st, op.n_dates, &sched);
+        int rc = get_schedule(st, op.n_dates, &sched);
         if (rc) return rc;
         const int v = variant[i] = gen_variant(op.n_dates, P.total_blocks);
-        amq::BatchOpt &d = desc[i];
+        amq::BatchOpt &d = B.desc[i];
         memset(&d, 0, sizeof d);
         d.S = ws + P.offS[i];
         d.pv = ws + P.offPV[i];
         d.sched = sched->d + sched->seg.off[v];
         d.seg_len = sched->seg.len[v];
-        if (d.seg_len > max_len) max_len = d.seg_len;
+        if (d.seg_len > B.max_len) B.max_len = d.seg_len;
         d.datec = (amq::DateConst *)(ws + P.offDatec[i]);
         d.rec = (double *)(ws + P.offRec[i]);
         d.result = (double *)(ws + P.off_res) + (size_t)i * 8;
@@ -1137,7 +1129,6 @@ int enqueue_batch(DevState *st, const am_option *opts, int32_t n_opts, am_basis 
         d.ld = P.ld[i];
         d.M = op.n_dates;
         d.G = (int32_t)((op.n_paths + tile - 1) / tile);
-        d.tile_base = tiles;
         d.rows = (uint64_t *)(ws + P.off_part) + rows_off;
         d.rows_n = amq::rows_words(d.G, basis.degree);
         rows_off += (size_t)d.rows_n;
@@ -1149,13 +1140,9 @@ int enqueue_batch(DevState *st, const am_option *opts, int32_t n_opts, am_basis 
         d.mu = (op.params.r - 0.5 * op.params.sigma * op.params.sigma) * dt;
         d.vol = op.params.sigma * sqrt(dt);
         d.shift = shifts ? shifts[i] : nullptr;
-        for (int g = 0; g < d.G; ++g) tile_opt.push_back(i);
-        tiles += d.G;
-        if (d.G > max_G) max_G = d.G;
+        B.tiles += d.G;
+        if (d.G > B.max_G) B.max_G = d.G;
     }
-    const int grid = tiles < capacity ? tiles : capacity;
-    if (max_G > grid)
-        return fail(AM_EDIM, "an option needs %d tiles but only %d workgroups are resident", max_G, grid);
     // generation units: about kBatchGenWavesPerCU waves per CU in total, each
     // wave given about the same number of path-steps (blocks x dates), so
     // options with many dates get fewer blocks per wave and no unit outlasts
@@ -1164,64 +1151,139 @@ int enqueue_batch(DevState *st, const am_option *opts, int32_t n_opts, am_basis 
     int64_t total_work = 0;
     for (int i = 0; i < n_opts; ++i) total_work += (P.ld[i] / 64) * (int64_t)opts[i].n_dates;
     const int64_t wave_work = (total_work + target_waves - 1) / target_waves;
-    std::vector<amq::GenUnit> units;
     for (int q = 0; q < n_opts; ++q) {
         const int i = P.order[q];
         const int64_t nb = P.ld[i] / 64;
-        const int32_t dates = desc[i].seg_len;   // a wave's
+        const int32_t dates = B.desc[i].seg_len;   // a wave's
         int64_t R = (wave_work + dates / 2) / dates;
         if (R < 1) R = 1;
         for (int64_t b = 0; b < nb; b += amq::kWaves * R)
             for (int sg = 0; sg < 1 << variant[i]; ++sg) {
                 amq::GenUnit u;
                 u.opt = i; u.seg = sg; u.b0 = b; u.b1 = b + amq::kWaves * R < nb ? b + amq::kWaves * R : nb;
-                units.push_back(u);
+                B.units.push_back(u);
             }
     }
-    if ((int64_t)units.size() > P.max_units) return fail(AM_EDEVICE, "unit table overflow");
-    const size_t bd = desc.size() * sizeof(amq::BatchOpt), bt = tile_opt.size() * 4,
-                 bu = units.size() * sizeof(amq::GenUnit);
-    const void *src_d = desc.data(), *src_t = tile_opt.data(), *src_u = units.data();
+    if ((int64_t)B.units.size() > P.max_units) return fail(AM_EDEVICE, "unit table overflow");
+    return AM_OK;
+}
+
+// Upload a part's tables (tile_opt may be empty: the other part holds the
+// list) and launch its generation.
+int generate_part(DevState *st, const BatchPart &B, const std::vector<int32_t> &tile_opt, int fp64, bool shifted,
+                  char *ws, const BatchPlan &P, hipStream_t stream, char *staging, size_t staging_bytes)
+{
+    const size_t bd = B.desc.size() * sizeof(amq::BatchOpt), bt = tile_opt.size() * 4,
+                 bu = B.units.size() * sizeof(amq::GenUnit);
+    const void *src_d = B.desc.data(), *src_t = tile_opt.data(), *src_u = B.units.data();
     if (staging && align256(bd) + align256(bt) + bu <= staging_bytes) {
-        memcpy(staging, desc.data(), bd);
-        memcpy(staging + align256(bd), tile_opt.data(), bt);
-        memcpy(staging + align256(bd) + align256(bt), units.data(), bu);
+        memcpy(staging, src_d, bd);
+        if (bt) memcpy(staging + align256(bd), src_t, bt);
+        memcpy(staging + align256(bd) + align256(bt), src_u, bu);
         src_d = staging;
         src_t = staging + align256(bd);
         src_u = staging + align256(bd) + align256(bt);
     }
     HIP_TRY(hipMemcpyAsync(ws + P.off_desc, src_d, bd, hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipMemcpyAsync(ws + P.off_tiles, src_t, bt, hipMemcpyHostToDevice, stream));
+    if (bt) HIP_TRY(hipMemcpyAsync(ws + P.off_tiles, src_t, bt, hipMemcpyHostToDevice, stream));
     HIP_TRY(hipMemcpyAsync(ws + P.off_units, src_u, bu, hipMemcpyHostToDevice, stream));
-    uint32_t *gsync = (uint32_t *)(ws + P.off_gsync);
+    HIP_TRY(amq::launch_generate_batch((const amq::BatchOpt *)(ws + P.off_desc),
+                                       (const amq::GenUnit *)(ws + P.off_units), (int)B.units.size(),
+                                       st->d_V, (uint32_t *)(ws + P.off_gsync), B.max_len, fp64, shifted, stream));
+    return AM_OK;
+}
+
+// Enqueue the parts h0 .. h1 of a split batch (their generations and one
+// persistent sweep) on `stream`: one part with its own tile, or both (mode
+// kMixed) with the default ones.  grid_cap
+// bounds the persistent grid (a fraction of the device when several batches
+// run side by side); cooperative selects hipLaunchCooperativeKernel.
+// staging[h] (optional, pinned) holds part h's uploaded tables.
+// shifts (nullable): per option, the device address of its digital shift
+// ([n_dates] words; randomised QMC); all options of the batch or none.
+int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, am_basis basis, char *ws,
+                  hipStream_t stream, int grid_cap, bool cooperative, char *const (&staging)[2],
+                  const size_t (&staging_bytes)[2], const int (&ppt)[2], const uint32_t *const *shifts)
+{
+    const int laguerre = basis.kind == AM_BASIS_LAGUERRE;
+    const int per_cu = amq::sweep_batch_blocks_per_cu(mode, laguerre, ppt[h0], basis.degree);
+    if (per_cu <= 0) return fail(AM_EDEVICE, "no batch sweep kernel for ppt %d degree %d", ppt[h0], basis.degree);
+    int capacity = per_cu * st->num_cu;
+    if (grid_cap > 0 && grid_cap < capacity) capacity = grid_cap;
+
+    BatchPart B[2];
+    int tiles = 0, max_G = 0;
+    for (int h = h0; h <= h1; ++h) {
+        std::vector<const uint32_t *> part_shifts;
+        if (shifts)
+            for (int j = 0; j < S.n(h); ++j) part_shifts.push_back(shifts[S.idx[h][j]]);
+        int rc = build_part(st, S.opts[h].data(), S.n(h), basis, ws + S.off[h], S.P[h], ppt[h],
+                            shifts ? part_shifts.data() : nullptr, B[h]);
+        if (rc) return rc;
+        tiles += B[h].tiles;
+        max_G = B[h].max_G > max_G ? B[h].max_G : max_G;
+    }
+    const int grid = tiles < capacity ? tiles : capacity;
+    if (max_G > grid)
+        return fail(AM_EDIM, "an option needs %d tiles but only %d workgroups are resident", max_G, grid);
+
+    // claim order: options by decreasing work (each part's order), merged
+    std::vector<int32_t> tile_opt;
+    tile_opt.reserve(tiles);
+    size_t q[2] = {0, 0};
+    const auto next_work = [&](int h) {
+        if (h < h0 || h > h1 || q[h] >= (size_t)S.n(h)) return -1.0;
+        const am_option &o = S.opts[h][S.P[h].order[q[h]]];
+        return (double)o.n_paths * o.n_dates;
+    };
+    for (;;) {
+        const double w0 = next_work(0), w1 = next_work(1);
+        if (w0 < 0.0 && w1 < 0.0) break;
+        const int h = w0 >= w1 ? 0 : 1;
+        const int i = S.P[h].order[q[h]++];
+        amq::BatchOpt &d = B[h].desc[i];
+        d.tile_base = (int32_t)tile_opt.size();
+        tile_opt.insert(tile_opt.end(), (size_t)d.G, mode == amq::kMixed && h == 1 ? (int32_t)((uint32_t)i | 0x80000000u) : i);
+    }
+    // the list lies in one part's tile table: a table has a word per 256 padded
+    // paths, 64 and more times that part's tiles, so the part with more tiles
+    // has room for both lists
+    const int ht = h0 == h1 ? h0 : (B[0].tiles >= B[1].tiles ? 0 : 1);
+
     ProfRec *pr = nullptr;
     if (g_prof.on) {
-        rc = prof_slot(&pr);
+        int rc = prof_slot(&pr);
         if (rc) return rc;
         HIP_TRY(hipEventRecord(pr->e[0], stream));
     }
-    HIP_TRY(amq::launch_generate_batch((const amq::BatchOpt *)(ws + P.off_desc),
-                                       (const amq::GenUnit *)(ws + P.off_units), (int)units.size(),
-                                       st->d_V, gsync, max_len, fp64, shifts != nullptr, stream));
+    const std::vector<int32_t> none;
+    for (int h = h0; h <= h1; ++h) {
+        int rc = generate_part(st, B[h], h == ht ? tile_opt : none, S.storage[h] == AM_FP64, shifts != nullptr,
+                               ws + S.off[h], S.P[h], stream, staging[h], staging_bytes[h]);
+        if (rc) return rc;
+    }
     if (pr) HIP_TRY(hipEventRecord(pr->e[1], stream));
     amq::BatchGlobal g;
     memset(&g, 0, sizeof g);
+    uint32_t *gsync = (uint32_t *)(ws + S.off[h0] + S.P[h0].off_gsync);
     g.claim = gsync;
     g.err = gsync + 1;
     g.total_tiles = tiles;
-    g.laguerre = basis.kind == AM_BASIS_LAGUERRE;
+    g.laguerre = laguerre;
     g.spin_limit = g_spin_limit ? g_spin_limit : kDefaultSpin;
-    hipError_t e = amq::launch_sweep_batch((const amq::BatchOpt *)(ws + P.off_desc),
-                                           (const int32_t *)(ws + P.off_tiles), g, grid, fp64, ppt,
-                                           basis.degree, cooperative, stream);
+    if (mode == amq::kMixed) {
+        g.opts64 = (const amq::BatchOpt *)(ws + S.off[1] + S.P[1].off_desc);
+        g.err64 = (uint32_t *)(ws + S.off[1] + S.P[1].off_gsync) + 1;
+    }
+    hipError_t e = amq::launch_sweep_batch((const amq::BatchOpt *)(ws + S.off[h0] + S.P[h0].off_desc),
+                                           (const int32_t *)(ws + S.off[ht] + S.P[ht].off_tiles), g, grid, mode,
+                                           ppt[h0], basis.degree, cooperative, stream);
     if (e != hipSuccess)
-        return fail(AM_EDEVICE, "batch sweep launch (grid %d, ppt %d) failed: %s", grid, ppt, hipGetErrorString(e));
+        return fail(AM_EDEVICE, "batch sweep launch (grid %d, ppt %d) failed: %s", grid, ppt[h0], hipGetErrorString(e));
     if (pr) HIP_TRY(hipEventRecord(pr->e[2], stream));
     return AM_OK;
 }
 
-// Bytes of pinned staging one part's tables need (descriptors, tile table,
-// generation units).
 size_t staging_bytes_for(const BatchPlan &P, int n)
 {
     return align256((size_t)n * sizeof(amq::BatchOpt)) + align256((size_t)P.total_blocks * 4) +
@@ -1233,26 +1295,38 @@ size_t staging_bytes_for(const BatchPlan &P, int n)
 // persistent grid (0: the device's resident capacity); staging (optional,
 // pinned) holds both parts' tables, part 1's after part 0's.
 // shifts (nullable): per caller option, the device address of its digital
-// shift (see enqueue_batch).
+// shift (see enqueue_parts).
 int enqueue_split(DevState *st, const SplitBatch &B, am_basis basis, int32_t dtype, char *ws,
                   hipStream_t stream, const int *grid_cap, bool cooperative, char *staging,
                   size_t staging_bytes, const int *ppt_in, const uint32_t *const *shifts = nullptr)
 {
     size_t so = 0;
+    int ppt[2] = {0, 0};
+    char *stg[2] = {nullptr, nullptr};
+    size_t stg_bytes[2] = {0, 0};
     for (int h = 0; h < 2; ++h) {
         if (!B.n(h)) continue;
-        std::vector<const uint32_t *> part_shifts;
-        if (shifts)
-            for (int j = 0; j < B.n(h); ++j) part_shifts.push_back(shifts[B.idx[h][j]]);
-        const int ppt = ppt_in && ppt_in[h] ? ppt_in[h]
-                                            : batch_ppt(B.opts[h].data(), B.n(h), basis, dtype, B.storage[h]);
+        ppt[h] = ppt_in && ppt_in[h] ? ppt_in[h] : batch_ppt(B.opts[h].data(), B.n(h), basis, dtype, B.storage[h]);
         const size_t need = staging_bytes_for(B.P[h], B.n(h));
-        char *stg = staging && so + need <= staging_bytes ? staging + so : nullptr;
-        int rc = enqueue_batch(st, B.opts[h].data(), B.n(h), basis, B.storage[h], ws + B.off[h], B.P[h], stream,
-                               grid_cap ? grid_cap[h] : 0, cooperative, stg, stg ? need : 0, ppt,
-                               shifts ? part_shifts.data() : nullptr);
-        if (rc) return rc;
+        if (staging && so + need <= staging_bytes) {
+            stg[h] = staging + so;
+            stg_bytes[h] = need;
+        }
         so += align256(need);
+    }
+    // both storage types in one sweep where both take the default tiles
+    if (B.n(0) && B.n(1) && basis.kind == AM_BASIS_MONOMIAL && ppt[0] == default_batch_ppt(AM_FP32_BULK) &&
+        ppt[1] == default_batch_ppt(AM_FP64)) {
+        const int cap = grid_cap ? (grid_cap[0] < grid_cap[1] ? grid_cap[0] : grid_cap[1]) : 0;
+        const int rc = enqueue_parts(st, B, 0, 1, amq::kMixed, basis, ws, stream, cap, cooperative, stg, stg_bytes, ppt,
+                                     shifts);
+        if (rc != AM_EDIM) return rc;   // (else too large for the shared grid: one after the other)
+    }
+    for (int h = 0; h < 2; ++h) {
+        if (!B.n(h)) continue;
+        const int rc = enqueue_parts(st, B, h, h, B.storage[h] == AM_FP64, basis, ws, stream,
+                                     grid_cap ? grid_cap[h] : 0, cooperative, stg, stg_bytes, ppt, shifts);
+        if (rc) return rc;
     }
     return AM_OK;
 }

@@ -161,7 +161,15 @@ struct BatchGlobal {
     uint32_t *err;            // error word (zeroed by generation)
     int32_t total_tiles, laguerre;
     uint32_t spin_limit, pad;
+    // a launch over both storage types (kMixed): the binary64 part's options
+    // and error word, else null
+    const BatchOpt *opts64;
+    uint32_t *err64;
 };
+
+// `fp64` of the batch sweep's launcher and capacity for both storage types
+// in one launch (monomials; ppt then names the binary32 tile, 64).
+constexpr int kMixed = 2;
 
 // Launchers (defined with the kernels).
 hipError_t launch_generate(const GenArgs &a, int fp64, hipStream_t s);
@@ -187,5 +195,7 @@ const void *sweep_table_f32_mono(int ppt, int degree, int kind);
 const void *sweep_table_f32_lag(int ppt, int degree, int kind);
 const void *sweep_table_f64_mono(int ppt, int degree, int kind);
 const void *sweep_table_f64_lag(int ppt, int degree, int kind);
+// Many options of both storage types, 64 binary32 or 32 binary64 paths per thread.
+const void *sweep_table_mixed(int degree);
 
 }  // namespace amq

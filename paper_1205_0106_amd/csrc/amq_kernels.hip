@@ -570,6 +570,12 @@ static const void *sweep_lookup(int fp64, int laguerre, int ppt, int degree, int
     return laguerre ? sweep_table_f32_lag(ppt, degree, kind) : sweep_table_f32_mono(ppt, degree, kind);
 }
 
+static const void *batch_lookup(int fp64, int laguerre, int ppt, int degree)
+{
+    if (fp64 == kMixed) return laguerre || ppt != 64 ? nullptr : sweep_table_mixed(degree);
+    return sweep_lookup(fp64, laguerre, ppt, degree, 1);
+}
+
 static int blocks_per_cu(const void *f, int wg)
 {
     if (!f) return 0;
@@ -586,7 +592,7 @@ int sweep_blocks_per_cu(int fp64, int laguerre, int wg, int ppt, int degree)
 
 int sweep_batch_blocks_per_cu(int fp64, int laguerre, int ppt, int degree)
 {
-    return blocks_per_cu(sweep_lookup(fp64, laguerre, ppt, degree, 1), kWG);
+    return blocks_per_cu(batch_lookup(fp64, laguerre, ppt, degree), kWG);
 }
 
 // Dynamic LDS that leaves room for one workgroup of `f` per CU (more than
@@ -720,7 +726,7 @@ hipError_t launch_generate_batch(const BatchOpt *opts, const GenUnit *units, int
 hipError_t launch_sweep_batch(const BatchOpt *opts, const int32_t *tile_opt, const BatchGlobal &g,
                               int grid, int fp64, int ppt, int degree, bool cooperative, hipStream_t s)
 {
-    const void *f = sweep_lookup(fp64, g.laguerre, ppt, degree, 1);
+    const void *f = batch_lookup(fp64, g.laguerre, ppt, degree);
     if (!f) return hipErrorInvalidValue;
     const BatchOpt *o = opts;
     const int32_t *to = tile_opt;

@@ -59,3 +59,22 @@ def test_book_units(orc, pricer, dtype, sizes):
         want = orc.price_american(**KW, K=d["K"], N=d["n_paths"], M=d["n_dates"], kind=orc.MONOMIAL, degree=2,
                                   is_call=d["is_call"], store32=dtype == "fp32")
         assert abs(got[q, 0] - want.price) <= TOL[dtype], (q, d)
+
+
+def test_mixed_storage_book(orc, pricer):
+    # a binary32 request whose options straddle the storage floor prices both
+    # kinds in one sweep: each option as in a book of its own kind, bit for bit
+    import paper_1205_0106_amd as amq
+    sizes = [16384, 40000, 16383, 300, 20481, 9000, 65536, 5]
+    specs = [dict(KW, K=92.0 + 2 * q, is_call=bool(q % 3 == 0), n_paths=n, n_dates=4 + 3 * q)
+             for q, n in enumerate(sizes)]
+    for degree in (2, 3):
+        b = amq.make_basis("monomial", degree)
+        got = pricer.price_batch(amq.make_options(specs), b, "fp32")
+        for big in (True, False):
+            idx = [q for q, n in enumerate(sizes) if (n >= 16384) == big]
+            alone = pricer.price_batch(amq.make_options([specs[q] for q in idx]), b, "fp32")
+            assert np.array_equal(got[idx], alone)
+        want = orc.price_american(**KW, K=specs[2]["K"], N=sizes[2], M=specs[2]["n_dates"], kind=orc.MONOMIAL,
+                                  degree=degree, is_call=specs[2]["is_call"])
+        assert abs(got[2, 0] - want.price) <= TOL["fp64"]
