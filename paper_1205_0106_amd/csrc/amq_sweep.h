@@ -495,7 +495,12 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
     // into two accumulator sets (independent chains), pinned per pair; the
     // in-the-money count from wave ballots (scalar unit); returns the group's
     // totals in the first wave's lanes at their words of the row (Gram sums
-    // 0..NA-1, count NV-1)
+    // 0..NA-1, count NV-1), or, with kSplit, leaves the reduction to
+    // split_sum_reduce while the first wave waits for this date's rows (that
+    // wave's share of the reduction and a barrier stood between it and the
+    // rows: 16 groups x 50 dates 167 -> 157 us per call, 15 x 365 1106 -> 1017,
+    // 256 groups x 100 dates 823 -> 809)
+    constexpr bool kSplit = WG == 512 && NA <= 7;
     const uint32_t cg = tid == NV - 1 ? (uint32_t)NA : tid < NA ? (uint32_t)tid : (uint32_t)NG;
     const uint32_t cr = tid >= NA ? (uint32_t)(tid - NA) : (uint32_t)NB;   // right-hand side: words NA..NA+NB-1
     // kCacheY: the Gram pass also keeps each path's right-hand-side factors
@@ -529,8 +534,15 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
 #pragma unroll
         for (int q = 0; q < NA; ++q) g[q] += g2[q];
         g[NA] = (double)cnt;
-        if constexpr (WG == 512 && NA <= 8) return group_sum_lds<NG, 1, WG>(g, s_x, s_red2, cg);
-        else return group_sum<NG, 1, WG>(g, s_red2, cg);
+        if constexpr (kSplit) {
+            split_sum_store<NG, 1, WG>(g, s_x, s_red2);
+            return 0.0;
+        } else {
+            return group_sum<NG, 1, WG>(g, s_red2, cg);
+        }
+    };
+    const auto gram_reduce = [&]() {
+        if constexpr (kSplit) split_sum_reduce<NG, 1, WG>(s_x, s_red2);
     };
 
     if (!(a.allow_exercise && M >= 2)) return;
@@ -556,6 +568,11 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
     prefetch(M - 2);
     double xa = uniform_f64(dcc[1]), xb = uniform_f64(dcc[2]), dk = uniform_f64(dcc[0]);
     double gt = gram_pass(sc, xa, xb, wbuf(M - 1));
+    if constexpr (kSplit) {
+        gram_reduce();
+        __syncthreads();
+        gt = split_sum_fetch<NG, 1, WG>(s_red2, cg);
+    }
     // (the first wave publishes; the announcements have had the first pass to arrive)
     const bool local = a.xcd_stride > 1 && tid < 64 && xcd_local<RW>(a.rows, G, a.err, a.spin_limit);
 
@@ -634,17 +651,23 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
                                                       s_clk[1] = __builtin_amdgcn_s_memrealtime();
                                                   }
                                               }
-                                          })) {
+                                          },
+                                          gram_reduce)) {
             alive = false;
             return;
         }
+        if constexpr (kSplit) gt = split_sum_fetch<NG, 1, WG>(s_red2, cg);
         if (gid == 0 && tid >= WG - 64) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
 
-        skipped += s_beta[8] == 0.0 ? 1u : 0u;
-        if (s_beta[8] != 0.0) {
-            double gam[P];
+        // the flag and the coefficients read together
+        double gam[P], solved = s_beta[8];
 #pragma unroll
-            for (int q = 0; q < P; ++q) gam[q] = s_beta[q];
+        for (int q = 0; q < P; ++q) gam[q] = s_beta[q];
+        asm volatile("" : "+v"(solved));
+#pragma unroll
+        for (int q = 0; q < P; ++q) asm volatile("" : "+v"(gam[q]));
+        skipped += solved == 0.0 ? 1u : 0u;
+        if (solved != 0.0) {
             const double *wl = wbuf(k);
 #pragma unroll
             for (int jj = 0; jj < NVEC; ++jj) {

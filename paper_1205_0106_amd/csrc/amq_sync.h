@@ -179,6 +179,58 @@ __device__ __forceinline__ double group_sum_lds(double (&v)[NV], double *s_x, do
     return t;
 }
 
+// The same sum in three steps, so that the first wave is free between them:
+// the threads' components into LDS (one barrier, inside), their reduction by
+// waves 1 .. NC (component q by wave q + 1; bitwise group_sum_lds' sums), and,
+// after a barrier of the caller's, each lane's component.
+template <int NV, int NU, int WG>
+__device__ __forceinline__ void split_sum_store(const double (&v)[NV], double *s_x, double (*s_red)[32])
+{
+    const uint32_t tx = tid_x();
+    constexpr int NC = NV - NU;
+    static_assert(WG == 512 && NC <= 7, "one wave per component, beside the first");
+#pragma unroll
+    for (int q = 0; q < NC; ++q) s_x[q * WG + tx] = v[q];
+    if ((tx & 63u) == 63u) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) s_red[tx >> 6][NC + u] = v[NC + u];
+    }
+    __syncthreads();
+}
+
+template <int NV, int NU, int WG>
+__device__ __forceinline__ void split_sum_reduce(const double *s_x, double (*s_red)[32])
+{
+    const uint32_t tx = tid_x();
+    constexpr int NC = NV - NU, TPC = WG / 8;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(tx >> 6)), l = tx & 63;
+    if (wave >= 1 && wave <= NC) {
+        const int q = wave - 1;
+        double x[8], acc = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = s_x[q * WG + l + i * TPC];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc += x[i];
+        acc = wave_sum(acc);
+        if (l == 63) s_red[0][q] = acc;
+    }
+}
+
+template <int NV, int NU, int WG>
+__device__ __forceinline__ double split_sum_fetch(double (*s_red)[32], uint32_t comp)
+{
+    constexpr int NC = NV - NU;
+    double t = 0.0;
+    if (tid_x() < 64 && comp < (uint32_t)NV) {
+        t = s_red[0][comp];
+        if (NU > 0 && comp >= (uint32_t)NC) {
+#pragma unroll
+            for (int w = 1; w < WG / 64; ++w) t += s_red[w][comp];
+        }
+    }
+    return t;
+}
+
 // Fixed-order sum of G partial slots (kPartStride doubles apart) into
 // tot[0..NV-1] (LDS), by the whole workgroup.  Thread t owns component t % 32
 // of groups t/32, t/32 + 8, ...; its loads are issued in batches of 4 before
@@ -257,9 +309,13 @@ __device__ void reduce_partials(const double *part, uint32_t G, double *tot, dou
 // read again, at most `limit` times.  Each thread adds its rows in ascending
 // order, then the group's lanes and waves in a fixed tree.  tot: LDS
 // [>= NV], valid in every thread on true.
-template <int NV, int RW, int WG, typename OnMiss>
+// meanwhile(): work of the whole group that needs no total, done once behind
+// the first batch of reads.
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <int NV, int RW, int WG, typename OnMiss, typename Work = Nothing>
 __device__ inline bool sum_rows(const uint64_t *slots, uint32_t count, uint64_t tag, uint32_t *err,
-                                uint32_t limit, double *tot, double (*s_red)[32], int *s_flag, OnMiss on_miss)
+                                uint32_t limit, double *tot, double (*s_red)[32], int *s_flag, OnMiss on_miss,
+                                Work meanwhile = Work())
 {
     const uint32_t tx = tid_x();
     static_assert(RW == 16 || RW == 32, "row width");
@@ -284,6 +340,7 @@ __device__ inline bool sum_rows(const uint64_t *slots, uint32_t count, uint64_t 
                            ? __hip_atomic_load(slots + (size_t)r * RW + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                            : tag;
             }
+            if (it == 0 && r0 == 0) meanwhile();
 #pragma unroll
             for (int k = 0; k < KB; ++k) {
                 bad |= (w[k] & 3u) != tag;
@@ -521,10 +578,10 @@ __device__ __forceinline__ void wave_lds_fence()
 // work since publishing, so the rows usually all carry the tag already) the
 // rows are read once before the counters, which saves their round trip.
 // Teams: wave 0 waits on the team rows' tags, then the team rows are summed.
-template <int NV, int RW, int WG = kWG>
+template <int NV, int RW, int WG = kWG, typename Work = Nothing>
 __device__ inline bool allreduce_gather(uint32_t G, uint64_t *rows, uint32_t *words, uint32_t *err,
                                         uint32_t epoch, uint32_t limit, double *tot, double (*s_red)[32],
-                                        int *s_flag, bool rows_first = false)
+                                        int *s_flag, bool rows_first = false, Work meanwhile = Work())
 {
     const uint32_t tx = tid_x();
     const uint64_t tag = epoch & 3u;
@@ -567,20 +624,24 @@ __device__ inline bool allreduce_gather(uint32_t G, uint64_t *rows, uint32_t *wo
     return sum_rows<NV, RW, WG>(flat ? slots : tslots, flat ? G : NT, tag, err, limit, tot, s_red, s_flag,
                                 [&](uint32_t attempt) {
                                     return (early && attempt == 1) ? poll() : rows_backoff(err, s_flag);
-                                });
+                                },
+                                meanwhile);
 }
 
 // Gathering half with the follow-up work `solve` (the first wave only, on the
 // totals in LDS): one group barrier between the totals and the group's use of
-// what `solve` left in LDS.  s_flag[0] carries the outcome.
-template <int NV, int RW, int WG, typename Solve>
+// what `solve` left in LDS.  s_flag[0] carries the outcome.  meanwhile():
+// work that needs no total and in which, where rows are spun on, the first
+// wave has no part: the other waves do it while the first spins.
+template <int NV, int RW, int WG, typename Solve, typename Work = Nothing>
 __device__ inline bool gather_and_solve(uint32_t G, uint64_t *rows, uint32_t *words, uint32_t *err, uint32_t epoch,
                                         uint32_t limit, double *tot, double (*s_red)[32], int *s_flag,
-                                        bool rows_first, Solve solve)
+                                        bool rows_first, Solve solve, Work meanwhile = Work())
 {
     const uint32_t tx = tid_x();
     const bool spin = spins_on_rows<RW>(G);
-    if (!spin && !allreduce_gather<NV, RW, WG>(G, rows, words, err, epoch, limit, tot, s_red, s_flag, rows_first))
+    if (!spin && !allreduce_gather<NV, RW, WG>(G, rows, words, err, epoch, limit, tot, s_red, s_flag, rows_first,
+                                               meanwhile))
         return false;
     if (tx < 64) {
         const bool ok = !spin || spin_rows<NV, RW, WG>(rows, G, err, epoch, limit, tot);
@@ -589,6 +650,8 @@ __device__ inline bool gather_and_solve(uint32_t G, uint64_t *rows, uint32_t *wo
             solve();
         }
         if (spin && tx == 0) s_flag[0] = ok ? 1 : 0;
+    } else if (spin) {
+        meanwhile();
     }
     __syncthreads();
     return !spin || s_flag[0] != 0;
