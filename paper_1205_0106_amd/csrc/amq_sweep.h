@@ -1139,7 +1139,6 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
                                               }
                                           })) {
             alive = false;
-            wait_vmcnt<0>();   // no request may land in LDS that the group has given back
             return;
         }
         if (gid == 0 && wave == WG / 64 - 1) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
@@ -1188,7 +1187,6 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
         // (s_beta and s_tot are next written after the next date's in-group
         // sum, as in sweep_keep)
     }
-    wait_vmcnt<0>();   // the last requests, unused
 }
 
 // The four vectors of a slab tile's unit under one LDS wait, complete on
@@ -1398,7 +1396,6 @@ __device__ __forceinline__ void sweep_slab(const SweepArgs &a, const T *__restri
                                               }
                                           })) {
             alive = false;
-            wait_vmcnt<0>();   // no request may land in LDS that the group has given back
             return;
         }
         if (gid == 0 && wave == WG / 64 - 1) record_date<D>(a, k, s_tot, s_beta, s_clk, stamp);
@@ -1430,7 +1427,6 @@ __device__ __forceinline__ void sweep_slab(const SweepArgs &a, const T *__restri
         // (s_beta and s_tot are next written after the next date's in-group
         // sum, as in sweep_keep)
     }
-    wait_vmcnt<0>();   // the last requests land before the LDS is used again or given back
 }
 
 // LDS of one sweep workgroup.
@@ -1455,6 +1451,16 @@ struct SweepLds {
     int flag[2 + WG / 64];
     uint64_t clk[2];   // group 0's clock stamps: totals in hand, solved
 };
+
+// Tiles that load straight into LDS request one date more than they use (and
+// may leave when a wait runs out): nothing of it may land in LDS that another
+// tile or group has by then.  Waited for here, where no path data is live (a
+// wait at the end of the date loop made the slab-resident tile spill).
+template <typename T, int PPT, bool LAG, int WG>
+__device__ __forceinline__ void requests_landed()
+{
+    if constexpr (Resident<T, PPT, WG, LAG>::on || Slab<T, PPT, LAG>::on) wait_vmcnt<0>();
+}
 
 // SIDE: 1 call, 2 put (slab-resident tiles are compiled per payoff side), 0
 // either (read from the arguments).
@@ -1597,8 +1603,8 @@ sweep_kernel(SweepArgs a, const T *__restrict__ S)
     uint32_t epoch = 0, skipped = 0;
     bool alive = true;
     sweep_body<T, PPT, D, LAG, WG, SIDE>(a, S, gid, e0, pv, epoch, alive, skipped, L);
-    if (!alive) return;
-    sweep_final<T, PPT, D, LAG, WG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
+    if (alive) sweep_final<T, PPT, D, LAG, WG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
+    requests_landed<T, PPT, LAG, WG>();
 }
 
 // One claimed tile of a batch: the option's whole backward sweep on this
@@ -1630,9 +1636,9 @@ __device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, uint32_t *e
     uint32_t epoch = 0, skipped = 0;
     bool alive = true;
     sweep_body<T, PPT, D, LAG, kWG>(a, (const T *)o.S, gid, e0, pv, epoch, alive, skipped, L);
-    if (!alive) return false;
-    sweep_final<T, PPT, D, LAG, kWG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
-    return true;
+    if (alive) sweep_final<T, PPT, D, LAG, kWG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
+    requests_landed<T, PPT, LAG, kWG>();
+    return alive;
 }
 
 // The next tile of a batch in claim order, or total_tiles (none left, or a
