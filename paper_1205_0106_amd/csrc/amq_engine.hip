@@ -517,7 +517,8 @@ int prof_slot(ProfRec **out)
 // event made by am_init).
 int enqueue(DevState *st, const am_params *p, int64_t N, int32_t M, am_basis b, int32_t dtype,
             char *ws, const Layout &L, hipStream_t stream, int rep = -1, int n_rep = 0,
-            const SegSchedule *noalloc_seg = nullptr, const amq::GenNode *noalloc_sched = nullptr)
+            const SegSchedule *noalloc_seg = nullptr, const amq::GenNode *noalloc_sched = nullptr,
+            double *host_out = nullptr)
 {
     const int fp64 = dtype == AM_FP64;
     Plan plan;
@@ -579,6 +580,7 @@ int enqueue(DevState *st, const am_params *p, int64_t N, int32_t M, am_basis b, 
     sa.rep_out = rep >= 0 ? (double *)(ws + L.off_rep) : nullptr;
     sa.rep = rep;
     sa.n_rep = n_rep;
+    sa.host_out = host_out;
     hipError_t e;
     {
         std::lock_guard<std::mutex> lk(st->persist_mu);
@@ -603,7 +605,8 @@ int enqueue(DevState *st, const am_params *p, int64_t N, int32_t M, am_basis b, 
 thread_local double *g_pinned = nullptr;
 thread_local uint64_t g_pinned_gen = 0;
 
-int fetch_result(char *ws, const Layout &L, hipStream_t stream, double *h_out)
+// This thread's pinned result buffer; its flag is clear on return.
+int pinned_result(double **out)
 {
     {
         std::lock_guard<std::mutex> lk(g_res_mu);
@@ -613,22 +616,45 @@ int fetch_result(char *ws, const Layout &L, hipStream_t stream, double *h_out)
         }
     }
     if (!g_pinned) {
-        if (hipHostMalloc((void **)&g_pinned, 256, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc((void **)&g_pinned, 256, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
             g_pinned = nullptr;
             return fail(AM_ENOMEM, "hipHostMalloc of the result buffer failed");
         }
         std::lock_guard<std::mutex> lk(g_res_mu);
         g_pinned_all.push_back(g_pinned);
     }
+    g_pinned[amq::kHostResultFlag] = 0.0;
+    *out = g_pinned;
+    return AM_OK;
+}
+
+int check_result(const double *res, double *h_out)
+{
+    if (!isfinite(res[0]) || !isfinite(res[1])) return fail(AM_EDEVICE, "non-finite result");
+    h_out[0] = res[0];
+    h_out[1] = res[1];
+    return AM_OK;
+}
+
+int fetch_result(char *ws, const Layout &L, hipStream_t stream, double *h_out)
+{
+    double *p = nullptr;
+    const int rc = pinned_result(&p);
+    if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(g_pinned, ws + L.off_result, 128, hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
     const uint32_t *sync = (const uint32_t *)((const char *)g_pinned + 64);
     if (sync[2] != 0u) return fail(AM_ETIMEOUT, "a device-side barrier wait ran out (spin limit)");
-    if (!isfinite(g_pinned[0]) || !isfinite(g_pinned[1]))
-        return fail(AM_EDEVICE, "non-finite result");
-    h_out[0] = g_pinned[0];
-    h_out[1] = g_pinned[1];
-    return AM_OK;
+    return check_result(g_pinned, h_out);
+}
+
+// Wait for a call enqueued with host_out = p (pinned_result).  Where the
+// kernel did not get to write it (a wait ran out), the workspace tells why.
+int wait_result(const double *p, char *ws, const Layout &L, hipStream_t stream, double *h_out)
+{
+    HIP_TRY(hipStreamSynchronize(stream));
+    if (p[amq::kHostResultFlag] != 1.0) return fetch_result(ws, L, stream, h_out);
+    return check_result(p, h_out);
 }
 
 }  // namespace
@@ -701,10 +727,15 @@ int am_price_american_ex(const am_params *params, int64_t n_paths, int32_t n_dat
     rc = get_state(&st);
     if (rc) return rc;
     hipStream_t stream = (hipStream_t)hip_stream;
-    rc = enqueue(st, params, n_paths, n_dates, basis, dtype, (char *)d_workspace, L, stream);
+    double *host = nullptr;
+    if (h_out) {
+        rc = pinned_result(&host);
+        if (rc) return rc;
+    }
+    rc = enqueue(st, params, n_paths, n_dates, basis, dtype, (char *)d_workspace, L, stream, -1, 0, nullptr, nullptr,
+                 host);
     if (rc) return rc;
-    if (!h_out) return AM_OK;
-    return fetch_result((char *)d_workspace, L, stream, h_out);
+    return h_out ? wait_result(host, (char *)d_workspace, L, stream, h_out) : AM_OK;
 }
 
 int am_price_american(const am_params *params, int64_t n_paths, int32_t n_dates, am_basis basis,
@@ -727,9 +758,13 @@ int am_price_american(const am_params *params, int64_t n_paths, int32_t n_dates,
             return fail(AM_ENOMEM, "hipMalloc of %zu workspace bytes failed", L.total);
         st->ws_bytes = L.total;
     }
-    rc = enqueue(st, params, n_paths, n_dates, basis, dtype, (char *)st->ws, L, st->stream);
+    double *host = nullptr;
+    rc = pinned_result(&host);
+    if (!rc)
+        rc = enqueue(st, params, n_paths, n_dates, basis, dtype, (char *)st->ws, L, st->stream, -1, 0, nullptr, nullptr,
+                     host);
     double out[2] = {0.0, 0.0};
-    if (!rc) rc = fetch_result((char *)st->ws, L, st->stream, out);
+    if (!rc) rc = wait_result(host, (char *)st->ws, L, st->stream, out);
     if (rc) return rc;
     *price = out[0];
     *std_err = out[1];
@@ -1073,9 +1108,12 @@ int am_price_paper_estimator(const am_params *params, int64_t n_paths, int32_t n
     pa.result = (double *)(ws + L.off_result);
     pa.N = n_paths; pa.ld = L.ld; pa.m = n_points; pa.is_call = params->is_call;
     pa.K = params->K; pa.r = params->r; pa.sigma = params->sigma; pa.dt = dt; pa.S0 = params->S0;
+    if (h_out) {
+        rc = pinned_result(&pa.host_out);
+        if (rc) return rc;
+    }
     HIP_TRY(amq::launch_paper(pa, fp64, stream));
-    if (!h_out) return AM_OK;
-    return fetch_result(ws, L, stream, h_out);
+    return h_out ? wait_result(pa.host_out, ws, L, stream, h_out) : AM_OK;
 }
 
 size_t am_batch_workspace_bytes(const am_option *opts, int32_t n_opts, am_basis basis, int32_t dtype)

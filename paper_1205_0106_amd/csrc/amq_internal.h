@@ -118,7 +118,20 @@ struct SweepArgs {
     int32_t xcd_stride;       // every xcd_stride-th workgroup is a group (set by launch_sweep)
     double *rep_out;          // randomised QMC: replicate prices [n_rep] or nullptr
     int32_t rep, n_rep;
+    double *host_out;         // pinned host copy of the result (put_host_result), or nullptr
 };
+
+// Result words in pinned host memory: result[0..5], then 1.0 once written.
+// A call that waits for its price reads it there after the stream is done;
+// copying 128 bytes back was a kernel of its own on the stream (3.7 us and
+// its launch).
+constexpr int kHostResultFlag = 8, kHostResultWords = 16;
+__device__ inline void put_host_result(double *host, const double *result)
+{
+    if (!host) return;
+    for (int q = 0; q < 6; ++q) host[q] = result[q];
+    host[kHostResultFlag] = 1.0;
+}
 
 struct PaperArgs {
     const void *S;            // [m][ld] T, dates t_i = i dt
@@ -128,6 +141,7 @@ struct PaperArgs {
     int64_t N, ld;
     int32_t m, is_call;
     double K, r, sigma, dt, S0;
+    double *host_out;         // as SweepArgs'
 };
 
 // One option of a batch, as the kernels see it (all pointers into the

@@ -844,12 +844,9 @@ __global__ void __launch_bounds__(kWG) paper_kernel(PaperArgs a, const T *__rest
         const double mean = csh + s_tot[0] / n;
         double var = a.N > 1 ? (s_tot[1] - s_tot[0] * (s_tot[0] / n)) / (n - 1.0) : 0.0;
         if (var < 0.0) var = 0.0;
-        a.result[0] = mean;
-        a.result[1] = sqrt(var / n);
-        a.result[2] = mean;
-        a.result[3] = 0.0;
-        a.result[4] = 0.0;
-        a.result[5] = 0.0;
+        const double res[6] = {mean, sqrt(var / n), mean, 0.0, 0.0, 0.0};
+        for (int q = 0; q < 6; ++q) a.result[q] = res[q];
+        put_host_result(a.host_out, res);
     }
 }
 

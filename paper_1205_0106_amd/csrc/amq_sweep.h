@@ -1558,6 +1558,8 @@ __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, ui
             a.result[3] = t0;
             a.result[4] = (double)skipped;   // dates that allowed no exercise
             a.result[5] = 0.0;
+            const double res[6] = {price, se, mean, t0, (double)skipped, 0.0};
+            put_host_result(a.host_out, res);
             if (a.rep_out) {
                 // randomised QMC: replicate prices of earlier launches are
                 // visible (stream order); the last replicate aggregates
@@ -1630,6 +1632,7 @@ __device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, uint32_t *e
     a.spin_limit = spin_limit;
     a.xcd_stride = 1;
     a.rep_out = nullptr; a.rep = 0; a.n_rep = 0;
+    a.host_out = nullptr;
     const uint32_t gid = (uint32_t)(t - o.tile_base);
     const uint32_t e0 = tile_e0<T, PPT, kWG>(gid);
     T pv[PPT];
