@@ -181,7 +181,7 @@ SegSchedule make_segments(int M)
     for (const auto &n : all) {
         amq::GenNode g;
         g.md = (uint32_t)n.m | (uint32_t)n.dim << 16;
-        g.slots = (uint32_t)n.sl | (uint32_t)n.sr << 8 | (uint32_t)n.dst << 16;
+        g.slots = 2u * ((uint32_t)n.sl | (uint32_t)n.sr << 8 | (uint32_t)n.dst << 16);
         g.wl = n.wl; g.wr = n.wr; g.sd = n.sd;
         by_date[n.m] = g;
     }
@@ -305,7 +305,7 @@ int host_schedule(int M, SegSchedule *out)
 {
     *out = make_segments(M);
     int mx = 0;
-    for (const auto &n : out->nodes) mx = (int)(n.slots >> 16) > mx ? (int)(n.slots >> 16) : mx;
+    for (const auto &n : out->nodes) mx = (int)(n.slots >> 17) > mx ? (int)(n.slots >> 17) : mx;
     if (mx >= amq::kAnchorSlot)
         return fail(AM_EDIM, "bridge schedule for %d dates does not fit the register window", M);
     return AM_OK;
@@ -1133,6 +1133,7 @@ struct BatchPart {
     std::vector<amq::BatchOpt> desc;      // tile_base set once the claim order is known
     std::vector<amq::GenUnit> units;
     int max_len = 0, max_G = 0, tiles = 0;
+    bool wide = false;
 };
 
 // The descriptors and generation units of one part (options of one storage
@@ -1178,6 +1179,7 @@ int build_part(DevState *st, const am_option *opts, int32_t n_opts, am_basis bas
         d.mu = (op.params.r - 0.5 * op.params.sigma * op.params.sigma) * dt;
         d.vol = op.params.sigma * sqrt(dt);
         d.shift = shifts ? shifts[i] : nullptr;
+        B.wide = B.wide || amq::wide_exponent(d.S0, d.mu, d.vol, d.M);
         B.tiles += d.G;
         if (d.G > B.max_G) B.max_G = d.G;
     }
@@ -1227,7 +1229,8 @@ int generate_part(DevState *st, const BatchPart &B, const std::vector<int32_t> &
     HIP_TRY(hipMemcpyAsync(ws + P.off_units, src_u, bu, hipMemcpyHostToDevice, stream));
     HIP_TRY(amq::launch_generate_batch((const amq::BatchOpt *)(ws + P.off_desc),
                                        (const amq::GenUnit *)(ws + P.off_units), (int)B.units.size(),
-                                       st->d_V, (uint32_t *)(ws + P.off_gsync), B.max_len, fp64, shifted, stream));
+                                       st->d_V, (uint32_t *)(ws + P.off_gsync), B.max_len,
+                                       fp64 | (B.wide ? amq::kGenWide : 0), shifted, stream));
     return AM_OK;
 }
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace amq {
@@ -59,11 +60,11 @@ struct BridgeNode {
 // The node as the generation kernels read it (scalar loads, half a line).
 struct alignas(32) GenNode {
     uint32_t md;     // m | dim << 16
-    uint32_t slots;  // sl | sr << 8 | dst << 16
+    uint32_t slots;  // 2 sl | 2 sr << 8 | 2 dst << 16: register offsets of the slots
     double wl, wr, sd;
 };
 static_assert(sizeof(GenNode) == 32, "packed bridge node");
-static_assert(kMaxDates < 65536 && kMaxSlots <= 256, "bridge node packing");
+static_assert(kMaxDates < 65536 && 2 * kMaxSlots <= 256, "bridge node packing");
 
 // A schedule of M dates in Q = 2^v segments of `len` nodes each, one after
 // another: segment s holds the ancestors of the s-th interval of tree level
@@ -184,6 +185,17 @@ struct BatchGlobal {
 // `fp64` of the batch sweep's launcher and capacity for both storage types
 // in one launch (monomials; ppt then names the binary32 tile, 64).
 constexpr int kMixed = 2;
+
+// Whether a path's log-price can leave the range in which the generator's
+// exponential builds the exponent by adding (|x| < 700).  |X| <= |log S0| +
+// |mu| M + 6.4 (the largest normal) x vol sqrt(M) x (1 + 1/2 + 1/2^1.5 + ...,
+// the bridge levels' deviations: below 2.8).
+inline bool wide_exponent(double S0, double mu, double vol, int M)
+{
+    const double bound = fabs(log(S0)) + fabs(mu) * M + 18.0 * vol * sqrt((double)M);
+    return !(bound < 700.0);
+}
+constexpr int kGenWide = 4;    // beside the storage type of launch_generate_batch: some option is wide
 
 // Launchers (defined with the kernels).
 hipError_t launch_generate(const GenArgs &a, int fp64, hipStream_t s);

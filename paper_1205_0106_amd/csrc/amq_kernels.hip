@@ -103,21 +103,33 @@ __constant__ double kExpTab[64] = {
     0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0,
 };
 
-template <typename Tab>
+// WIDE: any finite x (2^(n div 64) by ldexp, the table plain).  Otherwise for
+// |x| < 700: the table's entries come less j 2^46 in their bits
+// (exp_tab_entry), and adding n 2^46 gives 2^(n / 64) whole.  The same values.
+template <bool WIDE>
+__device__ __forceinline__ double exp_tab_entry(uint32_t j)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(kExpTab[j]);
+    return __longlong_as_double((long long)(WIDE ? b : b - ((uint64_t)j << 46)));
+}
+
+template <bool WIDE, typename Tab>
 __device__ __forceinline__ double exp_tab(double x, Tab tab)
 {
     // n = rint(64 x / ln 2) by adding 1.5 2^52: the integer is in the sum's low
     // word (two's complement), no rounding and conversion instructions
     const double r = fma3s(x, 92.332482616893658, 0x1.8p52);  // 64 / ln 2
     const double n = r - 0x1.8p52;
-    const int ni = (int)(uint32_t)(uint64_t)__double_as_longlong(r);
+    const uint32_t ni = (uint32_t)(uint64_t)__double_as_longlong(r);
     const double g = fma(-n, 3.6235106466348431e-19, fma(-n, 0.010830424696249145, x));
     double p = fma3s(1.0 / 120.0, g, kInvFact4);                // 1/4! (see exp_poly)
     p = fma3s(p, g, 1.0 / 6.0);
     p = fma(p, g, 0.5);
     p = fma(p, g, 1.0);
-    const double t = tab((uint32_t)ni & 63u);
-    return ldexp(fma(t, p * g, t), ni >> 6);
+    double t = tab(ni & 63u);
+    if (WIDE) return ldexp(fma(t, p * g, t), (int)ni >> 6);
+    t = __hiloint2double((int)((uint32_t)__double2hiint(t) + (ni << 14)), __double2loint(t));
+    return fma(t, p * g, t);
 }
 
 // F of interval j.
@@ -203,6 +215,35 @@ template <bool MID> struct Moro {
     }
 };
 
+// The bridge window: 16 binary64 values in v[96:127], the last registers of
+// the generators' 128, so that a node's slots (run-time numbers, the same in
+// every lane) index them in the instructions themselves (GPR index mode)
+// rather than through two moves an access: 4 vector instructions a node where
+// the compiler's indexing of an array took 9.
+typedef double Window __attribute__((ext_vector_type(16)));
+static_assert(kMaxSlots <= 16, "bridge window");
+
+// xv = wl X[l] + wr X[r] + sd z, X[dst] = xv; slots: byte q twice the slot of
+// l, r, dst (the index mode takes the low byte of its operand).
+__device__ __forceinline__ double bridge_step(Window &X, uint32_t slots, double wl, double wr, double sd, double z)
+{
+    double t;
+    const uint32_t sr = slots >> 8, sw = slots >> 16;
+    asm("s_set_gpr_idx_on %[sr], 0x2\n\t"                      // second operand indexed
+        "v_mul_f64 %[t], %[wr], v[96:97]\n\t"
+        "s_set_gpr_idx_idx %[sl]\n\t"
+        "v_fma_f64 %[t], %[wl], v[96:97], %[t]\n\t"
+        "s_set_gpr_idx_off\n\t"
+        "v_fma_f64 %[t], %[sd], %[z], %[t]\n\t"
+        "s_set_gpr_idx_on %[sw], 0x8\n\t"                      // destination indexed
+        "v_mov_b64 v[96:97], %[t]\n\t"
+        "s_set_gpr_idx_off"
+        : [t] "=&v"(t), "+{v[96:127]}"(X)
+        : [sl] "s"(slots), [sr] "s"(sr), [sw] "s"(sw), [wl] "s"(wl), [wr] "s"(wr), [sd] "s"(sd), [z] "v"(z)
+        : "m0");
+    return t;
+}
+
 // Nodes whose tail normals are evaluated together (binary64 paths): a
 // 64-point Sobol block puts about 10 of its 64 points of each dimension in
 // the tails (|u - 1/2| >= 0.42), so the tails of 5 nodes mostly fill one wave.
@@ -246,7 +287,7 @@ static size_t gen_lds_bytes(int len) { return kLdsNodes + (size_t)len * kLdsPerN
 // One workgroup's share: `init` (the group holding the option's first block)
 // writes the option's date constants and clears its barrier words; wave
 // blocks [w0, w1) are generated.
-template <typename T, int WHAT, bool MID>
+template <typename T, int WHAT, bool MID, bool WIDE>
 __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__restrict__ V,
                                          const GenNode *__restrict__ sched, int len,
                                          const uint32_t *__restrict__ shift, bool init, int64_t w0,
@@ -267,13 +308,17 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
     w1 = uniform_i64(w1);
     double *etab = reinterpret_cast<double *>(lds);
     LogEntry *ltab = reinterpret_cast<LogEntry *>(lds + kLdsLog);
-    double *tz = reinterpret_cast<double *>(lds + kLdsTz) + (size_t)wave * kTailCap;
-    uint32_t *spare = reinterpret_cast<uint32_t *>(lds + kLdsSpare) + tid;
+    // this wave's tail staging and the lane's spare word, as LDS addresses
+    using LdsU32 = __attribute__((address_space(3))) uint32_t *;
+    using LdsF64 = __attribute__((address_space(3))) double *;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)lds;
+    const uint32_t stage = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)kLdsTz + (uint32_t)wave * (kTailCap * 8u)));
+    const uint32_t spare = lds0 + (uint32_t)kLdsSpare + (uint32_t)tid * 4u;
     uint32_t *ttab = reinterpret_cast<uint32_t *>(lds + kLdsNodes);              // [len][16]
     uint32_t *xw = ttab + (size_t)len * 16 + (size_t)wave * len * 2;             // [len][2]
     uint32_t *dims = ttab + (size_t)len * (16 + kWaves * 2);                     // [len]
     for (int j = tid; j < 64; j += kWG) {
-        etab[j] = kExpTab[j];
+        etab[j] = exp_tab_entry<WIDE>((uint32_t)j);
         ltab[j].rcp = rcp_f64(log_tab_centre((uint32_t)j));
         ltab[j].log = kLogTab[j];
     }
@@ -370,9 +415,7 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
         if (a.is_call && (double)Kp > a.K) Kp = nextafterf(Kp, -INFINITY);
     }
 
-    double X[kMaxSlots];
-#pragma unroll
-    for (int q = 0; q < kMaxSlots; ++q) X[q] = 0.0;
+    Window X = 0.0;
     X[0] = log(a.S0);                                   // X(t_0)
     X[kAnchorSlot] = X[0] + a.mu * (double)M;           // read by the root node only
 
@@ -402,16 +445,9 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
             const auto chunk = [&](int s0, auto whole) {
                 constexpr bool FULL = decltype(whole)::value;
                 const auto has = [&](int q) { return FULL || s0 + q < len; };
-                uint32_t nmd[kTailChunk], nsl[kTailChunk];
-                double nwl[kTailChunk], nwr[kTailChunk], nsd[kTailChunk];
-#pragma unroll
-                for (int q = 0; q < kTailChunk; ++q) {
-                    GenNodeC *nd = (GenNodeC *)(sched + (has(q) ? s0 + q : s0));
-                    nmd[q] = nd->md; nsl[q] = nd->slots; nwl[q] = nd->wl; nwr[q] = nd->wr; nsd[q] = nd->sd;
-                }
                 const uint32_t *pL = tL + s0 * 16, *pH = tH + s0 * 16, *pX = tX + s0 * 2;
                 uint32_t x[kTailChunk];
-                double *slot[kTailChunk];
+                uint32_t slot[kTailChunk];   // LDS addresses
                 double zc[kTailChunk];
                 bool tl[kTailChunk];
                 uint32_t ntail = 0;   // wave-uniform
@@ -423,22 +459,36 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
                     zc[q] = Moro<MID>::central(d);
                     tl[q] = Moro<MID>::tail(d);
                     const uint64_t m = __builtin_amdgcn_ballot_w64(tl[q]);
-                    slot[q] = tz + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, ntail));
-                    *(tl[q] ? reinterpret_cast<uint32_t *>(slot[q]) : spare) = x[q];
+                    // the lane's rank among the tails, as an address: the count
+                    // starts at the staging's first slot
+                    slot[q] = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, stage / 8u + ntail)) * 8u;
+                    *(LdsU32)(tl[q] ? slot[q] : spare) = x[q];
                     ntail += (uint32_t)__builtin_popcountll(m);
                 }
                 wave_lds_fence();
                 for (uint32_t t0 = 0; t0 < ntail; t0 += 64) {
                     // lanes past the last point evaluate what the staging
                     // holds (kept out of every result)
-                    double *t = tz + t0 + lane;
-                    *t = Moro<MID>::tail_value(*reinterpret_cast<uint32_t *>(t), ltab_at);
+                    const uint32_t t = stage + (t0 + (uint32_t)lane) * 8u;
+                    *(LdsF64)t = Moro<MID>::tail_value(*(LdsU32)t, ltab_at);
                 }
                 wave_lds_fence();
+                // the nodes by scalar loads, all in flight together (loaded before
+                // the first part, they take the scalar registers that its
+                // constants need)
+                uint32_t nmd[kTailChunk], nsl[kTailChunk];
+                double nwl[kTailChunk], nwr[kTailChunk], nsd[kTailChunk];
+#pragma unroll
+                for (int q = 0; q < kTailChunk; ++q) {
+                    GenNodeC *nd = (GenNodeC *)(sched + (has(q) ? s0 + q : s0));
+                    nmd[q] = nd->md; nsl[q] = nd->slots; nwl[q] = nd->wl; nwr[q] = nd->wr; nsd[q] = nd->sd;
+                }
+                uint32_t off = lane_b;
+                asm volatile("" : "+v"(off));   // (widened outside the loop it would be a 64-bit add per store)
                 double zt[kTailChunk];
 #pragma unroll
-                for (int q = 0; q < kTailChunk; ++q) zt[q] = *slot[q];
+                for (int q = 0; q < kTailChunk; ++q) zt[q] = *(LdsF64)slot[q];
 #pragma unroll
                 for (int q = 0; q < kTailChunk; ++q) {
                     asm volatile("" : "+v"(zt[q]));   // (read by every lane: no masked regions)
@@ -447,15 +497,12 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
 #pragma unroll
                 for (int q = 0; q < kTailChunk; ++q) {
                     if (!has(q)) break;
-                    const uint32_t sv = nsl[q], mq = nmd[q] & 0xFFFFu;
-                    const double xv = fma(nsd[q], zc[q], fma(nwl[q], X[sv & 0xFFu], nwr[q] * X[(sv >> 8) & 0xFFu]));
-                    X[sv >> 16] = xv;
-                    const T Sv = (T)exp_tab(xv, etab_at);
+                    const uint32_t mq = nmd[q] & 0xFFFFu;
+                    const double xv = bridge_step(X, nsl[q], nwl[q], nwr[q], nsd[q], zc[q]);
+                    const T Sv = (T)exp_tab<WIDE>(xv, etab_at);
                     using RowPtr = __attribute__((address_space(1))) char *;
                     RowPtr row = (RowPtr)blk + (uint64_t)(mq - 1u) * ldb;
-                    // a scalar row base and the lane's 32-bit offset
-                    uint32_t off = lane_b;
-                    asm volatile("" : "+s"(row), "+v"(off));
+                    asm volatile("" : "+s"(row));   // a scalar row base and the lane's 32-bit offset
                     *(__attribute__((address_space(1))) T *)(row + off) = Sv;
                 }
                 // the next chunk rewrites the staging only after every lane
@@ -499,16 +546,19 @@ __device__ __forceinline__ void gen_body(const GenArgs &a, const uint32_t *__res
     }
 }
 
-// Bound by binary64 issue at the clock that its power allows (2.07 GHz
-// counted): 38 binary64 and 30 other vector instructions per path-step, the
-// LDS busy for 28 %.  Four waves per SIMD (128 registers) hide the per-lane
-// dependency chain of each path through the dates.  Whole calls, before and
-// after the branch-free chunks, the {1/F, log F} table, six nodes a chunk and
-// the segments: 2^24 x 252 binary32 16.59 -> 15.49 ms, 2^20 x 100 binary64 890
-// -> 823 us, 30011 x 365 1340 -> 1161 us (8 segments; one wave walked all 365
-// dates, 226 us of generation), 8 x 2^17 x 100 shifted 1191 -> 956 us (both
-// branches of every point, with divisions).  blockIdx.y: the schedule segment.
-template <typename T, int WHAT, bool MID>
+// Bound by vector issue at the clock that binary64 power allows (2.07 GHz
+// counted, a vector instruction every 4.1 cycles of each SIMD): 36 binary64
+// and 24 other vector instructions per path-step, the LDS busy for 28 %.
+// Four waves per SIMD (128 registers) hide the per-lane dependency chain of
+// each path through the dates.  2^24 x 252, binary32: 10.1 ms with a branch
+// per node, 9.2 with branch-free chunks of six, the {1/F, log F} table and
+// tails in place, 8.7 with the indexed window and the exponent added (per call
+// 15.76 -> 15.22 ms; both exponential forms in one kernel, 15.5, spill).  Few
+// blocks run in segments: 30011 x 365 226 us of generation when one wave
+// walked all the dates, about 45 now.  Shifted points took both branches of
+// every point, with divisions: 8 x 2^17 x 100 513 -> 280 us.  blockIdx.y: the
+// schedule segment.
+template <typename T, int WHAT, bool MID, bool WIDE>
 __global__ void __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4)))
 gen_kernel(GenArgs a, const uint32_t *__restrict__ V, const GenNode *__restrict__ sched,
            const uint32_t *__restrict__ shift)
@@ -522,7 +572,7 @@ gen_kernel(GenArgs a, const uint32_t *__restrict__ V, const GenNode *__restrict_
             a.rows[q] = 0ull;
     // (the last group of a segment holds the fewest paths: it writes the date
     // constants beside them)
-    gen_body<T, WHAT, MID>(a, V, sched + (size_t)blockIdx.y * a.seg_len, a.seg_len, shift,
+    gen_body<T, WHAT, MID, WIDE>(a, V, sched + (size_t)blockIdx.y * a.seg_len, a.seg_len, shift,
                            blockIdx.x == gridDim.x - 1 && blockIdx.y == 0, w0, w1);
 }
 
@@ -531,21 +581,20 @@ hipError_t launch_generate(const GenArgs &a, int fp64, hipStream_t s)
     const int64_t waves = (a.nblocks + a.R - 1) / a.R;
     const int64_t grid = (waves + kWaves - 1) / kWaves;
     const dim3 g((unsigned)grid, (unsigned)a.segs), b(kWG);
-    const bool mid = a.shift != nullptr;
+    const bool mid = a.shift != nullptr, wide = wide_exponent(a.S0, a.mu, a.vol, a.M);
     const size_t lds = gen_lds_bytes(a.seg_len);
-    if (a.what == 0) {
-        if (fp64) {
-            if (mid) hipLaunchKernelGGL((gen_kernel<double, 0, true>), g, b, lds, s, a, a.V, a.sched, a.shift);
-            else     hipLaunchKernelGGL((gen_kernel<double, 0, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
-        } else {
-            if (mid) hipLaunchKernelGGL((gen_kernel<float, 0, true>), g, b, lds, s, a, a.V, a.sched, a.shift);
-            else     hipLaunchKernelGGL((gen_kernel<float, 0, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
-        }
-    } else if (a.what == 1) {
-        hipLaunchKernelGGL((gen_kernel<float, 1, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
-    } else {
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, s, a, a.V, a.sched, a.shift); };
+    if (a.what == 1) {
+        go(gen_kernel<float, 1, false, false>);
+    } else if (a.what == 2) {
         // the normals are binary64 for both storage types
-        hipLaunchKernelGGL((gen_kernel<double, 2, false>), g, b, lds, s, a, a.V, a.sched, a.shift);
+        go(gen_kernel<double, 2, false, false>);
+    } else if (fp64) {
+        if (wide) mid ? go(gen_kernel<double, 0, true, true>) : go(gen_kernel<double, 0, false, true>);
+        else      mid ? go(gen_kernel<double, 0, true, false>) : go(gen_kernel<double, 0, false, false>);
+    } else {
+        if (wide) mid ? go(gen_kernel<float, 0, true, true>) : go(gen_kernel<float, 0, false, true>);
+        else      mid ? go(gen_kernel<float, 0, true, false>) : go(gen_kernel<float, 0, false, false>);
     }
     return hipGetLastError();
 }
@@ -556,8 +605,8 @@ hipError_t launch_generate(const GenArgs &a, int fp64, hipStream_t s)
 hipError_t preload_generate()
 {
     hipFuncAttributes fa;
-    hipError_t e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<float, 0, false>));
-    if (e == hipSuccess) e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<double, 0, false>));
+    hipError_t e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<float, 0, false, false>));
+    if (e == hipSuccess) e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&gen_kernel<double, 0, false, false>));
     return e;
 }
 
@@ -688,7 +737,7 @@ __device__ __forceinline__ GenArgs gen_args_of(const BatchOpt &o, const uint32_t
     return a;
 }
 
-template <typename T, bool MID>
+template <typename T, bool MID, bool WIDE>
 __global__ void __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4)))
 gen_batch_kernel(const BatchOpt *__restrict__ opts, const GenUnit *__restrict__ units,
                  const uint32_t *__restrict__ V, uint32_t *gsync)
@@ -702,7 +751,7 @@ gen_batch_kernel(const BatchOpt *__restrict__ opts, const GenUnit *__restrict__ 
     const int64_t per = (u.b1 - u.b0 + kWaves - 1) / kWaves;
     const int64_t w0 = u.b0 + (int64_t)(threadIdx.x >> 6) * per;
     const int64_t w1 = min(w0 + per, u.b1);
-    gen_body<T, 0, MID>(a, V, o.sched + (size_t)u.seg * o.seg_len, o.seg_len, MID ? o.shift : nullptr,
+    gen_body<T, 0, MID, WIDE>(a, V, o.sched + (size_t)u.seg * o.seg_len, o.seg_len, MID ? o.shift : nullptr,
                         u.b0 == 0 && u.seg == 0, w0, w1);
 }
 
@@ -712,13 +761,15 @@ hipError_t launch_generate_batch(const BatchOpt *opts, const GenUnit *units, int
 {
     const size_t lds = gen_lds_bytes(max_seg_len);
     const dim3 g(n_units), b(kWG);
-    if (shifted) {
-        // randomised QMC: every option of the batch carries its digital shift
-        if (fp64) hipLaunchKernelGGL((gen_batch_kernel<double, true>), g, b, lds, s, opts, units, V, gsync);
-        else      hipLaunchKernelGGL((gen_batch_kernel<float, true>), g, b, lds, s, opts, units, V, gsync);
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, s, opts, units, V, gsync); };
+    // shifted: randomised QMC, every option of the batch carries its digital shift
+    const bool f64 = fp64 & 1, wide = fp64 & kGenWide;
+    if (f64) {
+        if (wide) shifted ? go(gen_batch_kernel<double, true, true>) : go(gen_batch_kernel<double, false, true>);
+        else      shifted ? go(gen_batch_kernel<double, true, false>) : go(gen_batch_kernel<double, false, false>);
     } else {
-        if (fp64) hipLaunchKernelGGL((gen_batch_kernel<double, false>), g, b, lds, s, opts, units, V, gsync);
-        else      hipLaunchKernelGGL((gen_batch_kernel<float, false>), g, b, lds, s, opts, units, V, gsync);
+        if (wide) shifted ? go(gen_batch_kernel<float, true, true>) : go(gen_batch_kernel<float, false, true>);
+        else      shifted ? go(gen_batch_kernel<float, true, false>) : go(gen_batch_kernel<float, false, false>);
     }
     return hipGetLastError();
 }

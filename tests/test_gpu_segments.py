@@ -43,3 +43,20 @@ def test_batch_segments_equal_the_option_in_a_large_book(pricer):
         alone = pricer.price_batch(amq.make_options([opt]), b, dtype)
         mixed = pricer.price_batch(amq.make_options(big + [opt]), b, dtype)
         assert np.array_equal(np.asarray(alone)[0], np.asarray(mixed)[-1])
+
+
+@pytest.mark.parametrize("sigma,T,r", [(3.0, 100.0, 4.5), (20.0, 36.0, 200.0)])
+def test_paths_beyond_the_narrow_exponent(orc, pricer, sigma, T, r):
+    # deviations so large that log-prices may leave +-700: the exponential's
+    # general form.  The argument carries about 2e-16 of its terms (up to 10^4:
+    # drift and deviation cancel) from each of the five bridge levels on either
+    # side: 1e-11 relative on what is finite and normal
+    import paper_1205_0106_amd as amq
+    N, M = 2048, 16
+    kw = dict(S0=100.0, K=100.0, r=r, sigma=sigma, T=T)
+    got = np.asarray(amq.am_debug_generate(0, amq.make_params(**kw), N, M, "fp64"))
+    want = np.asarray(orc.paths(**kw, N=N, M=M))
+    ok = np.isfinite(want) & (want > 1e-300)
+    assert ok.mean() > 0.5
+    assert np.all(np.abs(got[ok] / want[ok] - 1.0) <= 1e-11)
+    assert np.array_equal(np.isinf(got), np.isinf(want))
