@@ -116,7 +116,8 @@ struct SweepArgs {
     int32_t is_call, allow_exercise, laguerre, degree;
     double S0, K;
     uint32_t spin_limit;
-    int32_t xcd_stride;       // every xcd_stride-th workgroup is a group (set by launch_sweep)
+    int32_t xcd_stride;       // > 1: every xcd_stride-th workgroup is a group; > 0: groups announce their XCD
+                              // (set by launch_sweep)
     double *rep_out;          // randomised QMC: replicate prices [n_rep] or nullptr
     int32_t rep, n_rep;
     double *host_out;         // pinned host copy of the result (put_host_result), or nullptr

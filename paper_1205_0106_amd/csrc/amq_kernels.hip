@@ -689,12 +689,15 @@ hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream
     // a plain launch: the grid is sized to what the device holds at once, and
     // the caller orders persistent sweeps on one device (a cooperative launch
     // measured 19 us slower per call, in the kernel's own event interval)
-    // few groups, in tiles that spin on the rows: all on one XCD, where its
-    // compute units hold one each
+    // few groups of a register-resident tile: all on one XCD, where its compute
+    // units hold one each; more of another tile are relayed, as dealt
     const uint32_t G = (uint32_t)a.G;
     const bool spin = row_words(a.degree) == 16 ? spins_on_rows<16>(G) : spins_on_rows<32>(G);
-    args.xcd_stride = spin && ppt * (fp64 ? 8 : 4) <= 64 && dyn > 0 && G * kXcds <= (uint32_t)cus ? (int)kXcds : 1;
-    return hipLaunchKernel(f, dim3((unsigned)(G * (uint32_t)args.xcd_stride)), dim3((unsigned)wg), params, (unsigned)dyn, s);
+    const bool keep = ppt * (fp64 ? 8 : 4) <= 64;
+    const bool strided = spin && keep && dyn > 0 && G * kXcds <= (uint32_t)cus;
+    args.xcd_stride = strided ? (int)kXcds : !spin && !keep && G <= kFlatMaxGroups ? 1 : 0;
+    const uint32_t grid = strided ? G * kXcds : G;
+    return hipLaunchKernel(f, dim3(grid), dim3((unsigned)wg), params, (unsigned)dyn, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -449,6 +449,15 @@ __device__ __forceinline__ void solve_date_wave(const double *tot, double *beta,
     }
 }
 
+// Whether this group's rows may stay in its L2 (in the first wave; false
+// elsewhere, which publishes nothing).
+template <int RW>
+__device__ __forceinline__ bool rows_stay_local(const SweepArgs &a, uint32_t gid)
+{
+    return a.xcd_stride > 0 && __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0 &&
+           xcd_local<RW>(a.rows, gid, (uint32_t)a.G, a.err, a.spin_limit);
+}
+
 // Register-resident tile (KEEP): the date's path values stay in registers
 // across the device-wide sum.  The Gram part of the next date's moments
 // depends only on that date's path values, so it is formed while this
@@ -574,7 +583,7 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         gt = split_sum_fetch<NG, 1, WG>(s_red2, cg);
     }
     // (the first wave publishes; the announcements have had the first pass to arrive)
-    const bool local = a.xcd_stride > 1 && tid < 64 && xcd_local<RW>(a.rows, G, a.err, a.spin_limit);
+    const bool local = rows_stay_local<RW>(a, gid);
 
     for (int k = M - 1; k >= 1; --k) {
         uint64_t stamp[3];
@@ -621,7 +630,7 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         else rt = group_sum<NB, 0, WG>(rs, s_red, cr);
         ++epoch;
         stamp[0] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG>(cr < (uint32_t)NB ? rt : gt, gid, G, a.rows, a.sync, a.err, epoch,
+        if (!allreduce_publish<NV, RW, WG, false>(cr < (uint32_t)NB ? rt : gt, gid, G, a.rows, a.sync, a.err, epoch,
                                            a.spin_limit, s_tot, s_red, s_flag, local)) {
             alive = false;
             return;
@@ -641,7 +650,8 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         if (k >= 2) gt = gram_pass(sn, xan, xbn, wbuf(k - 1));
         stamp[1] = record_clock(gid);
 
-        if (!gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, k >= 2,
+        if (!gather_and_solve<NV, RW, WG, false>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag,
+                                                  k >= 2,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
                                               if (tid == 0) {
@@ -714,6 +724,7 @@ __device__ __forceinline__ void sweep_stream(const SweepArgs &a, const T *__rest
     if (!(a.allow_exercise && a.M >= 2)) return;
     // date constants staged in LDS (a dependent global load at the top of
     // each date would stall the moment pass)
+    const bool local = rows_stay_local<RW>(a, gid);
     for (int k = tid; k <= a.M; k += WG) s_dc[k] = a.datec[k];
     __syncthreads();
     for (int k = a.M - 1; k >= 1; --k) {
@@ -750,9 +761,9 @@ __device__ __forceinline__ void sweep_stream(const SweepArgs &a, const T *__rest
         ++epoch;
         // (a clock read before group_sum would pin the moment pass's schedule)
         stamp[0] = stamp[1] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
-                                           s_flag) ||
-            !gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+        if (!allreduce_publish<NV, RW, WG, true>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+                                           s_flag, local) ||
+            !gather_and_solve<NV, RW, WG, true>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
                                               if (tid == 0) {
@@ -1066,6 +1077,7 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
         const float *row = S + (size_t)(M - 2) * ld;
         static_for<0, PF>([&](auto jc) { request(row, jc); });
     }
+    const bool local = rows_stay_local<RW>(a, gid);
     for (int k = M - 1; k >= 1; --k) {
         asm volatile("" : "+s"(wave_el));
         const double xa = dcc.xa, dk = dcc.disc;
@@ -1127,9 +1139,9 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
         const double at = group_sum<NV, 1, WG>(tv, s_red, tid == 0 ? (uint32_t)NV - 1u : (uint32_t)tid);
         ++epoch;
         stamp[0] = stamp[1] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
-                                           s_flag) ||
-            !gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+        if (!allreduce_publish<NV, RW, WG, true>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+                                           s_flag, local) ||
+            !gather_and_solve<NV, RW, WG, true>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
                                               solve_date_wave<D>(s_tot, s_beta, s_L);
@@ -1349,6 +1361,7 @@ __device__ __forceinline__ void sweep_slab(const SweepArgs &a, const T *__restri
         const T *row = S + (size_t)(M - 2) * ld;
         units([&](auto pc) { request(row, pc); });
     }
+    const bool local = rows_stay_local<RW>(a, gid);
     for (int k = M - 1; k >= 1; --k) {
         asm volatile("" : "+s"(wave_el));
         const double xa = dcc.xa, dk = dcc.disc;
@@ -1382,9 +1395,9 @@ __device__ __forceinline__ void sweep_slab(const SweepArgs &a, const T *__restri
         const double at = group_sum<NV, 1, WG>(tv, s_red, tid == 0 ? (uint32_t)NV - 1u : (uint32_t)tid);
         ++epoch;
         stamp[0] = stamp[1] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
-                                           s_flag) ||
-            !gather_and_solve<NV, RW, WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+        if (!allreduce_publish<NV, RW, WG, true>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+                                           s_flag, local) ||
+            !gather_and_solve<NV, RW, WG, true>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
                                               if (tid == 0) {
@@ -1504,7 +1517,7 @@ __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, ui
                                             double (*s_red)[32], double *s_tot, int *s_flag)
 {
     constexpr int VW = 16 / sizeof(T), NVEC = PPT / VW;
-    constexpr bool SLAB = Slab<T, PPT, LAG>::on;
+    constexpr bool SLAB = Slab<T, PPT, LAG>::on, RELAY = !SweepShape<T, PPT>::KEEP;
     constexpr uint32_t JS = (SLAB ? WG : 64) * VW;
     const int tid = threadIdx.x;
     const int64_t N = a.N;
@@ -1535,10 +1548,10 @@ __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, ui
     const double ft = group_sum<2, 0, WG>(fin, s_red, (uint32_t)tid);
     ++epoch;
     const uint32_t G = (uint32_t)a.G;
-    if (!allreduce_publish<2, row_words(D), WG>(ft, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+    if (!allreduce_publish<2, row_words(D), WG, RELAY>(ft, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
                                                 s_flag) ||
-        !gather_and_solve<2, row_words(D), WG>(G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag,
-                                               false, []() {}))
+        !gather_and_solve<2, row_words(D), WG, RELAY>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+                                               []() {}))
         return;
     if (gid == 0) {
         if (tid == 0) {
@@ -1598,8 +1611,8 @@ sweep_kernel(SweepArgs a, const T *__restrict__ S)
     __shared__ SweepLds<T, PPT, LAG, WG> L;
 
     if (a.xcd_stride > 1 && blockIdx.x % (uint32_t)a.xcd_stride != 0) return;   // (another XCD's group)
-    const uint32_t gid = blockIdx.x / (uint32_t)a.xcd_stride;
-    if (a.xcd_stride > 1) xcd_announce<row_words(D)>(a.rows, gid, (uint32_t)a.G);
+    const uint32_t gid = a.xcd_stride > 1 ? blockIdx.x / (uint32_t)a.xcd_stride : blockIdx.x;
+    if (a.xcd_stride > 0) xcd_announce<row_words(D)>(a.rows, gid, (uint32_t)a.G);
     const uint32_t e0 = tile_e0<T, PPT, WG>(gid);
     T pv[PPT];
     uint32_t epoch = 0, skipped = 0;
@@ -1630,7 +1643,7 @@ __device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, uint32_t *e
     a.laguerre = LAG; a.degree = D;
     a.S0 = o.S0; a.K = o.K;
     a.spin_limit = spin_limit;
-    a.xcd_stride = 1;
+    a.xcd_stride = 0;
     a.rep_out = nullptr; a.rep = 0; a.n_rep = 0;
     a.host_out = nullptr;
     const uint32_t gid = (uint32_t)(t - o.tile_base);

@@ -273,22 +273,27 @@ __device__ void reduce_partials(const double *part, uint32_t G, double *tot, dou
 // of `rows` ([2][G][RW]).  Lanes of the first wave store the group's NV partials there with
 // single-copy-atomic 8-byte stores, the two lowest mantissa bits of each word
 // replaced by epoch & 3 (a change of at most 3 units in the last place, the
-// same in every run).  With few groups (spins_on_rows) wave 0 reads all rows
-// until every word carries the tag.  Otherwise thread 0 bumps its team's
-// arrival counter, and wave 0 polls the
-// team counters until the epoch is complete; then the whole group reads every
-// row (lane c of each RW-lane slice reads word c, all loads of a batch issued
-// before any is used), checks that every word carries this epoch's tag
-// (re-reading if a store had not yet landed: the counter is only a hint, so no
-// store needs to drain before it), and sums in a fixed order: each thread its
-// rows in ascending order, then the lanes and waves of the group in a fixed
-// tree.  Every group computes bitwise the same total.
-//
-// Above kFlatMaxGroups groups (every group reading every row would move
-// G^2 rows per date), the last arriver of each team (from its counter's
-// return value) first sums its team's rows in member order into a tagged
-// team row; every group then polls the team rows' tags and sums the team
-// rows in team order.
+// same in every run).  A reader reads rows until every word carries this
+// epoch's tag (no store needs to drain before another), then adds them in a
+// fixed order.  Three forms by group count:
+//  - few groups (spins_on_rows): the first wave of every group reads all rows;
+//  - up to kFlatMaxGroups, in tiles with work to do behind the exchange
+//    (register-resident; RELAY false): flat.  Thread 0 bumps its team's arrival
+//    counter with the row; behind the overlapped work the whole group reads
+//    every row at once, and only on a miss waits for the counters;
+//  - up to kFlatMaxGroups, in other tiles (RELAY): relayed.  Group g belongs to
+//    team g mod kXcds, on one XCD where workgroups are dealt to XCDs in turn;
+//    the first member (group t of team t) adds its team's rows, up to 32 and
+//    from its own L2, and publishes a team row; every group reads the kXcds
+//    team rows.  One round trip inside an XCD and one through memory, where the
+//    flat form takes two through memory and 8 MB of reads a date (245 groups x
+//    60 dates 1103 us per call flat, 995 relayed; 2^24 x 252 15.28 and 14.9 ms;
+//    but register-resident, 256 groups x 100 dates, 778 flat and 814 relayed:
+//    the first round trip is hidden there, the relay's turn is not);
+//  - above: teams of consecutive groups; a team's last arriver (its arrival
+//    counter's return value) sums the team's rows, every group then polls and
+//    sums the team rows.
+// Every group computes bitwise the same total.
 //
 // Two parities suffice: a group writes the parity of epoch e + 2 only after
 // epoch e + 1 is complete, and every group finished reading epoch e before
@@ -401,29 +406,26 @@ __device__ __forceinline__ void put_row(uint64_t *row, double v, uint64_t tag, b
     }
 }
 
-// Groups at or below this count read every group's row; above it, teams sum
-// first (see allreduce).
-constexpr uint32_t kFlatMaxGroups = 256;
-
 // Words of all rows (G x RW) up to which one wave reads every row in one go
-// and spins on the tags themselves (spin_rows): eight loads per lane.  No
-// arrival counters are kept then: waiting on a counter and reading the rows
-// after it is one memory round trip more per date, which is most of a date
+// and spins on the tags themselves (spin_rows): eight loads per lane.  With
+// arrival counters, waiting on a counter and reading the rows
+// after it was one memory round trip more per date, which is most of a date
 // with few groups: 15 groups x 365 dates (30011 paths, binary32) 1554 -> 1340
 // us per call, 16 groups x 50 dates 217 -> 194 us, a book of 12 options 3861
-// -> 3037 us.  Above it the whole group reads the rows, and spinning on
-// them all would load the memory that the late groups still stream from.
+// -> 3037 us.
 constexpr uint32_t kSpinWords = 512;
+constexpr uint32_t kXcds = 8;
+constexpr uint32_t kFlatMaxGroups = 32 * kXcds;
 template <int RW> __host__ __device__ __forceinline__ bool spins_on_rows(uint32_t G) { return G * (uint32_t)RW <= kSpinWords; }
 
-// Publishing half of allreduce: the first wave's lanes store the group's row
-// (lane c: word c), and thread 0 bumps its team's counter (not where the
-// gathering half spins on the rows); above kFlatMaxGroups the team's last
-// arriver also sums its team's rows into the team row.  The caller may do independent work
-// before the gathering half (allreduce_gather) with the same epoch.  Uses
-// s_flag[1 + WG / 64] (the team-last flag), so that the gathering half's
-// flags never overlap it.
-template <int NV, int RW, int WG = kWG>
+// Publishing half of the sum: the first wave's lanes store the group's row
+// (lane c: word c); where counters are kept (flat, and above kFlatMaxGroups)
+// thread 0 bumps its team's, and above kFlatMaxGroups the team's last arriver
+// also sums its team's rows into the team row.
+// The caller may do independent work before the gathering half with the same
+// epoch.  Uses s_flag[1 + WG / 64] (the team-last flag), so that the
+// gathering half's flags never overlap it.  local: see put_row.
+template <int NV, int RW, int WG, bool RELAY>
 __device__ inline bool allreduce_publish(double v, uint32_t gid, uint32_t G, uint64_t *rows,
                                          uint32_t *words, uint32_t *err, uint32_t epoch, uint32_t limit,
                                          double *tot, double (*s_red)[32], int *s_flag, bool local = false)
@@ -432,47 +434,46 @@ __device__ inline bool allreduce_publish(double v, uint32_t gid, uint32_t G, uin
     static_assert(NV <= RW && RW <= 32 && (RW & (RW - 1)) == 0, "row width");
     const uint64_t tag = epoch & 3u;
     uint64_t *slots = rows + (size_t)(epoch & 1u) * G * RW;
+    put_row<NV>(slots + (size_t)gid * RW, v, tag, local);
+    if (spins_on_rows<RW>(G) || (RELAY && G <= kFlatMaxGroups)) return true;
     uint64_t *tslots = rows + (size_t)2 * G * RW + (size_t)(epoch & 1u) * kMaxTeams * RW;
     const uint32_t TS = team_size(G);
     const uint32_t tau = gid / TS;
-    const bool flat = G <= kFlatMaxGroups;
-    put_row<NV>(slots + (size_t)gid * RW, v, tag, local);
-    if (spins_on_rows<RW>(G)) return true;
-    if (flat) {
+    if (G <= kFlatMaxGroups) {
         // the counter's old value is not used: nothing waits for the round trip
         if (tx == 0)
             (void)__hip_atomic_fetch_add(words + kSyncLine * (1 + tau), 1u, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        // team level: the team's last arriver sums its team's rows in member
-        // order and publishes the team row (tagged like the group rows)
-        if (tx == 0) {
-            const uint32_t old = __hip_atomic_fetch_add(words + kSyncLine * (1 + tau), 1u, __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
-            s_flag[1 + WG / 64] = old + 1u == epoch * min(TS, G - tau * TS) ? 1 : 0;
-        }
-        __syncthreads();
-        if (s_flag[1 + WG / 64]) {
-            const uint32_t first = tau * TS;
-            if (!sum_rows<NV, RW, WG>(slots + (size_t)first * RW, min(TS, G - first), tag, err, limit, tot, s_red,
-                                      s_flag, [&](uint32_t) { return rows_backoff(err, s_flag); }))
-                return false;
-            put_row<NV>(tslots + (size_t)tau * RW, tx < (uint32_t)NV ? tot[tx] : 0.0, tag);
-        }
+        return true;
+    }
+    // team level: the team's last arriver sums its team's rows in member
+    // order and publishes the team row (tagged like the group rows)
+    if (tx == 0) {
+        const uint32_t old = __hip_atomic_fetch_add(words + kSyncLine * (1 + tau), 1u, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        s_flag[1 + WG / 64] = old + 1u == epoch * min(TS, G - tau * TS) ? 1 : 0;
+    }
+    __syncthreads();
+    if (s_flag[1 + WG / 64]) {
+        const uint32_t first = tau * TS;
+        if (!sum_rows<NV, RW, WG>(slots + (size_t)first * RW, min(TS, G - first), tag, err, limit, tot, s_red,
+                                  s_flag, [&](uint32_t) { return rows_backoff(err, s_flag); }))
+            return false;
+        put_row<NV>(tslots + (size_t)tau * RW, tx < (uint32_t)NV ? tot[tx] : 0.0, tag);
     }
     return true;
 }
 
-// Gathering half for few groups (spins_on_rows), by the first wave alone:
-// reads every row until each word carries the epoch's tag, then adds them in
-// exactly sum_rows' order (thread rs + 64 / RW wave of the group there is
-// lane rs of step `wave` here), so the totals are bitwise the same.  tot: LDS
-// [>= NV], written by lanes 0..NV-1.  NL: loads per lane (G RW <= 64 NL).
+// Reads `count` rows, `stride` words apart, until each word carries the
+// epoch's tag, by the first wave alone, then adds them in exactly sum_rows'
+// order (thread rs + 64 / RW wave of the group there is lane rs of step
+// `wave` here), so the totals are bitwise the same.  NL: loads per lane
+// (count RW <= 64 NL).  t: the total of component `lane` in lanes 0..NV-1.
 // Returns false (in every lane) when the wait runs out or another group
 // raised the error word.
 template <int NV, int RW, int WG, int NL>
-__device__ __forceinline__ bool spin_rows_n(const uint64_t *slots, uint32_t G, uint64_t tag, uint32_t *err,
-                                            uint32_t limit, double *tot)
+__device__ __forceinline__ bool spin_rows(const uint64_t *slots, uint32_t stride, uint32_t count, uint64_t tag,
+                                          uint32_t *err, uint32_t limit, double &t)
 {
     constexpr int NW = WG / 64;
     constexpr uint32_t RL = 64 / RW;    // rows per step
@@ -484,8 +485,8 @@ __device__ __forceinline__ bool spin_rows_n(const uint64_t *slots, uint32_t G, u
         // rows past the last read the last again (its tag is waited for anyway)
 #pragma unroll
         for (int j = 0; j < NL; ++j)
-            w[j] = __hip_atomic_load(slots + (size_t)min((uint32_t)j * RL + sub, G - 1u) * RW + c, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
+            w[j] = __hip_atomic_load(slots + (size_t)min((uint32_t)j * RL + sub, count - 1u) * stride + c,
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t raised = ld_agent(err);
         bool bad = false;
 #pragma unroll
@@ -497,58 +498,82 @@ __device__ __forceinline__ bool spin_rows_n(const uint64_t *slots, uint32_t G, u
             return false;
         }
     }
-    double t = 0.0;
+    t = 0.0;
 #pragma unroll
     for (int q = 0; q < NW && q < NL; ++q) {
         double acc = 0.0;
 #pragma unroll
         for (int j = q; j < NL; j += NW)
-            acc += (uint32_t)j * RL + sub < G ? __longlong_as_double((long long)(w[j] & ~3ull)) : 0.0;
+            acc += (uint32_t)j * RL + sub < count ? __longlong_as_double((long long)(w[j] & ~3ull)) : 0.0;
         if (RW == 16) acc = add_rows16(acc);
         t += add_halves32(acc);
+    }
+    return true;
+}
+
+// The totals of `epoch` where rows are spun on or relayed, by the first wave
+// alone.  tot: LDS [>= NV], written by lanes 0..NV-1.
+template <int NV, int RW, int WG, bool RELAY>
+__device__ __forceinline__ bool first_wave_totals(uint64_t *rows, uint32_t gid, uint32_t G, uint32_t *err,
+                                                  uint32_t epoch, uint32_t limit, double *tot)
+{
+    const uint64_t tag = epoch & 3u;
+    const uint64_t *slots = rows + (size_t)(epoch & 1u) * G * RW;
+    const uint32_t lane = tid_x() & 63u;
+    double t = 0.0;
+    if (spins_on_rows<RW>(G)) {
+        const bool ok = G * (uint32_t)RW <= kSpinWords / 2
+                            ? spin_rows<NV, RW, WG, 4>(slots, RW, G, tag, err, limit, t)
+                            : spin_rows<NV, RW, WG, 8>(slots, RW, G, tag, err, limit, t);
+        if (!ok) return false;
+    } else if constexpr (RELAY) {
+        uint64_t *tslots = rows + (size_t)2 * G * RW + (size_t)(epoch & 1u) * kMaxTeams * RW;
+        if (gid < kXcds) {
+            if (!spin_rows<NV, RW, WG, RW / 2>(slots + (size_t)gid * RW, kXcds * RW, (G - gid + kXcds - 1) / kXcds, tag,
+                                               err, limit, t))
+                return false;
+            put_row<NV>(tslots + (size_t)gid * RW, t, tag);
+        }
+        if (!spin_rows<NV, RW, WG, (int)kXcds * RW / 64>(tslots, RW, kXcds, tag, err, limit, t)) return false;
     }
     if (lane < (uint32_t)NV) tot[lane] = t;
     return true;
 }
 
-template <int NV, int RW, int WG>
-__device__ __forceinline__ bool spin_rows(uint64_t *rows, uint32_t G, uint32_t *err, uint32_t epoch, uint32_t limit,
-                                          double *tot)
-{
-    const uint64_t tag = epoch & 3u;
-    const uint64_t *slots = rows + (size_t)(epoch & 1u) * G * RW;
-    return G * (uint32_t)RW <= kSpinWords / 2 ? spin_rows_n<NV, RW, WG, 4>(slots, G, tag, err, limit, tot)
-                                              : spin_rows_n<NV, RW, WG, 8>(slots, G, tag, err, limit, tot);
-}
-
-// One XCD for few groups.  The device deals a launch's workgroups out to its
-// XCDs in turn, so of kXcds times the groups every kXcds-th lands on one XCD
-// and the others exit at once.  That placement is not relied on: each group
-// announces the XCD it runs on (hardware register XCC_ID; in the rows' team
-// words, zeroed with them, device scope), and only where all agree do the
-// rows stay in that XCD's L2 (xcd_local, by the first wave, every group the
-// same answer).  Readers use device-scope loads either way.  Between groups on
-// different XCDs a published row takes a round trip through memory: 1.07 us
+// Which stores may stop in an L2.  The device deals a launch's workgroups out
+// to its XCDs in turn.  With few groups, kXcds times as many are launched and
+// every kXcds-th, all on one XCD, is kept; with more, a relayed team is one
+// XCD's.  That placement is not relied on: groups announce the XCD they run on
+// (hardware register XCC_ID; past the team rows, zeroed with them, device
+// scope), and a group's rows stay in its L2 only where all readers are there
+// too: every group (spins_on_rows; all give the same answer), or its team's
+// first (relayed).  Readers use device-scope loads either way.  Between groups
+// on different XCDs a published row takes a round trip through memory: 1.07 us
 // per exchange of 16 groups, 0.44 on one XCD (measured alone).
-constexpr uint32_t kXcds = 8;
-
 __device__ __forceinline__ uint64_t own_xcd()
 {
     return 1ull + (uint64_t)(__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xFFu);   // XCC_ID, whole register
 }
 
 template <int RW>
-__device__ __forceinline__ void xcd_announce(uint64_t *rows, uint32_t gid, uint32_t G)
+__device__ __forceinline__ uint64_t *xcd_words(uint64_t *rows, uint32_t G)
 {
-    if (tid_x() == 0)
-        __hip_atomic_store(rows + (size_t)2 * G * RW + gid, own_xcd(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return rows + (size_t)2 * G * RW + (size_t)kXcds * RW;
 }
 
 template <int RW>
-__device__ __forceinline__ bool xcd_local(const uint64_t *rows, uint32_t G, uint32_t *err, uint32_t limit)
+__device__ __forceinline__ void xcd_announce(uint64_t *rows, uint32_t gid, uint32_t G)
+{
+    if (tid_x() == 0 && gid < (spins_on_rows<RW>(G) ? G : kXcds))
+        __hip_atomic_store(xcd_words<RW>(rows, G) + gid, own_xcd(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Call with every lane of the first wave.
+template <int RW>
+__device__ __forceinline__ bool xcd_local(uint64_t *rows, uint32_t gid, uint32_t G, uint32_t *err, uint32_t limit)
 {
     const uint32_t lane = tid_x() & 63u;
-    const uint64_t *w = rows + (size_t)2 * G * RW + min(lane, G - 1u);
+    const uint64_t *w = xcd_words<RW>(rows, G) + (spins_on_rows<RW>(G) ? min(lane, G - 1u) : gid % kXcds);
     uint64_t x = 0;
     for (uint32_t it = 0;;) {
         x = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -578,10 +603,10 @@ __device__ __forceinline__ void wave_lds_fence()
 // work since publishing, so the rows usually all carry the tag already) the
 // rows are read once before the counters, which saves their round trip.
 // Teams: wave 0 waits on the team rows' tags, then the team rows are summed.
-template <int NV, int RW, int WG = kWG, typename Work = Nothing>
+template <int NV, int RW, int WG, typename Work>
 __device__ inline bool allreduce_gather(uint32_t G, uint64_t *rows, uint32_t *words, uint32_t *err,
                                         uint32_t epoch, uint32_t limit, double *tot, double (*s_red)[32],
-                                        int *s_flag, bool rows_first = false, Work meanwhile = Work())
+                                        int *s_flag, bool rows_first, Work meanwhile)
 {
     const uint32_t tx = tid_x();
     const uint64_t tag = epoch & 3u;
@@ -631,30 +656,30 @@ __device__ inline bool allreduce_gather(uint32_t G, uint64_t *rows, uint32_t *wo
 // Gathering half with the follow-up work `solve` (the first wave only, on the
 // totals in LDS): one group barrier between the totals and the group's use of
 // what `solve` left in LDS.  s_flag[0] carries the outcome.  meanwhile():
-// work that needs no total and in which, where rows are spun on, the first
-// wave has no part: the other waves do it while the first spins.
-template <int NV, int RW, int WG, typename Solve, typename Work = Nothing>
-__device__ inline bool gather_and_solve(uint32_t G, uint64_t *rows, uint32_t *words, uint32_t *err, uint32_t epoch,
-                                        uint32_t limit, double *tot, double (*s_red)[32], int *s_flag,
+// work that needs no total and in which, where rows are spun on or relayed,
+// the first wave has no part: the other waves do it while the first waits.
+template <int NV, int RW, int WG, bool RELAY, typename Solve, typename Work = Nothing>
+__device__ inline bool gather_and_solve(uint32_t gid, uint32_t G, uint64_t *rows, uint32_t *words, uint32_t *err,
+                                        uint32_t epoch, uint32_t limit, double *tot, double (*s_red)[32], int *s_flag,
                                         bool rows_first, Solve solve, Work meanwhile = Work())
 {
     const uint32_t tx = tid_x();
-    const bool spin = spins_on_rows<RW>(G);
-    if (!spin && !allreduce_gather<NV, RW, WG>(G, rows, words, err, epoch, limit, tot, s_red, s_flag, rows_first,
-                                               meanwhile))
+    const bool one = spins_on_rows<RW>(G) || (RELAY && G <= kFlatMaxGroups);
+    if (!one && !allreduce_gather<NV, RW, WG>(G, rows, words, err, epoch, limit, tot, s_red, s_flag, rows_first,
+                                              meanwhile))
         return false;
     if (tx < 64) {
-        const bool ok = !spin || spin_rows<NV, RW, WG>(rows, G, err, epoch, limit, tot);
+        const bool ok = !one || first_wave_totals<NV, RW, WG, RELAY>(rows, gid, G, err, epoch, limit, tot);
         if (ok) {
             wave_lds_fence();
             solve();
         }
-        if (spin && tx == 0) s_flag[0] = ok ? 1 : 0;
-    } else if (spin) {
+        if (one && tx == 0) s_flag[0] = ok ? 1 : 0;
+    } else if (one) {
         meanwhile();
     }
     __syncthreads();
-    return !spin || s_flag[0] != 0;
+    return !one || s_flag[0] != 0;
 }
 
 }  // namespace amq

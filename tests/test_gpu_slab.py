@@ -78,3 +78,22 @@ def test_mixed_storage_book(orc, pricer):
         want = orc.price_american(**KW, K=specs[2]["K"], N=sizes[2], M=specs[2]["n_dates"], kind=orc.MONOMIAL,
                                   degree=degree, is_call=specs[2]["is_call"])
         assert abs(got[2, 0] - want.price) <= TOL["fp64"]
+
+
+# one unit a group: just past the rows that one wave reads whole (32 groups of
+# 16-word rows, 16 of 32-word ones), uneven and even teams, the most relayed
+@pytest.mark.parametrize("groups,degree", [(33, 2), (40, 3), (64, 2), (255, 1), (256, 2), (17, 5), (33, 6)])
+def test_relayed_sum(orc, pricer, groups, degree):
+    import paper_1205_0106_amd as amq
+    N, M, K = groups * 4096 - 11, 4, 103.0
+    p, b = amq.make_params(**KW, K=K, is_call=False), amq.make_basis("monomial", degree)
+    print(f"  relay: groups={groups} d={degree}", flush=True)
+    amq.am_debug_set_sweep_tile(512, 32)
+    try:
+        price, se = pricer.price(p, N, M, b, "fp64")
+        assert pricer.price(p, N, M, b, "fp64") == (price, se)
+    finally:
+        amq.am_debug_set_sweep_tile(0, 0)
+    want = orc.price_american(**KW, K=K, N=N, M=M, kind=orc.MONOMIAL, degree=degree)
+    assert abs(price - want.price) <= TOL["fp64"]
+    assert abs(se - want.std_err) <= TOL["fp64"]
