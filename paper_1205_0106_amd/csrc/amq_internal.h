@@ -172,8 +172,16 @@ struct GenUnit {              // one generation workgroup: blocks [b0, b1) of op
     int64_t b0, b1;
 };
 
+// Claim queues of a batch sweep: a workgroup claims from queue blockIdx mod
+// kClaimQueues first (the device deals workgroups out to its XCDs in turn, so
+// an option's tiles run on one XCD and exchange within its L2), from the
+// others once that is empty.
+constexpr int kClaimQueues = 8;
+
 struct BatchGlobal {
-    uint32_t *claim;          // tile claim counter (zeroed by generation)
+    uint32_t *claim;          // claim counters [queues] (zeroed by generation)
+    int32_t queues;           // kClaimQueues or 1
+    int32_t q_off[kClaimQueues + 1];   // queue q: tiles q_off[q] .. q_off[q + 1] - 1 of the list
     uint32_t *err;            // error word (zeroed by generation)
     int32_t total_tiles, laguerre;
     uint32_t spin_limit, pad;

@@ -704,14 +704,11 @@ hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream
 // Batches: many options with uneven path and date counts in two launches.
 //
 // Generation: each workgroup owns a block range of one option (unit table
-// built on the host).  Sweep: one cooperative persistent grid; workgroups
-// claim (option, tile) slots from a global counter in a fixed order (options
-// by decreasing work, each option's tiles contiguous), run that tile through
+// built on the host).  Sweep: one persistent grid; workgroups
+// claim (option, tile) slots from one or several queues in a fixed order (options
+// by decreasing work, each option's tiles contiguous; see claim_tile), run that tile through
 // all of the option's dates with the option's own barrier words and partial
-// slots, then claim again.  Claims are in order, so at most one option is
-// partly claimed at any time and every earlier option can finish; with each
-// option needing no more tiles than the grid holds, every claimed tile is
-// eventually joined by the rest of its option.  An option's result depends
+// slots, then claim again.  An option's result depends
 // only on its own tiles and the fixed reduction order, not on which group ran
 // which tile, so it is the same alone and in any mix.
 // ---------------------------------------------------------------------------

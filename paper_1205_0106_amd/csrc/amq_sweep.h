@@ -1625,7 +1625,7 @@ sweep_kernel(SweepArgs a, const T *__restrict__ S)
 // One claimed tile of a batch: the option's whole backward sweep on this
 // group's paths.  Returns false when a wait ran out.
 template <typename T, int PPT, int D, bool LAG>
-__device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, uint32_t *err, uint32_t spin_limit,
+__device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, int queues, uint32_t *err, uint32_t spin_limit,
                                            SweepLds<T, PPT, LAG, kWG> &L)
 {
     SweepArgs a;
@@ -1643,10 +1643,13 @@ __device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, uint32_t *e
     a.laguerre = LAG; a.degree = D;
     a.S0 = o.S0; a.K = o.K;
     a.spin_limit = spin_limit;
-    a.xcd_stride = 0;
+    const uint32_t G = (uint32_t)o.G;
+    const bool shared = spins_on_rows<row_words(D)>(G) || (!SweepShape<T, PPT>::KEEP && G <= kFlatMaxGroups);
+    a.xcd_stride = queues > 1 && shared ? 1 : 0;   // an option's groups mostly share an XCD
     a.rep_out = nullptr; a.rep = 0; a.n_rep = 0;
     a.host_out = nullptr;
     const uint32_t gid = (uint32_t)(t - o.tile_base);
+    if (a.xcd_stride > 0) xcd_announce<row_words(D)>(a.rows, gid, (uint32_t)a.G);
     const uint32_t e0 = tile_e0<T, PPT, kWG>(gid);
     T pv[PPT];
     uint32_t epoch = 0, skipped = 0;
@@ -1657,15 +1660,31 @@ __device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, uint32_t *e
     return alive;
 }
 
-// The next tile of a batch in claim order, or total_tiles (none left, or a
-// wait ran out somewhere); wave-uniform, so the descriptor and everything
-// derived from it live in scalar registers.
+// The next tile of a batch, or total_tiles (none left, or a wait ran out
+// somewhere); wave-uniform, so the descriptor and everything derived from it
+// live in scalar registers.  Tiles of a queue are claimed in order and an
+// option's are contiguous, so a queue has at most one partly claimed option;
+// its own groups (at least as many as any of its options has tiles) leave it
+// only when every tile is claimed, so that option is always joined by the rest
+// of its groups, whoever else helps.
 __device__ __forceinline__ int claim_tile(const BatchGlobal &g, int *s_claim)
 {
     __syncthreads();
     if (threadIdx.x == 0) {
-        int t = (int)__hip_atomic_fetch_add(g.claim, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (ld_agent(g.err) != 0u || (g.err64 && ld_agent(g.err64) != 0u)) t = g.total_tiles;
+        int t = g.total_tiles;
+        if (ld_agent(g.err) == 0u && !(g.err64 && ld_agent(g.err64) != 0u)) {
+            for (int i = 0; i < g.queues; ++i) {
+                const int q = (int)(blockIdx.x + (uint32_t)i) % g.queues;
+                const int n = g.q_off[q + 1] - g.q_off[q];
+                // (an empty queue's counter is not counted up for ever)
+                if ((int)ld_agent(g.claim + q) >= n) continue;
+                const int c = (int)__hip_atomic_fetch_add(g.claim + q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (c < n) {
+                    t = g.q_off[q] + c;
+                    break;
+                }
+            }
+        }
         *s_claim = t;
     }
     __syncthreads();
@@ -1683,7 +1702,7 @@ sweep_batch_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
     for (;;) {
         const int t = claim_tile(g, &s_claim);
         if (t >= g.total_tiles) return;
-        if (!batch_tile<T, PPT, D, LAG>(opts[tile_opt[t]], t, g.err, g.spin_limit, L)) return;
+        if (!batch_tile<T, PPT, D, LAG>(opts[tile_opt[t]], t, g.queues, g.err, g.spin_limit, L)) return;
     }
 }
 
@@ -1705,9 +1724,9 @@ sweep_mixed_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
         if (t >= g.total_tiles) return;
         const int32_t e = __builtin_amdgcn_readfirstlane(tile_opt[t]);
         if (e < 0) {
-            if (!batch_tile<double, PPT64, D, false>(g.opts64[e & 0x7FFFFFFF], t, g.err64, g.spin_limit, L.d)) return;
+            if (!batch_tile<double, PPT64, D, false>(g.opts64[e & 0x7FFFFFFF], t, g.queues, g.err64, g.spin_limit, L.d)) return;
         } else {
-            if (!batch_tile<float, PPT32, D, false>(opts[e], t, g.err, g.spin_limit, L.f)) return;
+            if (!batch_tile<float, PPT32, D, false>(opts[e], t, g.queues, g.err, g.spin_limit, L.f)) return;
         }
     }
 }
