@@ -694,7 +694,7 @@ hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream
     const uint32_t G = (uint32_t)a.G;
     const bool spin = row_words(a.degree) == 16 ? spins_on_rows<16>(G) : spins_on_rows<32>(G);
     const bool keep = ppt * (fp64 ? 8 : 4) <= 64;
-    const bool strided = spin && keep && dyn > 0 && G * kXcds <= (uint32_t)cus;
+    const bool strided = G > 1 && spin && keep && dyn > 0 && G * kXcds <= (uint32_t)cus;
     args.xcd_stride = strided ? (int)kXcds : !spin && !keep && G <= kFlatMaxGroups ? 1 : 0;
     const uint32_t grid = strided ? G * kXcds : G;
     return hipLaunchKernel(f, dim3(grid), dim3((unsigned)wg), params, (unsigned)dyn, s);

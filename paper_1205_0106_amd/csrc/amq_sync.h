@@ -433,6 +433,12 @@ __device__ inline bool allreduce_publish(double v, uint32_t gid, uint32_t G, uin
     const uint32_t tx = tid_x();
     static_assert(NV <= RW && RW <= 32 && (RW & (RW - 1)) == 0, "row width");
     const uint64_t tag = epoch & 3u;
+    if (G == 1) {
+        // alone: the group's sums are the totals (rounded as a row's words are)
+        if (tx < (uint32_t)NV)
+            tot[tx] = __longlong_as_double((long long)((uint64_t)__double_as_longlong(v) & ~3ull));
+        return true;
+    }
     uint64_t *slots = rows + (size_t)(epoch & 1u) * G * RW;
     put_row<NV>(slots + (size_t)gid * RW, v, tag, local);
     if (spins_on_rows<RW>(G) || (RELAY && G <= kFlatMaxGroups)) return true;
@@ -517,6 +523,7 @@ template <int NV, int RW, int WG, bool RELAY>
 __device__ __forceinline__ bool first_wave_totals(uint64_t *rows, uint32_t gid, uint32_t G, uint32_t *err,
                                                   uint32_t epoch, uint32_t limit, double *tot)
 {
+    if (G == 1) return true;   // (published straight into tot)
     const uint64_t tag = epoch & 3u;
     const uint64_t *slots = rows + (size_t)(epoch & 1u) * G * RW;
     const uint32_t lane = tid_x() & 63u;
