@@ -251,8 +251,8 @@ struct DevState {
     void *ws = nullptr;
     size_t ws_bytes = 0;
     std::map<long, int> occ;                        // (kind, fp64, wg, ppt, degree) -> groups per CU
-    // single-option sweeps hold every CU for their whole run and wait on one
-    // another's groups only within their own grid: launches on different
+    // single-option sweeps and whole-device batches hold every CU for their whole
+    // run and wait on one another's groups only within their own grid: launches on different
     // streams are ordered through this event, in enqueue order, so two never
     // share the device
     std::mutex persist_mu;
@@ -509,6 +509,26 @@ int prof_slot(ProfRec **out)
     return AM_OK;
 }
 
+// Launch a sweep that holds the device for its whole run, after the persistent
+// sweeps that other streams have enqueued (see DevState).  *e: the launch's
+// own outcome.  create: the ordering event may be created here.
+template <typename Launch>
+int launch_persistent(DevState *st, hipStream_t stream, bool create, Launch launch, hipError_t *e)
+{
+    std::lock_guard<std::mutex> lk(st->persist_mu);
+    if (!st->persist_done) {
+        if (!create) return fail(AM_EINVAL, "am_init has not run on this device");
+        HIP_TRY(hipEventCreateWithFlags(&st->persist_done, hipEventDisableTiming));
+    } else if (st->persist_stream != stream)
+        HIP_TRY(hipStreamWaitEvent(stream, st->persist_done, 0));
+    *e = launch();
+    if (*e == hipSuccess) {
+        HIP_TRY(hipEventRecord(st->persist_done, stream));
+        st->persist_stream = stream;
+    }
+    return AM_OK;
+}
+
 // Enqueue both kernels; result stays in the workspace.
 // noalloc_seg, noalloc_sched: the allocation-free entry point passes the
 // schedule and where in its scratch memory it placed the variant that this
@@ -581,20 +601,10 @@ int enqueue(DevState *st, const am_params *p, int64_t N, int32_t M, am_basis b, 
     sa.rep = rep;
     sa.n_rep = n_rep;
     sa.host_out = host_out;
-    hipError_t e;
-    {
-        std::lock_guard<std::mutex> lk(st->persist_mu);
-        if (!st->persist_done) {
-            if (noalloc_sched) return fail(AM_EINVAL, "am_init has not run on this device");
-            HIP_TRY(hipEventCreateWithFlags(&st->persist_done, hipEventDisableTiming));
-        } else if (st->persist_stream != stream)
-            HIP_TRY(hipStreamWaitEvent(stream, st->persist_done, 0));
-        e = amq::launch_sweep(sa, fp64, plan.wg, plan.ppt, stream);
-        if (e == hipSuccess) {
-            HIP_TRY(hipEventRecord(st->persist_done, stream));
-            st->persist_stream = stream;
-        }
-    }
+    hipError_t e = hipSuccess;
+    rc = launch_persistent(st, stream, noalloc_sched == nullptr,
+                           [&]() { return amq::launch_sweep(sa, fp64, plan.wg, plan.ppt, stream); }, &e);
+    if (rc) return rc;
     if (e != hipSuccess)
         return fail(AM_EDEVICE, "sweep launch (%d threads, ppt %d, groups %d) failed: %s", plan.wg, plan.ppt, plan.G,
                     hipGetErrorString(e));
@@ -1241,12 +1251,14 @@ static_assert(kClaimWord + amq::kClaimQueues <= 16, "batch words");
 // persistent sweep) on `stream`: one part with its own tile, or both (mode
 // kMixed) with the default ones.  grid_cap
 // bounds the persistent grid (a fraction of the device when several batches
-// run side by side); cooperative selects hipLaunchCooperativeKernel.
+// run side by side).  alone: the sweep may take the whole device, ordered
+// after other streams' persistent sweeps as single options are (a cooperative
+// launch, which orders too, took 20 to 40 us more a call).
 // staging[h] (optional, pinned) holds part h's uploaded tables.
 // shifts (nullable): per option, the device address of its digital shift
 // ([n_dates] words; randomised QMC); all options of the batch or none.
 int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, am_basis basis, char *ws,
-                  hipStream_t stream, int grid_cap, bool cooperative, char *const (&staging)[2],
+                  hipStream_t stream, int grid_cap, bool alone, char *const (&staging)[2],
                   const size_t (&staging_bytes)[2], const int (&ppt)[2], const uint32_t *const *shifts)
 {
     const int laguerre = basis.kind == AM_BASIS_LAGUERRE;
@@ -1352,9 +1364,18 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
         g.opts64 = (const amq::BatchOpt *)(ws + S.off[1] + S.P[1].off_desc);
         g.err64 = (uint32_t *)(ws + S.off[1] + S.P[1].off_gsync) + 1;
     }
-    hipError_t e = amq::launch_sweep_batch((const amq::BatchOpt *)(ws + S.off[h0] + S.P[h0].off_desc),
-                                           (const int32_t *)(ws + S.off[ht] + S.P[ht].off_tiles), g, grid, mode,
-                                           ppt[h0], basis.degree, cooperative, stream);
+    const auto launch = [&]() {
+        return amq::launch_sweep_batch((const amq::BatchOpt *)(ws + S.off[h0] + S.P[h0].off_desc),
+                                       (const int32_t *)(ws + S.off[ht] + S.P[ht].off_tiles), g, grid, mode, ppt[h0],
+                                       basis.degree, alone && grid <= st->num_cu, stream);
+    };
+    hipError_t e = hipSuccess;
+    if (alone) {
+        const int rc = launch_persistent(st, stream, true, launch, &e);
+        if (rc) return rc;
+    } else {
+        e = launch();
+    }
     if (e != hipSuccess)
         return fail(AM_EDEVICE, "batch sweep launch (grid %d, ppt %d) failed: %s", grid, ppt[h0], hipGetErrorString(e));
     if (pr) HIP_TRY(hipEventRecord(pr->e[2], stream));
@@ -1374,7 +1395,7 @@ size_t staging_bytes_for(const BatchPlan &P, int n)
 // shifts (nullable): per caller option, the device address of its digital
 // shift (see enqueue_parts).
 int enqueue_split(DevState *st, const SplitBatch &B, am_basis basis, int32_t dtype, char *ws,
-                  hipStream_t stream, const int *grid_cap, bool cooperative, char *staging,
+                  hipStream_t stream, const int *grid_cap, bool alone, char *staging,
                   size_t staging_bytes, const int *ppt_in, const uint32_t *const *shifts = nullptr)
 {
     size_t so = 0;
@@ -1395,14 +1416,14 @@ int enqueue_split(DevState *st, const SplitBatch &B, am_basis basis, int32_t dty
     if (B.n(0) && B.n(1) && basis.kind == AM_BASIS_MONOMIAL && ppt[0] == default_batch_ppt(AM_FP32_BULK) &&
         ppt[1] == default_batch_ppt(AM_FP64)) {
         const int cap = grid_cap ? (grid_cap[0] < grid_cap[1] ? grid_cap[0] : grid_cap[1]) : 0;
-        const int rc = enqueue_parts(st, B, 0, 1, amq::kMixed, basis, ws, stream, cap, cooperative, stg, stg_bytes, ppt,
+        const int rc = enqueue_parts(st, B, 0, 1, amq::kMixed, basis, ws, stream, cap, alone, stg, stg_bytes, ppt,
                                      shifts);
         if (rc != AM_EDIM) return rc;   // (else too large for the shared grid: one after the other)
     }
     for (int h = 0; h < 2; ++h) {
         if (!B.n(h)) continue;
         const int rc = enqueue_parts(st, B, h, h, B.storage[h] == AM_FP64, basis, ws, stream,
-                                     grid_cap ? grid_cap[h] : 0, cooperative, stg, stg_bytes, ppt, shifts);
+                                     grid_cap ? grid_cap[h] : 0, alone, stg, stg_bytes, ppt, shifts);
         if (rc) return rc;
     }
     return AM_OK;

@@ -220,8 +220,9 @@ hipError_t launch_paper(const PaperArgs &a, int fp64, hipStream_t s);
 hipError_t launch_generate_batch(const BatchOpt *opts, const GenUnit *units, int n_units,
                                  const uint32_t *V, uint32_t *gsync, int max_seg_len, int fp64,
                                  bool shifted, hipStream_t s);
+// spread: at most one workgroup per CU (grid <= CUs, nothing else persistent beside it).
 hipError_t launch_sweep_batch(const BatchOpt *opts, const int32_t *tile_opt, const BatchGlobal &g,
-                              int grid, int fp64, int ppt, int degree, bool cooperative, hipStream_t s);
+                              int grid, int fp64, int ppt, int degree, bool spread, hipStream_t s);
 int sweep_batch_blocks_per_cu(int fp64, int laguerre, int ppt, int degree);
 // Sweep kernel tables, one translation unit per (precision, basis kind);
 // kind 0: single option, 256-thread groups; 1: many options; 2: single
