@@ -1279,27 +1279,24 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
         tiles += B[h].tiles;
         max_G = B[h].max_G > max_G ? B[h].max_G : max_G;
     }
-    // claim order: options by decreasing work (each part's order), merged.
+    // claim order: options by decreasing date count.  A claimed tile lasts as
+    // long as its option's dates whatever the option's size, so this is
+    // longest first; by work, options of many dates and few paths came last and
+    // ran on alone (96 options binary64: 408 dates from first to last claim's
+    // end against 278, by total work 252; sweep 3.12 -> 2.2 ms).
     // Where every tile is resident at once, with room for the largest option in
     // an eighth of the grid, the options are dealt to the claim queues, each to
     // the one with the least work, and exchange within an XCD (12 options 1782
     // -> 1680 us, 8 x 2^17 x 100 randomised 933 -> 917).  A book that claims
     // again and again is bound by its total work, and the queues' uneven ends
     // cost more (1024 options 41.4 ms with queues, 40.8 without).
-    struct Item { int h, i; double work; };
+    struct Item { int h, i; const am_option *o; };
     std::vector<Item> items;
-    size_t q[2] = {0, 0};
-    const auto next_work = [&](int h) {
-        if (h < h0 || h > h1 || q[h] >= (size_t)S.n(h)) return -1.0;
-        const am_option &o = S.opts[h][S.P[h].order[q[h]]];
-        return (double)o.n_paths * o.n_dates;
-    };
-    for (;;) {
-        const double w[2] = {next_work(0), next_work(1)};
-        if (w[0] < 0.0 && w[1] < 0.0) break;
-        const int h = w[0] >= w[1] ? 0 : 1;
-        items.push_back({h, S.P[h].order[q[h]++], w[h]});
-    }
+    for (int h = h0; h <= h1; ++h)
+        for (int i : S.P[h].order) items.push_back({h, i, &S.opts[h][i]});
+    std::stable_sort(items.begin(), items.end(), [](const Item &x, const Item &y) {
+        return x.o->n_dates != y.o->n_dates ? x.o->n_dates > y.o->n_dates : x.o->n_paths > y.o->n_paths;
+    });
     const int nq = tiles <= capacity && max_G <= capacity / amq::kClaimQueues ? amq::kClaimQueues : 1;
     std::vector<int> queue_of(items.size());
     double load[amq::kClaimQueues] = {0.0};
@@ -1309,7 +1306,7 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
         for (int c = 1; c < nq; ++c)
             if (load[c] < load[best]) best = c;
         queue_of[j] = best;
-        load[best] += items[j].work;
+        load[best] += (double)items[j].o->n_paths * items[j].o->n_dates;
         q_tiles[best] += B[items[j].h].desc[items[j].i].G;
         most = q_tiles[best] > most ? q_tiles[best] : most;
     }

@@ -706,7 +706,7 @@ hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream
 // Generation: each workgroup owns a block range of one option (unit table
 // built on the host).  Sweep: one persistent grid; workgroups
 // claim (option, tile) slots from one or several queues in a fixed order (options
-// by decreasing work, each option's tiles contiguous; see claim_tile), run that tile through
+// by decreasing date count, each option's tiles contiguous; see claim_tile), run that tile through
 // all of the option's dates with the option's own barrier words and partial
 // slots, then claim again.  An option's result depends
 // only on its own tiles and the fixed reduction order, not on which group ran
