@@ -261,10 +261,10 @@ __device__ __forceinline__ T exercise_update(T s_t, T pvj, double sg, double nsk
 
 // ---------------------------------------------------------------------------
 // Backward induction (Section V), persistent.  Group g owns the tile of
-// 256*PPT consecutive paths starting at g*256*PPT; wave w of the group owns
-// the 64*PPT paths from g*256*PPT + w*64*PPT, read as 16-byte vectors, vector
+// WG*PPT consecutive paths starting at g*WG*PPT; wave w of the group owns
+// the 64*PPT paths from g*WG*PPT + w*64*PPT, read as 16-byte vectors, vector
 // jj of lane l at element w*64*PPT + jj*64*VW + l*VW (each wave load reads
-// 1 KiB contiguous).  The discounted cashflows pv[] of a thread's PPT paths
+// 1 KiB contiguous).  (Slab tiles divide their paths otherwise: SlabRange.)  The discounted cashflows pv[] of a thread's PPT paths
 // stay in registers for the whole sweep.  Per date k = M-1..1:
 //   in-the-money moments (Hankel form of the Gram matrix in the standardised
 //   abscissa xs; weights wA = wB = 1 for monomials, wA = w^2, wB = w with
