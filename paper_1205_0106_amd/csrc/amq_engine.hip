@@ -1044,6 +1044,7 @@ struct SplitBatch {
     BatchPlan P[2];
     size_t off[2] = {0, 0};
     size_t total = 0;
+    bool one_sweep = false;    // both parts ran in one sweep, on part 0's error word (set by enqueue_split)
     int n(int h) const { return (int)opts[h].size(); }
 };
 
@@ -1357,10 +1358,7 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
     g.total_tiles = tiles;
     g.laguerre = laguerre;
     g.spin_limit = g_spin_limit ? g_spin_limit : kDefaultSpin;
-    if (mode == amq::kMixed) {
-        g.opts64 = (const amq::BatchOpt *)(ws + S.off[1] + S.P[1].off_desc);
-        g.err64 = (uint32_t *)(ws + S.off[1] + S.P[1].off_gsync) + 1;
-    }
+    if (mode == amq::kMixed) g.opts64 = (const amq::BatchOpt *)(ws + S.off[1] + S.P[1].off_desc);
     const auto launch = [&]() {
         return amq::launch_sweep_batch((const amq::BatchOpt *)(ws + S.off[h0] + S.P[h0].off_desc),
                                        (const int32_t *)(ws + S.off[ht] + S.P[ht].off_tiles), g, grid, mode, ppt[h0],
@@ -1390,12 +1388,13 @@ size_t staging_bytes_for(const BatchPlan &P, int n)
 // persistent grid (0: the device's resident capacity); staging (optional,
 // pinned) holds both parts' tables, part 1's after part 0's.
 // shifts (nullable): per caller option, the device address of its digital
-// shift (see enqueue_parts).
-int enqueue_split(DevState *st, const SplitBatch &B, am_basis basis, int32_t dtype, char *ws,
+// shift (see enqueue_parts).  Sets B.one_sweep.
+int enqueue_split(DevState *st, SplitBatch &B, am_basis basis, int32_t dtype, char *ws,
                   hipStream_t stream, const int *grid_cap, bool alone, char *staging,
                   size_t staging_bytes, const int *ppt_in, const uint32_t *const *shifts = nullptr)
 {
     size_t so = 0;
+    B.one_sweep = false;
     int ppt[2] = {0, 0};
     char *stg[2] = {nullptr, nullptr};
     size_t stg_bytes[2] = {0, 0};
@@ -1415,6 +1414,7 @@ int enqueue_split(DevState *st, const SplitBatch &B, am_basis basis, int32_t dty
         const int cap = grid_cap ? (grid_cap[0] < grid_cap[1] ? grid_cap[0] : grid_cap[1]) : 0;
         const int rc = enqueue_parts(st, B, 0, 1, amq::kMixed, basis, ws, stream, cap, alone, stg, stg_bytes, ppt,
                                      shifts);
+        B.one_sweep = rc == AM_OK;
         if (rc != AM_EDIM) return rc;   // (else too large for the shared grid: one after the other)
     }
     for (int h = 0; h < 2; ++h) {
@@ -1453,15 +1453,18 @@ size_t split_results_doubles(const SplitBatch &B)
 
 // Read results written by enqueue_split_results back into the caller's order
 // (price, std_err per option).  Returns AM_ETIMEOUT if a part's bounded
-// wait ran out.
+// wait ran out; where both parts ran in one sweep that ends it for both (its
+// groups claim no more tiles of either, so options of both may be unpriced).
 int scatter_split_results(const SplitBatch &B, const double *h_res, double *h_out, int32_t *status)
 {
     size_t o = 0;
     int rc = AM_OK;
+    bool sweep_timed_out = false;   // part 0's, kept for part 1 of one sweep
     for (int h = 0; h < 2; ++h) {
         if (!B.n(h)) continue;
         const uint32_t *gs = (const uint32_t *)(h_res + o + (size_t)B.n(h) * 8);
-        const bool timed_out = gs[1] != 0u;
+        const bool timed_out = gs[1] != 0u || (B.one_sweep && sweep_timed_out);
+        sweep_timed_out = timed_out;
         if (timed_out) rc = fail(AM_ETIMEOUT, "a device-side barrier wait ran out (spin limit)");
         for (int j = 0; j < B.n(h); ++j) {
             const int i = B.idx[h][j];
@@ -1703,7 +1706,6 @@ int am_batch_graph_create(const am_option *opts, int32_t n_opts, am_basis basis,
     }
     std::unique_ptr<am_batch_graph> g(new am_batch_graph);
     g->n = n_opts;
-    g->split.reset(new SplitBatch(B));
     size_t stage = 0;
     for (int h = 0; h < 2; ++h)
         if (B.n(h)) stage += align256(staging_bytes_for(B.P[h], B.n(h)));
@@ -1724,6 +1726,7 @@ int am_batch_graph_create(const am_option *opts, int32_t n_opts, am_basis basis,
     if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
     if (e != hipSuccess) return fail(AM_EDEVICE, "graph capture failed: %s", hipGetErrorString(e));
     g->graph = graph;
+    g->split.reset(new SplitBatch(B));
     HIP_TRY(hipGraphInstantiate(&g->exec, graph, nullptr, nullptr, 0));
     *out = g.release();
     return AM_OK;
@@ -1842,6 +1845,7 @@ struct am_server {
     int grid_cap[2] = {0, 0};         // per part: 1/n_streams of the resident capacity
     int full_cap[2] = {0, 0};         // per part: the whole device's resident capacity
     int ppt[2] = {0, 0};              // per part: batch tile (paths per thread)
+    uint32_t spin_limit = 0;          // the creating thread's test hook
     std::mutex mu;
     std::condition_variable cv;
     std::deque<Request> pending;
@@ -1992,6 +1996,7 @@ bool launch_some(am_server *sv, Slot &sl, std::deque<Request> &pend, std::vector
 void server_loop(am_server *sv)
 {
     (void)hipSetDevice(sv->st->dev);   // the device was validated at create
+    g_spin_limit = sv->spin_limit;
     std::deque<Request> local;
     std::vector<am_result> out;
     for (;;) {
@@ -2044,6 +2049,7 @@ int am_server_create(const am_server_config *cfg, am_server **out)
     std::unique_ptr<am_server> sv(new am_server);
     sv->cfg = *cfg;
     sv->st = st;
+    sv->spin_limit = g_spin_limit;
     if (hipMalloc((void **)&sv->pool, cfg->hbm_budget_bytes) != hipSuccess)
         return fail(AM_ENOMEM, "hipMalloc of the %zu-byte serving pool failed", cfg->hbm_budget_bytes);
     sv->alloc.init(cfg->hbm_budget_bytes);

@@ -182,13 +182,11 @@ struct BatchGlobal {
     uint32_t *claim;          // claim counters [queues] (zeroed by generation)
     int32_t queues;           // kClaimQueues or 1
     int32_t q_off[kClaimQueues + 1];   // queue q: tiles q_off[q] .. q_off[q + 1] - 1 of the list
-    uint32_t *err;            // error word (zeroed by generation)
+    uint32_t *err;            // error word (zeroed by generation), of every option of the launch
     int32_t total_tiles, laguerre;
     uint32_t spin_limit, pad;
-    // a launch over both storage types (kMixed): the binary64 part's options
-    // and error word, else null
+    // a launch over both storage types (kMixed): the binary64 part's options, else null
     const BatchOpt *opts64;
-    uint32_t *err64;
 };
 
 // `fp64` of the batch sweep's launcher and capacity for both storage types

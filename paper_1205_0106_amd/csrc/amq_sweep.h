@@ -1672,7 +1672,7 @@ __device__ __forceinline__ int claim_tile(const BatchGlobal &g, int *s_claim)
     __syncthreads();
     if (threadIdx.x == 0) {
         int t = g.total_tiles;
-        if (ld_agent(g.err) == 0u && !(g.err64 && ld_agent(g.err64) != 0u)) {
+        if (ld_agent(g.err) == 0u) {
             for (int i = 0; i < g.queues; ++i) {
                 const int q = (int)(blockIdx.x + (uint32_t)i) % g.queues;
                 const int n = g.q_off[q + 1] - g.q_off[q];
@@ -1708,7 +1708,8 @@ sweep_batch_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
 
 // Options of both storage types in one persistent grid (a binary32 request
 // stores small options in binary64): tiles of the two kinds share the claim
-// order, bit 31 of a tile's entry marking binary64.  As two launches one
+// order and the error word (a wait that runs out ends the claims of both),
+// bit 31 of a tile's entry marking binary64.  As two launches one
 // after the other, a small book paid for the longest option of each kind in
 // turn with most of the device idle (12 options of 2^12 .. 2^16 paths: 2793 us
 // per call, now 1795).
@@ -1724,7 +1725,7 @@ sweep_mixed_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
         if (t >= g.total_tiles) return;
         const int32_t e = __builtin_amdgcn_readfirstlane(tile_opt[t]);
         if (e < 0) {
-            if (!batch_tile<double, PPT64, D, false>(g.opts64[e & 0x7FFFFFFF], t, g.queues, g.err64, g.spin_limit, L.d)) return;
+            if (!batch_tile<double, PPT64, D, false>(g.opts64[e & 0x7FFFFFFF], t, g.queues, g.err, g.spin_limit, L.d)) return;
         } else {
             if (!batch_tile<float, PPT32, D, false>(opts[e], t, g.queues, g.err, g.spin_limit, L.f)) return;
         }

@@ -1,0 +1,87 @@
+// The host engine on a stand-in device (fake_device.h): one scenario a run,
+// named on the command line.  Exit status 0 and "passed" = pass.
+#include "fake_device.h"
+
+#include "../../paper_1205_0106_amd/csrc/amq_engine.hip"
+
+static int g_failed = 0;
+#define CHECK(c)                                                                  \
+    do {                                                                          \
+        if (!(c)) {                                                               \
+            fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #c);       \
+            ++g_failed;                                                           \
+        }                                                                         \
+    } while (0)
+
+static am_option option(int64_t n_paths, int32_t n_dates)
+{
+    am_option o;
+    memset(&o, 0, sizeof o);
+    o.params = am_params{100.0, 100.0, 0.05, 0.2, 1.0, 0, 1};
+    o.n_paths = n_paths;
+    o.n_dates = n_dates;
+    return o;
+}
+
+// A wait runs out in a sweep over both storage types before the options of
+// one type are claimed: none of the book's options reads as priced, whichever
+// type had the wait (the words of a result that was never written hold an
+// earlier price).
+static void mixed_timeout()
+{
+    const am_basis b{AM_BASIS_MONOMIAL, 2};
+    const am_server_config cfg{(size_t)256 << 20, 1e12, 64, 1, b, AM_FP32_BULK, 1};
+    std::mutex gate;
+    std::unique_lock<std::mutex> hold(gate);
+    std::atomic<int> mixed{0};
+    fake::on_sweep_batch = [&](const amq::BatchOpt *, const int32_t *, const amq::BatchGlobal &g, int, int mode) {
+        if (mode != amq::kMixed) {
+            std::lock_guard<std::mutex> wait(gate);   // the first batch runs until the others are queued
+            return;
+        }
+        mixed++;
+        *g.err = 1u;
+    };
+    am_server *sv = nullptr;
+    CHECK(am_server_create(&cfg, &sv) == AM_OK);
+    const am_option first = option(20000, 4), f32 = option(40000, 5), f64 = option(3000, 6);
+    CHECK(am_server_submit(sv, &first, 0, -1.0) == AM_OK);
+    am_result r[8];
+    int32_t n = 0;
+    double st[4] = {0};
+    while (st[0] < 1.0) {   // (the first batch is counted once its launch returns: wait for the slot by its pool bytes)
+        CHECK(am_server_stats(sv, st) == AM_OK);
+        if (st[3] > 0.0) break;
+    }
+    CHECK(am_server_submit(sv, &f32, 1, -1.0) == AM_OK);
+    CHECK(am_server_submit(sv, &f64, 2, -1.0) == AM_OK);
+    CHECK(am_server_submit(sv, &f32, 3, -1.0) == AM_OK);
+    hold.unlock();
+    int got = 0, late = 0;
+    for (int spin = 0; got < 4 && spin < 5000; ++spin) {
+        CHECK(am_server_poll(sv, r, 8, &n) == AM_OK);
+        for (int i = 0; i < n; ++i) {
+            ++got;
+            if (r[i].request_id > 0 && r[i].status == AM_ETIMEOUT) ++late;
+        }
+        std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    }
+    CHECK(am_server_destroy(sv) == AM_OK);
+    CHECK(got == 4 && mixed == 1);
+    CHECK(late == 3);
+}
+
+int main(int argc, char **argv)
+{
+    const std::map<std::string, void (*)()> scenarios = {
+        {"mixed_timeout", mixed_timeout},
+    };
+    const auto it = scenarios.find(argc > 1 ? argv[1] : "");
+    if (it == scenarios.end()) {
+        for (const auto &s : scenarios) printf("%s\n", s.first.c_str());
+        return 2;
+    }
+    it->second();
+    printf(g_failed ? "%d checks failed\n" : "passed\n", g_failed);
+    return g_failed ? 1 : 0;
+}
