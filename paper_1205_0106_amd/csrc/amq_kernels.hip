@@ -103,9 +103,14 @@ __constant__ double kExpTab[64] = {
     0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0,
 };
 
-// WIDE: any finite x (2^(n div 64) by ldexp, the table plain).  Otherwise for
-// |x| < 700: the table's entries come less j 2^46 in their bits
-// (exp_tab_entry), and adding n 2^46 gives 2^(n / 64) whole.  The same values.
+// WIDE: any x (2^(n div 64) by ldexp, the table plain), brought into
+// [-kWideExp, kWideExp] first: the value is 0 or infinite at either end, and n
+// stays an integer that the sum's low word holds (from |x| = 2.3e7 it would
+// wrap: a path whose drift takes it far below 0 came out infinite).  A NaN
+// stays one.  Otherwise for |x| < 700: the table's entries come less j 2^46 in
+// their bits (exp_tab_entry), and adding n 2^46 gives 2^(n / 64) whole.  The
+// same values.
+constexpr double kWideExp = 2000.0;
 template <bool WIDE>
 __device__ __forceinline__ double exp_tab_entry(uint32_t j)
 {
@@ -116,6 +121,7 @@ __device__ __forceinline__ double exp_tab_entry(uint32_t j)
 template <bool WIDE, typename Tab>
 __device__ __forceinline__ double exp_tab(double x, Tab tab)
 {
+    if (WIDE) x = x < -kWideExp ? -kWideExp : x > kWideExp ? kWideExp : x;
     // n = rint(64 x / ln 2) by adding 1.5 2^52: the integer is in the sum's low
     // word (two's complement), no rounding and conversion instructions
     const double r = fma3s(x, 92.332482616893658, 0x1.8p52);  // 64 / ln 2
