@@ -133,7 +133,10 @@ int am_workspace_layout(int64_t n_paths, int32_t n_dates, am_basis basis, int32_
  * (>= am_workspace_bytes, 256-byte aligned, on the current device).  The
  * workspace must not be shared by calls that may overlap.  Calls enqueued
  * on different streams of one device may overlap in generation; their
- * sweeps (each holding every CU) run one after another, in enqueue order.
+ * sweeps (each holding every CU) run one after another, in enqueue order, and
+ * so do those of am_price_batch and whole am_batch_graph_launch replays.  A
+ * call made while the caller captures the stream is outside that order: its
+ * replays must not overlap other sweeps on the device.
  * A sweep kept from being fully resident by other work on the device waits
  * boundedly and then fails with AM_ETIMEOUT.  If h_out is
  * non-NULL the call waits for the stream and writes h_out[0] = price,
@@ -148,7 +151,7 @@ int am_price_american_ex(const am_params *params, int64_t n_paths, int32_t n_dat
 enum { AM_SCRATCH_BYTES = 134217728 };
 
 /* Set up the current device for the library: direction-number table,
- * stream, the event that orders single-option sweeps, the device address of
+ * stream, the event that orders sweeps of different streams, the device address of
  * the allocation-free entry point's workspace, and every single-option
  * kernel's code loaded on the device.  Allocates; idempotent; any thread.
  * Needed once per device (and again after am_shutdown) before
@@ -308,7 +311,9 @@ int am_batch_autotune(const am_option *opts, int32_t n_opts, am_basis basis, int
 
 /* A batch captured once as a HIP graph (table uploads from pinned staging,
  * both kernels, result download) and replayed with one launch.  The
- * options, workspace and tile choice are fixed at capture. */
+ * options, workspace and tile choice are fixed at capture.  A launch is
+ * ordered against other streams' sweeps as am_price_american_ex says; after
+ * am_shutdown it fails with AM_EINVAL. */
 typedef struct am_batch_graph am_batch_graph;
 int am_batch_graph_create(const am_option *opts, int32_t n_opts, am_basis basis, int32_t dtype,
                           void *d_workspace, size_t ws_bytes, am_batch_graph **out);
@@ -382,8 +387,7 @@ int am_server_destroy(am_server *server);
 
 /* Release what the library holds for the life of the process: per device
  * the direction-number table, the bridge schedules, the synchronous entry
- * point's workspace and stream and the event that orders single-option
- * sweeps; the pinned result buffers and profiling events of every thread.
+ * point's workspace and stream and the event that orders sweeps; the pinned result buffers and profiling events of every thread.
  * Waits for the library's own streams first.  Call it with no other library
  * call in flight and no server alive (AM_EINVAL otherwise); a later call
  * sets the state up again.  The Python binding calls it at interpreter exit,

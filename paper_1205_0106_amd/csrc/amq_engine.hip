@@ -251,10 +251,11 @@ struct DevState {
     void *ws = nullptr;
     size_t ws_bytes = 0;
     std::map<long, int> occ;                        // (kind, fp64, wg, ppt, degree) -> groups per CU
-    // single-option sweeps and whole-device batches hold every CU for their whole
-    // run and wait on one another's groups only within their own grid: launches on different
-    // streams are ordered through this event, in enqueue order, so two never
-    // share the device
+    // single-option sweeps, whole-device batches and replays of captured
+    // batches may hold every CU for their whole run and wait on one another's
+    // groups only within their own grid: launches on different streams are
+    // ordered through this event, in enqueue order, so two never share the
+    // device
     std::mutex persist_mu;
     hipEvent_t persist_done = nullptr;
     hipStream_t persist_stream = nullptr;
@@ -291,14 +292,19 @@ int get_state(DevState **out)
     return AM_OK;
 }
 
-// The current device's state if a call has set it up, else nullptr (creates nothing).
-DevState *find_state()
+// A device's state if a call has set it up, else nullptr (creates nothing).
+DevState *find_state(int dev)
 {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     std::lock_guard<std::mutex> lk(g_dev_mu);
     auto it = g_devs.find(dev);
     return it == g_devs.end() ? nullptr : it->second.get();
+}
+
+// The current device's.
+DevState *find_state()
+{
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess ? find_state(dev) : nullptr;
 }
 
 int host_schedule(int M, SegSchedule *out)
@@ -509,12 +515,21 @@ int prof_slot(ProfRec **out)
     return AM_OK;
 }
 
-// Launch a sweep that holds the device for its whole run, after the persistent
-// sweeps that other streams have enqueued (see DevState).  *e: the launch's
-// own outcome.  create: the ordering event may be created here.
+// Launch work that may hold the device for its whole run, after what other
+// streams have enqueued of that kind (see DevState).  *e: the launch's
+// own outcome.  create: the ordering event may be created here.  On a stream
+// that is being captured by the caller the launch alone is made: an event
+// recorded inside a capture orders nothing outside it, and cannot be waited for
+// there; whoever replays such a graph keeps it from overlapping other sweeps.
 template <typename Launch>
 int launch_persistent(DevState *st, hipStream_t stream, bool create, Launch launch, hipError_t *e)
 {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (stream) HIP_TRY(hipStreamIsCapturing(stream, &capture));
+    if (capture != hipStreamCaptureStatusNone) {
+        *e = launch();
+        return AM_OK;
+    }
     std::lock_guard<std::mutex> lk(st->persist_mu);
     if (!st->persist_done) {
         if (!create) return fail(AM_EINVAL, "am_init has not run on this device");
@@ -1681,7 +1696,7 @@ struct am_batch_graph {
     hipEvent_t done = nullptr;
     char *staging = nullptr;
     double *h_res = nullptr;
-    int32_t n = 0;
+    int32_t n = 0, dev = 0;
 };
 
 extern "C" {
@@ -1706,6 +1721,7 @@ int am_batch_graph_create(const am_option *opts, int32_t n_opts, am_basis basis,
     }
     std::unique_ptr<am_batch_graph> g(new am_batch_graph);
     g->n = n_opts;
+    g->dev = st->dev;
     size_t stage = 0;
     for (int h = 0; h < 2; ++h)
         if (B.n(h)) stage += align256(staging_bytes_for(B.P[h], B.n(h)));
@@ -1736,7 +1752,13 @@ int am_batch_graph_launch(am_batch_graph *g, void *hip_stream)
 {
     if (!g) return fail(AM_EINVAL, "graph is NULL");
     hipStream_t s = (hipStream_t)hip_stream;
-    HIP_TRY(hipGraphLaunch(g->exec, s));
+    DevState *st = find_state(g->dev);
+    if (!st) return fail(AM_EINVAL, "am_shutdown released what the graph reads");
+    // the captured sweep may fill the device: ordered as the eager calls are
+    hipError_t e = hipSuccess;
+    const int rc = launch_persistent(st, s, true, [&]() { return hipGraphLaunch(g->exec, s); }, &e);
+    if (rc) return rc;
+    if (e != hipSuccess) return fail(AM_EDEVICE, "graph launch failed: %s", hipGetErrorString(e));
     HIP_TRY(hipEventRecord(g->done, s));
     return AM_OK;
 }
@@ -2208,7 +2230,7 @@ int am_shutdown(void)
                 continue;
             }
             // the library's own work first: the synchronous stream and the
-            // last single-option sweep on any stream
+            // last ordered sweep on any stream
             if (st->stream) (void)hipStreamSynchronize(st->stream);
             if (st->persist_done) (void)hipEventSynchronize(st->persist_done);
             for (auto &sc : st->sched) (void)hipFree(sc.second.d);

@@ -71,10 +71,73 @@ static void mixed_timeout()
     CHECK(late == 3);
 }
 
+// The calls logged since the last time, in order, as "wait:A", "sweep:A",
+// "record:A" or "graph:A" on stream A.
+static std::vector<std::string> logged(const std::map<const void *, char> &name)
+{
+    std::vector<std::string> out;
+    for (const std::string &l : fake::log) {
+        char what[16];
+        void *s = nullptr, *o = nullptr;
+        if (sscanf(l.c_str(), "%15s %p %p", what, &s, &o) < 2) continue;
+        const auto it = name.find(s);
+        out.push_back(std::string(what) + ":" + (it == name.end() ? '?' : it->second));
+    }
+    fake::log.clear();
+    return out;
+}
+
+// Sweeps that may fill the device run in enqueue order whatever enqueued them:
+// single options, books and replays of captured books.
+static void order_across_streams()
+{
+    using V = std::vector<std::string>;
+    const am_basis b{AM_BASIS_MONOMIAL, 2};
+    const hipStream_t A = (hipStream_t)0xA0, B = (hipStream_t)0xB0;
+    const std::map<const void *, char> name = {{A, 'A'}, {B, 'B'}};
+    const am_option o = option(20000, 4);
+    void *w1 = nullptr, *w2 = nullptr;
+    CHECK(fake::alloc(&w1, am_workspace_bytes(o.n_paths, o.n_dates, b, AM_FP64)) == hipSuccess);
+    const size_t nb = am_batch_workspace_bytes(&o, 1, b, AM_FP64);
+    CHECK(fake::alloc(&w2, nb) == hipSuccess);
+    const auto single = [&](hipStream_t s) {
+        return am_price_american_ex(&o.params, o.n_paths, o.n_dates, b, AM_FP64, w1,
+                                    am_workspace_bytes(o.n_paths, o.n_dates, b, AM_FP64), s, nullptr);
+    };
+    am_batch_graph *g = nullptr;
+    CHECK(am_batch_graph_create(&o, 1, b, AM_FP64, w2, nb, &g) == AM_OK);
+    fake::log.clear();
+    CHECK(single(A) == AM_OK);
+    CHECK(logged(name) == (V{"sweep:A", "record:A"}));
+    // (a replay's second record is its own end)
+    CHECK(am_batch_graph_launch(g, B) == AM_OK);
+    CHECK(logged(name) == (V{"wait:B", "graph:B", "record:B", "record:B"}));
+    CHECK(am_batch_graph_launch(g, B) == AM_OK);
+    CHECK(logged(name) == (V{"graph:B", "record:B", "record:B"}));
+    CHECK(single(A) == AM_OK);
+    CHECK(logged(name) == (V{"wait:A", "sweep:A", "record:A"}));
+    CHECK(am_price_batch(&o, 1, b, AM_FP64, w2, nb, B, nullptr) == AM_OK);
+    CHECK(logged(name) == (V{"wait:B", "sweep:B", "record:B"}));
+    CHECK(am_batch_graph_launch(g, A) == AM_OK);
+    CHECK(logged(name) == (V{"wait:A", "graph:A", "record:A", "record:A"}));
+    // a call into the caller's own capture leaves the order as it was
+    fake::capturing = B;
+    CHECK(single(B) == AM_OK);
+    fake::capturing = nullptr;
+    CHECK(logged(name) == (V{"sweep:B"}));
+    CHECK(single(A) == AM_OK);
+    CHECK(logged(name) == (V{"sweep:A", "record:A"}));
+    // what a graph reads is gone after am_shutdown
+    CHECK(am_shutdown() == AM_OK);
+    CHECK(am_batch_graph_launch(g, A) == AM_EINVAL);
+    CHECK(am_batch_graph_destroy(g) == AM_OK);
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
         {"mixed_timeout", mixed_timeout},
+        {"order_across_streams", order_across_streams},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {

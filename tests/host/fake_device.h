@@ -54,6 +54,12 @@ inline hipError_t copy_async(void *d, const void *s, size_t n, hipMemcpyKind, hi
 inline hipError_t stream_create(hipStream_t *s, unsigned) { return handle(s); }
 inline hipError_t stream_destroy(hipStream_t) { return hipSuccess; }
 inline hipError_t stream_wait_event(hipStream_t s, hipEvent_t e, unsigned) { note("wait", s, e); return hipSuccess; }
+hipStream_t capturing = nullptr;       // the stream under capture
+inline hipError_t stream_capturing(hipStream_t s, hipStreamCaptureStatus *c)
+{
+    *c = s == capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 inline hipError_t stream_sync(hipStream_t) { return hipSuccess; }
 inline hipError_t event_create(hipEvent_t *e) { return handle(e); }
 inline hipError_t event_create_flags(hipEvent_t *e, unsigned) { return handle(e); }
@@ -61,8 +67,8 @@ inline hipError_t event_destroy(hipEvent_t) { return hipSuccess; }
 inline hipError_t event_record(hipEvent_t e, hipStream_t s) { note("record", s, e); return hipSuccess; }
 inline hipError_t event_ok(hipEvent_t) { return hipSuccess; }
 inline hipError_t event_elapsed(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
-inline hipError_t begin_capture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
-inline hipError_t end_capture(hipStream_t, hipGraph_t *g) { return handle(g); }
+inline hipError_t begin_capture(hipStream_t s, hipStreamCaptureMode) { capturing = s; return hipSuccess; }
+inline hipError_t end_capture(hipStream_t, hipGraph_t *g) { capturing = nullptr; return handle(g); }
 inline hipError_t graph_instantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, char *, size_t) { return handle(x); }
 inline hipError_t graph_launch(hipGraphExec_t x, hipStream_t s) { note("graph", s, x); return hipSuccess; }
 inline hipError_t graph_destroy(hipGraph_t) { return hipSuccess; }
@@ -125,6 +131,7 @@ int sweep_batch_blocks_per_cu(int, int, int, int) { return fake::batch_groups_pe
 #define hipStreamCreateWithFlags fake::stream_create
 #define hipStreamDestroy fake::stream_destroy
 #define hipStreamWaitEvent fake::stream_wait_event
+#define hipStreamIsCapturing fake::stream_capturing
 #define hipStreamSynchronize fake::stream_sync
 #define hipEventCreate fake::event_create
 #define hipEventCreateWithFlags fake::event_create_flags
