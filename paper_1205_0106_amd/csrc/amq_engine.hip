@@ -1300,12 +1300,18 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
     // longest first; by work, options of many dates and few paths came last and
     // ran on alone (96 options binary64: 408 dates from first to last claim's
     // end against 278, by total work 252; sweep 3.12 -> 2.2 ms).
-    // Where every tile is resident at once, with room for the largest option in
-    // an eighth of the grid, the options are dealt to the claim queues, each to
-    // the one with the least work, and exchange within an XCD (12 options 1782
-    // -> 1680 us, 8 x 2^17 x 100 randomised 933 -> 917).  A book that claims
+    // Where the device has a compute unit for every group, the options are dealt
+    // to the claim queues, each to the one with the least work, and exchange
+    // within an XCD (12 options 1782 -> 1680 us, 8 x 2^17 x 100 randomised 933 ->
+    // 917).  All queues' options are then under way at once, so every group has
+    // to become resident, whatever else runs on the device for a while: one a
+    // compute unit (spread) always finds room.  Two a unit may not: a group of
+    // 66 KB placed in the middle of a unit's LDS, between groups of another
+    // stream's generation, keeps a second one out for as long as it stays.  With
+    // one queue the groups that are resident finish options in turn, as long as
+    // they hold the largest one.  (A book that claims
     // again and again is bound by its total work, and the queues' uneven ends
-    // cost more (1024 options 41.4 ms with queues, 40.8 without).
+    // cost more: 1024 options 41.4 ms with queues, 40.8 without.)
     struct Item { int h, i; const am_option *o; };
     std::vector<Item> items;
     for (int h = h0; h <= h1; ++h)
@@ -1313,22 +1319,24 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
     std::stable_sort(items.begin(), items.end(), [](const Item &x, const Item &y) {
         return x.o->n_dates != y.o->n_dates ? x.o->n_dates > y.o->n_dates : x.o->n_paths > y.o->n_paths;
     });
-    const int nq = tiles <= capacity && max_G <= capacity / amq::kClaimQueues ? amq::kClaimQueues : 1;
     std::vector<int> queue_of(items.size());
     double load[amq::kClaimQueues] = {0.0};
     int q_tiles[amq::kClaimQueues] = {0}, most = 0;
     for (size_t j = 0; j < items.size(); ++j) {
         int best = 0;
-        for (int c = 1; c < nq; ++c)
+        for (int c = 1; c < amq::kClaimQueues; ++c)
             if (load[c] < load[best]) best = c;
         queue_of[j] = best;
         load[best] += (double)items[j].o->n_paths * items[j].o->n_dates;
         q_tiles[best] += B[items[j].h].desc[items[j].i].G;
         most = q_tiles[best] > most ? q_tiles[best] : most;
     }
-    // every queue's own groups (grid / nq of them) hold its largest option
-    int64_t want = nq > 1 ? (int64_t)nq * most : tiles;
-    const int grid = (int)(want < capacity ? want : capacity / nq * nq);
+    // (the queues' groups are dealt out in turn: each gets the largest one's tiles)
+    const int units = capacity < st->num_cu ? capacity : st->num_cu;
+    const bool queued = alone && (int64_t)amq::kClaimQueues * most <= units;
+    const int nq = queued ? amq::kClaimQueues : 1;
+    if (!queued) std::fill(queue_of.begin(), queue_of.end(), 0);
+    const int grid = queued ? amq::kClaimQueues * most : tiles < capacity ? tiles : capacity;
     if (max_G > grid)
         return fail(AM_EDIM, "an option needs %d tiles but only %d workgroups are resident", max_G, grid);
     std::vector<int32_t> tile_opt;
@@ -1733,7 +1741,7 @@ int am_batch_graph_create(const am_option *opts, int32_t n_opts, am_basis basis,
     HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     char *ws = (char *)d_workspace;
-    rc = enqueue_split(st, B, basis, dtype, ws, cs, nullptr, false, g->staging, stage, nullptr);
+    rc = enqueue_split(st, B, basis, dtype, ws, cs, nullptr, true, g->staging, stage, nullptr);
     if (rc == AM_OK && enqueue_split_results(B, ws, g->h_res, cs) != AM_OK)
         rc = fail(AM_EDEVICE, "result download could not be captured");
     hipGraph_t graph = nullptr;

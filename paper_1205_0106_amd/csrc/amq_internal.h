@@ -173,9 +173,9 @@ struct GenUnit {              // one generation workgroup: blocks [b0, b1) of op
 };
 
 // Claim queues of a batch sweep: a workgroup claims from queue blockIdx mod
-// kClaimQueues first (the device deals workgroups out to its XCDs in turn, so
-// an option's tiles run on one XCD and exchange within its L2), from the
-// others once that is empty.
+// kClaimQueues (the device deals workgroups out to its XCDs in turn, so an
+// option's tiles run on one XCD and exchange within its L2).  Only where every
+// group has a compute unit of its own; else there is one queue.
 constexpr int kClaimQueues = 8;
 
 struct BatchGlobal {

@@ -1662,27 +1662,23 @@ __device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, int queues,
 
 // The next tile of a batch, or total_tiles (none left, or a wait ran out
 // somewhere); wave-uniform, so the descriptor and everything derived from it
-// live in scalar registers.  Tiles of a queue are claimed in order and an
-// option's are contiguous, so a queue has at most one partly claimed option;
-// its own groups (at least as many as any of its options has tiles) leave it
-// only when every tile is claimed, so that option is always joined by the rest
-// of its groups, whoever else helps.
+// live in scalar registers.  A group claims from its own queue.  Tiles of a
+// queue are claimed in order and an option's are contiguous, so a queue has at
+// most one partly claimed option; the queue's groups are at least as many as
+// any of its options has tiles and leave only when every tile is claimed, so
+// that option is always joined by the rest of its groups.
 __device__ __forceinline__ int claim_tile(const BatchGlobal &g, int *s_claim)
 {
     __syncthreads();
     if (threadIdx.x == 0) {
         int t = g.total_tiles;
         if (ld_agent(g.err) == 0u) {
-            for (int i = 0; i < g.queues; ++i) {
-                const int q = (int)(blockIdx.x + (uint32_t)i) % g.queues;
-                const int n = g.q_off[q + 1] - g.q_off[q];
-                // (an empty queue's counter is not counted up for ever)
-                if ((int)ld_agent(g.claim + q) >= n) continue;
+            const int q = (int)blockIdx.x % g.queues;
+            const int n = g.q_off[q + 1] - g.q_off[q];
+            // (an exhausted queue's counter is not counted up for ever)
+            if ((int)ld_agent(g.claim + q) < n) {
                 const int c = (int)__hip_atomic_fetch_add(g.claim + q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (c < n) {
-                    t = g.q_off[q] + c;
-                    break;
-                }
+                if (c < n) t = g.q_off[q] + c;
             }
         }
         *s_claim = t;

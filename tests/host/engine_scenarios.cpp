@@ -133,11 +133,96 @@ static void order_across_streams()
     CHECK(am_batch_graph_destroy(g) == AM_OK);
 }
 
+// Whether a batch sweep's grid finishes with only `room` groups resident at a
+// time (the rest start as others leave): every group claims its queue's next
+// tile and holds it until all of that option's tiles are held.
+static bool finishes(const amq::BatchGlobal &g, const int32_t *tile_opt, int grid, int room)
+{
+    std::vector<int> next(g.q_off, g.q_off + g.queues);
+    std::map<int32_t, int> tiles, held;             // per option
+    for (int t = 0; t < g.total_tiles; ++t) tiles[tile_opt[t]]++;
+    std::vector<std::pair<int, int32_t>> resident;  // (queue, option held)
+    int started = 0, done = 0;
+    for (;;) {
+        bool moved = false;
+        while (started < grid && (int)resident.size() < room) {
+            const int q = started++ % g.queues;
+            moved = true;
+            if (next[q] >= g.q_off[q + 1]) continue;
+            resident.push_back({q, tile_opt[next[q]++]});
+            held[resident.back().second]++;
+        }
+        for (size_t i = 0; i < resident.size();) {
+            auto &[q, o] = resident[i];
+            if (held[o] < tiles[o]) { ++i; continue; }
+            moved = true;
+            ++done;
+            if (next[q] < g.q_off[q + 1]) {
+                o = tile_opt[next[q]++];
+                held[o]++;
+                ++i;
+            } else {
+                resident.erase(resident.begin() + i);
+            }
+        }
+        if (done == g.total_tiles) return true;
+        if (!moved) return false;
+    }
+}
+
+// A book finishes with one group a compute unit, however many a unit may hold
+// (other work on the device can leave no more), and options share the device
+// through several claim queues only where every group has a unit of its own.
+static void claim_queues()
+{
+    struct Shape { int n, step; int64_t n_paths; int32_t n_dates; };
+    const Shape shapes[] = {{1, 0, 20000, 4}, {2, 9, 60000, 9}, {8, 0, 700000, 7}, {6, 37, 1 << 20, 5}, {12, 5000, 9000, 40},
+                            {8, 0, 1 << 19, 6}, {5, 0, 900000, 6}, {40, 1000, 30000, 12}, {300, 77, 16000, 10},
+                            {3, 0, 4000000, 3}, {64, 0, 65536, 8}, {65, 0, 65536, 8}};
+    const am_basis b{AM_BASIS_MONOMIAL, 2};
+    int launches = 0, queued = 0;
+    fake::on_sweep_batch = [&](const amq::BatchOpt *, const int32_t *tile_opt, const amq::BatchGlobal &g, int grid, int) {
+        ++launches;
+        CHECK(g.queues == 1 || g.queues == amq::kClaimQueues);
+        CHECK(g.q_off[0] == 0 && g.q_off[g.queues] == g.total_tiles);
+        if (g.queues > 1) {
+            ++queued;
+            CHECK(grid <= fake::kCus && grid % g.queues == 0);
+            for (int q = 0; q < g.queues; ++q) CHECK(g.q_off[q + 1] - g.q_off[q] <= grid / g.queues);
+        }
+        CHECK(grid <= fake::kCus * fake::batch_groups_per_cu);
+        CHECK(finishes(g, tile_opt, grid, fake::kCus));
+    };
+    for (const Shape &s : shapes)
+        for (int dtype : {AM_FP64, AM_FP32_BULK}) {
+            std::vector<am_option> o;
+            for (int i = 0; i < s.n; ++i) o.push_back(option(s.n_paths + (int64_t)s.step * i, s.n_dates + i % 5));
+            const int64_t tile = 256 * (dtype == AM_FP64 ? 32 : 64);
+            if ((s.n_paths + tile - 1) / tile > fake::kCus) continue;   // (more tiles than units: needs what it needs)
+            const size_t nb = am_batch_workspace_bytes(o.data(), s.n, b, dtype);
+            void *w = nullptr;
+            CHECK(nb > 0 && fake::alloc(&w, nb) == hipSuccess);
+            CHECK(am_price_batch(o.data(), s.n, b, dtype, w, nb, (hipStream_t)0xA0, nullptr) == AM_OK);
+            fake::release(w);
+        }
+    CHECK(launches > 20 && queued > 8 && queued < launches);
+    // served batches share the device: one queue
+    const am_server_config cfg{(size_t)256 << 20, 1e12, 64, 2, b, AM_FP64, 1};
+    queued = 0;
+    am_server *sv = nullptr;
+    CHECK(am_server_create(&cfg, &sv) == AM_OK);
+    const am_option o = option(20000, 4);
+    for (int i = 0; i < 6; ++i) CHECK(am_server_submit(sv, &o, i, -1.0) == AM_OK);
+    CHECK(am_server_destroy(sv) == AM_OK);
+    CHECK(queued == 0);
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
         {"mixed_timeout", mixed_timeout},
         {"order_across_streams", order_across_streams},
+        {"claim_queues", claim_queues},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {
