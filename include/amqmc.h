@@ -252,7 +252,10 @@ size_t am_batch_workspace_bytes(const am_option *opts, int32_t n_opts, am_basis 
  * stream; am_batch_workspace_bytes covers both).  h_out (2 * n_opts
  * doubles, or NULL to return after enqueueing) receives price and std_err
  * per option in the caller's order.  Fails with AM_EDIM if one option needs
- * more tiles than the device holds resident. */
+ * more tiles than the device holds resident.  An option of more tiles than
+ * compute units (binary32 monomials from 2^22 paths, binary64 from 2^21) needs
+ * two workgroups on a unit: other work on the device while the sweep starts can
+ * keep them apart, and the call then fails with AM_ETIMEOUT. */
 int am_price_batch(const am_option *opts, int32_t n_opts, am_basis basis, int32_t dtype,
                    void *d_workspace, size_t ws_bytes, void *hip_stream, double *h_out);
 
@@ -354,7 +357,8 @@ typedef struct am_result {
  * (am_price_batch's kernels, persistent grid limited to 1/n_streams of the
  * device so in-flight batches run side by side); completed batches return
  * their memory.  A request whose sweep needs more workgroups than that share
- * runs alone on the whole device once every stream is idle (later requests
+ * (of one workgroup per compute unit, where their LDS leaves a second one room
+ * only in some placements: the larger tile on monomials) runs alone on the whole device once every stream is idle (later requests
  * wait behind it).  Paths and cashflows stay resident in the pool until a
  * request completes.  Results are those of am_price_batch, hence identical
  * to pricing the request alone with the same batch tile.  The tile is fixed

@@ -1873,6 +1873,8 @@ struct am_server {
     PoolAlloc alloc;
     std::vector<Slot> slots;
     int grid_cap[2] = {0, 0};         // per part: 1/n_streams of the resident capacity
+    int share = 0;                    // tiles of one request beside other batches: 1/n_streams of the groups
+                                      // that find room in any case (kAnyPlacement)
     int full_cap[2] = {0, 0};         // per part: the whole device's resident capacity
     int ppt[2] = {0, 0};              // per part: batch tile (paths per thread)
     uint32_t spin_limit = 0;          // the creating thread's test hook
@@ -1938,7 +1940,10 @@ int64_t request_tiles(const am_server *sv, const am_option &o, int *part)
 // Launch the longest admissible prefix of the pending queue on slot `sl`.
 // A request whose sweep needs more groups than a stream's share of the
 // device goes alone, on the whole device, once every slot is idle; nothing
-// launches while it runs.  Returns true if something was launched.
+// launches while it runs.  Were every batch in flight short of its largest
+// request's groups, fewer groups than the shares' sum would be resident, so a
+// compute unit would have room for one more: one of them goes on.  Returns
+// true if something was launched.
 bool launch_some(am_server *sv, Slot &sl, std::deque<Request> &pend, std::vector<am_result> &out)
 {
     const am_server_config &c = sv->cfg;
@@ -1952,8 +1957,7 @@ bool launch_some(am_server *sv, Slot &sl, std::deque<Request> &pend, std::vector
     double work = 0.0;
     bool exclusive = false;
     for (size_t i = 0; i < pend.size() && (int)take.size() < c.max_batch_requests; ++i) {
-        int h = 0;
-        const bool big = request_tiles(sv, pend[i].opt, &h) > sv->grid_cap[h];
+        const bool big = request_tiles(sv, pend[i].opt, nullptr) > sv->share;
         if (big) {
             if (!take.empty()) break;          // the prefix stops before it
             if (any_busy) return false;        // waits for the device to drain
@@ -2099,6 +2103,10 @@ int am_server_create(const am_server_config *cfg, am_server **out)
         if (per_cu <= 0) return fail(AM_EDEVICE, "no batch sweep kernel");
         sv->full_cap[h] = per_cu * st->num_cu;
         sv->grid_cap[h] = sv->full_cap[h] / cfg->n_streams;
+        const int sure = amq::sweep_batch_blocks_per_cu(fp64 | amq::kAnyPlacement, cfg->basis.kind == AM_BASIS_LAGUERRE,
+                                                        sv->ppt[h], cfg->basis.degree);
+        const int share = sure * st->num_cu / cfg->n_streams;
+        if (h == 0 || share < sv->share) sv->share = share;
     }
     sv->slots.resize(cfg->n_streams);
     for (auto &sl : sv->slots) {

@@ -222,6 +222,11 @@ hipError_t launch_generate_batch(const BatchOpt *opts, const GenUnit *units, int
 hipError_t launch_sweep_batch(const BatchOpt *opts, const int32_t *tile_opt, const BatchGlobal &g,
                               int grid, int fp64, int ppt, int degree, bool spread, hipStream_t s);
 int sweep_batch_blocks_per_cu(int fp64, int laguerre, int ppt, int degree);
+// Beside the storage type of sweep_batch_blocks_per_cu: how many of those
+// groups find room whatever else has run on the CU.  With k - 1 groups anywhere
+// in its LDS a hole for the k-th is left if (2k - 1) groups' LDS fit (one of the
+// 66 KB tiles, though two fit side by side).
+constexpr int kAnyPlacement = 8;
 // Sweep kernel tables, one translation unit per (precision, basis kind);
 // kind 0: single option, 256-thread groups; 1: many options; 2: single
 // option, 512-thread groups.  Null where not built.

@@ -648,7 +648,16 @@ int sweep_blocks_per_cu(int fp64, int laguerre, int wg, int ppt, int degree)
 
 int sweep_batch_blocks_per_cu(int fp64, int laguerre, int ppt, int degree)
 {
-    return blocks_per_cu(batch_lookup(fp64, laguerre, ppt, degree), kWG);
+    const void *f = batch_lookup(fp64 & ~kAnyPlacement, laguerre, ppt, degree);
+    const int n = blocks_per_cu(f, kWG);
+    if (!(fp64 & kAnyPlacement) || n <= 1) return n;
+    int dev = 0, lds_cu = 0;
+    hipFuncAttributes fa;
+    if (hipGetDevice(&dev) != hipSuccess || hipFuncGetAttributes(&fa, f) != hipSuccess || !fa.sharedSizeBytes ||
+        hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess)
+        return 1;
+    const int sure = (int)(((size_t)lds_cu / fa.sharedSizeBytes + 1) / 2);
+    return sure < 1 ? 1 : sure < n ? sure : n;
 }
 
 // Dynamic LDS that leaves room for one workgroup of `f` per CU (more than

@@ -217,12 +217,52 @@ static void claim_queues()
     CHECK(queued == 0);
 }
 
+// Batches served side by side: whatever is in flight, the requests' groups fit
+// in what every compute unit has room for in any placement; larger ones run
+// alone.
+static void served_share()
+{
+    const am_basis b{AM_BASIS_MONOMIAL, 2};
+    const int64_t tile = 256 * 32;
+    for (int sure = 1; sure <= 2; ++sure)
+        for (int streams : {1, 2, 3, 8}) {
+            fake::batch_sure_per_cu = sure;
+            const int share = sure * fake::kCus / streams;
+            const am_server_config cfg{(size_t)2 << 30, 1e12, 1, streams, b, AM_FP64, 1};
+            am_server *sv = nullptr;
+            std::mutex mu;
+            std::map<int, bool> alone;   // by tiles
+            fake::on_sweep_batch = [&](const amq::BatchOpt *o, const int32_t *, const amq::BatchGlobal &, int grid, int) {
+                CHECK(grid >= o[0].G);
+                for (Slot &sl : sv->slots)
+                    if (sl.reqs.size() == 1 && !sl.busy && (sl.reqs[0].opt.n_paths + tile - 1) / tile == o[0].G) {
+                        std::lock_guard<std::mutex> lk(mu);
+                        alone[o[0].G] = sl.exclusive;
+                    }
+            };
+            CHECK(am_server_create(&cfg, &sv) == AM_OK);
+            const int sizes[] = {1, share - 1, share, share + 1, 2 * fake::kCus};
+            int id = 0;
+            for (int t : sizes)
+                if (t >= 1 && t <= 2 * fake::kCus) {
+                    const am_option o = option(t * tile, 2);
+                    CHECK(am_server_submit(sv, &o, id++, -1.0) == AM_OK);
+                }
+            const am_option too_big = option((2 * fake::kCus + 1) * tile, 2);
+            CHECK(am_server_submit(sv, &too_big, 99, -1.0) == AM_EDIM);
+            CHECK(am_server_destroy(sv) == AM_OK);   // finishes what is queued
+            for (const auto &[t, a] : alone) CHECK(a == (t > share));
+            CHECK(alone.size() >= 3);
+        }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
         {"mixed_timeout", mixed_timeout},
         {"order_across_streams", order_across_streams},
         {"claim_queues", claim_queues},
+        {"served_share", served_share},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {

@@ -79,7 +79,7 @@ inline hipError_t symbol_address(void **p, const void *) { return alloc(p, 1); }
 std::function<void(const amq::BatchOpt *, const int32_t *, const amq::BatchGlobal &, int grid, int mode)> on_sweep_batch;
 std::function<void(const amq::GenUnit *, int n, int max_seg_len)> on_generate_batch;
 std::function<void(const amq::SweepArgs &)> on_sweep;
-int batch_groups_per_cu = 2;
+int batch_groups_per_cu = 2, batch_sure_per_cu = 1;
 
 }  // namespace fake
 
@@ -116,7 +116,7 @@ hipError_t launch_sweep_batch(const BatchOpt *o, const int32_t *tile_opt, const 
     if (fake::on_sweep_batch) fake::on_sweep_batch(o, tile_opt, g, grid, mode);
     return hipSuccess;
 }
-int sweep_batch_blocks_per_cu(int, int, int, int) { return fake::batch_groups_per_cu; }
+int sweep_batch_blocks_per_cu(int mode, int, int, int) { return mode & kAnyPlacement ? fake::batch_sure_per_cu : fake::batch_groups_per_cu; }
 }  // namespace amq
 
 #define hipGetDevice fake::get_device
