@@ -219,9 +219,9 @@ SegSchedule make_segments(int M)
 // segment's dates: while whole schedules leave fewer than kGenFillWaves waves
 // (16 a CU, what is resident), splitting them puts idle lanes to work at the
 // cost of recomputed ancestors; and a segment's tables must let four groups
-// share a CU's LDS.
+// share a CU's LDS (261 nodes).
 constexpr int64_t kGenFillWaves = 4096;
-constexpr int kMaxSegLen = 280;
+constexpr int kMaxSegLen = (int)((amq::kLdsCu / 4 - amq::kLdsNodes) / amq::kLdsPerNode);
 
 // Nodes of the longest of M dates' 2^v segments: an interval of ceil(M / 2^v)
 // dates holds one node less, its ancestors and the root are v + 1 more.

@@ -74,6 +74,31 @@ static_assert(kMaxDates < 65536 && 2 * kMaxSlots <= 256, "bridge node packing");
 // so segments of one path block run in different waves.
 constexpr int kSegVariants = 4;    // Q = 1, 2, 4, 8
 
+// Nodes whose tail normals are evaluated together (binary64 paths): a
+// 64-point Sobol block puts 10 to 13 of its 64 points of each dimension in
+// the tails (|u - 1/2| >= 0.42; 10.24 on average, nearly always 10 or 11), so
+// the tails of 6 nodes fill one wave and seldom more (2^24 x 252: 15.64 ms per
+// call with 5 nodes, 15.49 with 6).
+constexpr int kTailChunk = 6;
+// Tail points staged per wave and chunk.  An aligned block of 64 Sobol points
+// has exactly one point in each interval [k/64, (k+1)/64) of every dimension
+// (the generator matrix's leading 6 x 6 block is triangular with unit
+// diagonal; a digital shift permutes the intervals), and the tails meet 12
+// such intervals; a wave's lanes hold 63 points of one aligned block and the
+// first of the next, so a node has at most 13 tail points.  The staging holds every lane of every node all the same, so no point
+// set could write outside it; a point's word becomes its normal in place.
+constexpr int kTailCap = kTailChunk * 64;
+
+// Dynamic LDS of a generation workgroup (bytes): the exponential's table [64]
+// f64 and the logarithm's [64] {1/F, log F} at fixed offsets (their addresses
+// are then immediates), the per-wave tail staging ([kTailCap] points, then
+// normals, and 64 spare words), then per schedule node the lane tables [16]
+// u32, every wave's block words [2] u32 and the node's dimension.
+constexpr size_t kLdsLog = 64 * 8, kLdsTz = kLdsLog + 64 * 16, kLdsSpare = kLdsTz + (size_t)kWaves * kTailCap * 8,
+                 kLdsNodes = kLdsSpare + (size_t)kWaves * 64 * 4, kLdsPerNode = 64 + kWaves * 8 + 4;
+inline size_t gen_lds_bytes(int len) { return kLdsNodes + (size_t)len * kLdsPerNode; }
+constexpr size_t kLdsCu = 160 * 1024;
+
 // Per-date constants written by the generation kernel, read by the sweep.
 //   disc = exp(-r t_k); standardised abscissa xs = S * xa + xb with
 //   xa = 1/(K sd_k), xb = -mean_k/sd_k (mean/sd of S_k/K in the money under

@@ -4,6 +4,8 @@
 
 #include "../../paper_1205_0106_amd/csrc/amq_engine.hip"
 
+#include <set>
+
 static int g_failed = 0;
 #define CHECK(c)                                                                  \
     do {                                                                          \
@@ -256,6 +258,44 @@ static void served_share()
         }
 }
 
+// Every schedule's segment forms: each covers every date, a node's parents are in
+// the slots that it reads, and the form that a launch of many blocks takes leaves
+// room for four generation groups in a CU's LDS.
+static void segments()
+{
+    for (int M = 1; M <= amq::kMaxDates; ++M) {
+        const std::vector<amq::BridgeNode> all = make_schedule(M);
+        std::vector<std::pair<int, int>> parent(M + 1, {0, 0});
+        std::vector<int> slot_date(amq::kMaxSlots, 0);
+        for (const auto &n : all) {
+            parent[n.m] = {n.sl == amq::kAnchorSlot ? -1 : slot_date[n.sl], n.sr == amq::kAnchorSlot ? -1 : slot_date[n.sr]};
+            slot_date[n.dst] = n.m;
+        }
+        SegSchedule S;
+        CHECK(host_schedule(M, &S) == AM_OK);
+        for (int v = 0; v < amq::kSegVariants && S.len[v]; ++v) {
+            CHECK(S.len[v] == seg_len(M, v));
+            std::set<int> dates;
+            for (int s = 0; s < 1 << v; ++s) {
+                std::vector<int> slot(amq::kMaxSlots, -2);
+                slot[0] = 0;
+                slot[amq::kAnchorSlot] = -1;
+                for (int q = 0; q < S.len[v]; ++q) {
+                    const amq::GenNode &n = S.nodes[S.off[v] + s * S.len[v] + q];
+                    const int m = n.md & 0xFFFF, sl = (n.slots & 0xFF) / 2, sr = (n.slots >> 8 & 0xFF) / 2, d = (n.slots >> 16) / 2;
+                    // (of a last node's repeats too: the same value again)
+                    CHECK(slot[sl] == parent[m].first && (slot[sr] == parent[m].second || n.wr == 0.0));
+                    slot[d] = m;
+                    dates.insert(m);
+                }
+            }
+            CHECK((int)dates.size() == M);
+        }
+        const int v = gen_variant(M, (int64_t)1 << 30);
+        CHECK(S.len[v] > 0 && 4 * amq::gen_lds_bytes(S.len[v]) <= amq::kLdsCu);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
@@ -263,6 +303,7 @@ int main(int argc, char **argv)
         {"order_across_streams", order_across_streams},
         {"claim_queues", claim_queues},
         {"served_share", served_share},
+        {"segments", segments},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {

@@ -60,3 +60,19 @@ def test_paths_beyond_the_narrow_exponent(orc, pricer, sigma, T, r):
     assert ok.mean() > 0.5
     assert np.all(np.abs(got[ok] / want[ok] - 1.0) <= 1e-11)
     assert np.array_equal(np.isinf(got), np.isinf(want))
+
+
+# the longest schedule whose tables let four generation groups share a CU's LDS
+# stays whole in a launch of many blocks, the next one is split; so are the
+# longest halves (521 dates) and the next (522, 523)
+@pytest.mark.parametrize("M", [261, 262, 520, 521, 522, 523])
+def test_segments_around_the_longest(pricer, M):
+    import paper_1205_0106_amd as amq
+    b, p = amq.make_basis("monomial", 2), amq.make_params(**KW)
+    few = 1000 + 5
+    print(f"  segments: M={M} N={few} and {MANY}", flush=True)
+    pricer.price(p, few, M, b, "fp64")
+    got = pricer.views(few, M, b, "fp64")["S"].clone()
+    pricer.price(p, MANY, M, b, "fp64")
+    want = pricer.views(MANY, M, b, "fp64")["S"][:, :few]
+    assert np.array_equal(got.cpu().numpy(), want.cpu().numpy())
