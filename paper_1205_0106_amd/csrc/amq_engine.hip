@@ -1354,9 +1354,11 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
         q_off[c + 1] = (int32_t)tile_opt.size();
     }
     // the list lies in one part's tile table: a table has a word per 256 padded
-    // paths, 64 and more times that part's tiles, so the part with more tiles
-    // has room for both lists
+    // paths, 32 and more times that part's tiles (64 in binary32, at the default
+    // tiles, the only ones of a launch over both), so the part with more tiles has
+    // room for both lists
     const int ht = h0 == h1 ? h0 : (B[0].tiles >= B[1].tiles ? 0 : 1);
+    if (tile_opt.size() * 4 > S.P[ht].off_part - S.P[ht].off_tiles) return fail(AM_EDEVICE, "tile table overflow");
 
     ProfRec *pr = nullptr;
     if (g_prof.on) {

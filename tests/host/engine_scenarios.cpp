@@ -296,6 +296,40 @@ static void segments()
     }
 }
 
+// The tile list of a book fits the table it is uploaded to, also where one part's
+// holds both parts' lists; a plan whose table is too short is refused before the
+// upload.
+static void tile_table()
+{
+    const am_basis b{AM_BASIS_MONOMIAL, 2};
+    DevState *st = nullptr;
+    CHECK(get_state(&st) == AM_OK);
+    for (int n32 : {0, 1, 3, 40})
+        for (int n64 : {0, 1, 50, 200}) {
+            if (n32 + n64 == 0) continue;
+            std::vector<am_option> o;
+            for (int i = 0; i < n32; ++i) o.push_back(option(16384 + 40000 * (i % 2), 3));
+            for (int i = 0; i < n64; ++i) o.push_back(option(10 + 80 * i, 3));
+            SplitBatch B;
+            split_batch(o.data(), (int32_t)o.size(), AM_FP32_BULK, B);
+            int words = 0;
+            fake::on_sweep_batch = [&](const amq::BatchOpt *, const int32_t *, const amq::BatchGlobal &g, int, int) {
+                words = g.total_tiles;
+            };
+            void *w = nullptr;
+            CHECK(fake::alloc(&w, B.total) == hipSuccess);
+            CHECK(enqueue_split(st, B, b, AM_FP32_BULK, (char *)w, (hipStream_t)0xA0, nullptr, true, nullptr, 0, nullptr) == AM_OK);
+            CHECK(B.one_sweep == (n32 > 0 && n64 > 0));
+            if (B.one_sweep) {
+                const size_t room[2] = {B.P[0].off_part - B.P[0].off_tiles, B.P[1].off_part - B.P[1].off_tiles};
+                CHECK((size_t)words * 4 <= (room[0] > room[1] ? room[0] : room[1]));
+            }
+            for (int h = 0; h < 2; ++h) B.P[h].off_part = B.P[h].off_tiles;
+            CHECK(enqueue_split(st, B, b, AM_FP32_BULK, (char *)w, (hipStream_t)0xA0, nullptr, true, nullptr, 0, nullptr) == AM_EDEVICE);
+            fake::release(w);
+        }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
@@ -304,6 +338,7 @@ int main(int argc, char **argv)
         {"claim_queues", claim_queues},
         {"served_share", served_share},
         {"segments", segments},
+        {"tile_table", tile_table},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {
