@@ -252,9 +252,8 @@ int sweep_batch_blocks_per_cu(int fp64, int laguerre, int ppt, int degree);
 // in its LDS a hole for the k-th is left if (2k - 1) groups' LDS fit (one of the
 // 66 KB tiles, though two fit side by side).
 constexpr int kAnyPlacement = 8;
-// Sweep kernel tables, one translation unit per (precision, basis kind);
-// kind 0: single option, 256-thread groups; 1: many options; 2: single
-// option, 512-thread groups.  Null where not built.
+// Sweep kernel tables, one translation unit per (precision, basis kind); kinds
+// as sweep_addr says.  Null where not built.
 const void *sweep_table_f32_mono(int ppt, int degree, int kind);
 const void *sweep_table_f32_lag(int ppt, int degree, int kind);
 const void *sweep_table_f64_mono(int ppt, int degree, int kind);

@@ -666,8 +666,14 @@ static size_t one_per_cu_lds(int dev, const void *f)
 hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream_t s)
 {
     if (wg != kWG && wg != 512) return hipErrorInvalidValue;
-    // slab-resident tiles come in a call form (kind 3) and a put form (kind 2)
-    const void *f = (wg == 512 && a.is_call) ? sweep_lookup(fp64, a.laguerre, ppt, a.degree, 3) : nullptr;
+    const uint32_t G = (uint32_t)a.G;
+    const bool spin = row_words(a.degree) == 16 ? spins_on_rows<16>(G) : spins_on_rows<32>(G);
+    const bool keep = ppt * (fp64 ? 8 : 4) <= 64;
+    // slab-resident tiles come in a call form (kind 3) and a put form (kind 2),
+    // register-resident ones in a form for few groups (4) and one for more (2)
+    const void *f = nullptr;
+    if (wg == 512 && keep && spin) f = sweep_lookup(fp64, a.laguerre, ppt, a.degree, 4);
+    else if (wg == 512 && a.is_call) f = sweep_lookup(fp64, a.laguerre, ppt, a.degree, 3);
     if (!f) f = sweep_lookup(fp64, a.laguerre, ppt, a.degree, wg == 512 ? 2 : 0);
     if (!f) return hipErrorInvalidValue;
     SweepArgs args = a;
@@ -683,9 +689,6 @@ hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream
     // measured 19 us slower per call, in the kernel's own event interval)
     // few groups of a register-resident tile: all on one XCD, where its compute
     // units hold one each; more of another tile are relayed, as dealt
-    const uint32_t G = (uint32_t)a.G;
-    const bool spin = row_words(a.degree) == 16 ? spins_on_rows<16>(G) : spins_on_rows<32>(G);
-    const bool keep = ppt * (fp64 ? 8 : 4) <= 64;
     const bool strided = G > 1 && spin && keep && dyn > 0 && G * kXcds <= (uint32_t)cus;
     args.xcd_stride = strided ? (int)kXcds : !spin && !keep && G <= kFlatMaxGroups ? 1 : 0;
     const uint32_t grid = strided ? G * kXcds : G;

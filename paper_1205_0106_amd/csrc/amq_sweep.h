@@ -468,7 +468,7 @@ __device__ __forceinline__ bool rows_stay_local(const SweepArgs &a, uint32_t gid
 // of two dates are cached in LDS ([2][path][thread], each thread touching
 // only its own entries).  Date constants come through uniform vector loads
 // issued a date ahead.
-template <typename T, int PPT, int D, bool LAG, int WG>
+template <typename T, int PPT, int D, bool LAG, int WG, int FORM>
 __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restrict__ S, uint32_t gid,
                                            const TileIO<T, PPT, WG> &io, T (&pv)[PPT], uint32_t &epoch, bool &alive,
                                            double (*s_red)[32], double (*s_red2)[32], double *s_tot,
@@ -505,10 +505,10 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
     // in-the-money count from wave ballots (scalar unit); returns the group's
     // totals in the first wave's lanes at their words of the row (Gram sums
     // 0..NA-1, count NV-1), or, with kSplit, leaves the reduction to
-    // split_sum_reduce while the first wave waits for this date's rows (that
-    // wave's share of the reduction and a barrier stood between it and the
-    // rows: 16 groups x 50 dates 167 -> 157 us per call, 15 x 365 1106 -> 1017,
-    // 256 groups x 100 dates 823 -> 809)
+    // split_sum_reduce, which the first wave has no part in: with few groups it
+    // waits for this date's rows meanwhile (its share of the reduction and a
+    // barrier stood between it and the rows: 16 groups x 50 dates 167 -> 157 us
+    // per call, 15 x 365 1106 -> 1017)
     constexpr bool kSplit = WG == 512 && NA <= 7;
     const uint32_t cg = tid == NV - 1 ? (uint32_t)NA : tid < NA ? (uint32_t)tid : (uint32_t)NG;
     const uint32_t cr = tid >= NA ? (uint32_t)(tid - NA) : (uint32_t)NB;   // right-hand side: words NA..NA+NB-1
@@ -583,7 +583,7 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         gt = split_sum_fetch<NG, 1, WG>(s_red2, cg);
     }
     // (the first wave publishes; the announcements have had the first pass to arrive)
-    const bool local = rows_stay_local<RW>(a, gid);
+    const bool local = FORM != kCounterForm && rows_stay_local<RW>(a, gid);
 
     for (int k = M - 1; k >= 1; --k) {
         uint64_t stamp[3];
@@ -630,7 +630,7 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         else rt = group_sum<NB, 0, WG>(rs, s_red, cr);
         ++epoch;
         stamp[0] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG, false>(cr < (uint32_t)NB ? rt : gt, gid, G, a.rows, a.sync, a.err, epoch,
+        if (!allreduce_publish<NV, RW, WG, FORM>(cr < (uint32_t)NB ? rt : gt, gid, G, a.rows, a.sync, a.err, epoch,
                                            a.spin_limit, s_tot, s_red, s_flag, local)) {
             alive = false;
             return;
@@ -650,7 +650,7 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
         if (k >= 2) gt = gram_pass(sn, xan, xbn, wbuf(k - 1));
         stamp[1] = record_clock(gid);
 
-        if (!gather_and_solve<NV, RW, WG, false>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag,
+        if (!gather_and_solve<NV, RW, WG, FORM>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag,
                                                   k >= 2,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
@@ -662,7 +662,9 @@ __device__ __forceinline__ void sweep_keep(const SweepArgs &a, const T *__restri
                                                   }
                                               }
                                           },
-                                          gram_reduce)) {
+                                          [&]() {
+                                              if (FORM == kFewForm || k >= 2) gram_reduce();
+                                          })) {
             alive = false;
             return;
         }
@@ -761,9 +763,9 @@ __device__ __forceinline__ void sweep_stream(const SweepArgs &a, const T *__rest
         ++epoch;
         // (a clock read before group_sum would pin the moment pass's schedule)
         stamp[0] = stamp[1] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG, true>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+        if (!allreduce_publish<NV, RW, WG, kRelayForm>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
                                            s_flag, local) ||
-            !gather_and_solve<NV, RW, WG, true>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+            !gather_and_solve<NV, RW, WG, kRelayForm>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
                                               if (tid == 0) {
@@ -1139,9 +1141,9 @@ __device__ __forceinline__ void sweep_resident(const SweepArgs &a, const float *
         const double at = group_sum<NV, 1, WG>(tv, s_red, tid == 0 ? (uint32_t)NV - 1u : (uint32_t)tid);
         ++epoch;
         stamp[0] = stamp[1] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG, true>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+        if (!allreduce_publish<NV, RW, WG, kRelayForm>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
                                            s_flag, local) ||
-            !gather_and_solve<NV, RW, WG, true>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+            !gather_and_solve<NV, RW, WG, kRelayForm>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
                                               solve_date_wave<D>(s_tot, s_beta, s_L);
@@ -1395,9 +1397,9 @@ __device__ __forceinline__ void sweep_slab(const SweepArgs &a, const T *__restri
         const double at = group_sum<NV, 1, WG>(tv, s_red, tid == 0 ? (uint32_t)NV - 1u : (uint32_t)tid);
         ++epoch;
         stamp[0] = stamp[1] = record_clock(gid);
-        if (!allreduce_publish<NV, RW, WG, true>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+        if (!allreduce_publish<NV, RW, WG, kRelayForm>(at, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
                                            s_flag, local) ||
-            !gather_and_solve<NV, RW, WG, true>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+            !gather_and_solve<NV, RW, WG, kRelayForm>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
                                           [&]() {
                                               const uint64_t c0 = record_clock(gid);
                                               if (tid == 0) {
@@ -1476,8 +1478,8 @@ __device__ __forceinline__ void requests_landed()
 }
 
 // SIDE: 1 call, 2 put (slab-resident tiles are compiled per payoff side), 0
-// either (read from the arguments).
-template <typename T, int PPT, int D, bool LAG, int WG, int SIDE = 0>
+// either (read from the arguments).  FORM: a register-resident tile's exchange.
+template <typename T, int PPT, int D, bool LAG, int WG, int SIDE = 0, int FORM = kAnyForm>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a, const T *__restrict__ S, uint32_t gid,
                                            uint32_t e0, T (&pv)[PPT], uint32_t &epoch, bool &alive,
                                            uint32_t &skipped, SweepLds<T, PPT, LAG, WG> &L)
@@ -1485,7 +1487,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const T *__restri
     const TileIO<T, PPT, WG> io(gid, e0);
     if constexpr (!Slab<T, PPT, LAG>::on) sweep_terminal<T, PPT, WG>(a, S, io, pv);
     if constexpr (SweepShape<T, PPT>::KEEP) {
-        sweep_keep<T, PPT, D, LAG, WG>(a, S, gid, io, pv, epoch, alive, L.red, L.red2, L.tot, L.beta, L.wl, L.x,
+        sweep_keep<T, PPT, D, LAG, WG, FORM>(a, S, gid, io, pv, epoch, alive, L.red, L.red2, L.tot, L.beta, L.wl, L.x,
                                        L.flag, L.clk, skipped);
     } else if constexpr (Slab<T, PPT, LAG>::on) {
         sweep_slab<T, PPT, D, WG>(a, S, gid, slab_range<PPT * WG / 4>(a.N, gid, (uint32_t)a.G), pv, epoch, alive, L.red,
@@ -1511,13 +1513,14 @@ __device__ __forceinline__ double moment_shift(const SweepArgs &a)
     return h0 > 0.0 ? h0 : 0.0;
 }
 
-template <typename T, int PPT, int D, bool LAG, int WG>
+template <typename T, int PPT, int D, bool LAG, int WG, int KEEP_FORM = kAnyForm>
 __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, uint32_t e0,
                                             const T (&pv)[PPT], uint32_t epoch, uint32_t skipped,
                                             double (*s_red)[32], double *s_tot, int *s_flag)
 {
     constexpr int VW = 16 / sizeof(T), NVEC = PPT / VW;
-    constexpr bool SLAB = Slab<T, PPT, LAG>::on, RELAY = !SweepShape<T, PPT>::KEEP;
+    constexpr bool SLAB = Slab<T, PPT, LAG>::on;
+    constexpr int FORM = SweepShape<T, PPT>::KEEP ? KEEP_FORM : kRelayForm;
     constexpr uint32_t JS = (SLAB ? WG : 64) * VW;
     const int tid = threadIdx.x;
     const int64_t N = a.N;
@@ -1548,9 +1551,9 @@ __device__ __forceinline__ void sweep_final(const SweepArgs &a, uint32_t gid, ui
     const double ft = group_sum<2, 0, WG>(fin, s_red, (uint32_t)tid);
     ++epoch;
     const uint32_t G = (uint32_t)a.G;
-    if (!allreduce_publish<2, row_words(D), WG, RELAY>(ft, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
+    if (!allreduce_publish<2, row_words(D), WG, FORM>(ft, gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red,
                                                 s_flag) ||
-        !gather_and_solve<2, row_words(D), WG, RELAY>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
+        !gather_and_solve<2, row_words(D), WG, FORM>(gid, G, a.rows, a.sync, a.err, epoch, a.spin_limit, s_tot, s_red, s_flag, false,
                                                []() {}))
         return;
     if (gid == 0) {
@@ -1602,7 +1605,7 @@ __device__ __forceinline__ uint32_t tile_e0(uint32_t gid)
 // WG: threads per group, 256 or (register-resident tiles) 512: two waves
 // of one group per SIMD, so one wave's dependent binary64 latencies and
 // scalar/LDS issue slots overlap the other's vector work.
-template <typename T, int PPT, int D, bool LAG, int WG, int SIDE = 0>
+template <typename T, int PPT, int D, bool LAG, int WG, int SIDE = 0, int FORM = kAnyForm>
 __global__ void __launch_bounds__(WG)
 __attribute__((amdgpu_waves_per_eu(WG == 512 ? 2 : SweepShape<T, PPT>::template waves<D, LAG>())))
 sweep_kernel(SweepArgs a, const T *__restrict__ S)
@@ -1612,13 +1615,13 @@ sweep_kernel(SweepArgs a, const T *__restrict__ S)
 
     if (a.xcd_stride > 1 && blockIdx.x % (uint32_t)a.xcd_stride != 0) return;   // (another XCD's group)
     const uint32_t gid = a.xcd_stride > 1 ? blockIdx.x / (uint32_t)a.xcd_stride : blockIdx.x;
-    if (a.xcd_stride > 0) xcd_announce<row_words(D)>(a.rows, gid, (uint32_t)a.G);
+    if (FORM != kCounterForm && a.xcd_stride > 0) xcd_announce<row_words(D)>(a.rows, gid, (uint32_t)a.G);
     const uint32_t e0 = tile_e0<T, PPT, WG>(gid);
     T pv[PPT];
     uint32_t epoch = 0, skipped = 0;
     bool alive = true;
-    sweep_body<T, PPT, D, LAG, WG, SIDE>(a, S, gid, e0, pv, epoch, alive, skipped, L);
-    if (alive) sweep_final<T, PPT, D, LAG, WG>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
+    sweep_body<T, PPT, D, LAG, WG, SIDE, FORM>(a, S, gid, e0, pv, epoch, alive, skipped, L);
+    if (alive) sweep_final<T, PPT, D, LAG, WG, FORM>(a, gid, e0, pv, epoch, skipped, L.red, L.tot, L.flag);
     requests_landed<T, PPT, LAG, WG>();
 }
 
@@ -1732,19 +1735,23 @@ sweep_mixed_kernel(const BatchOpt *__restrict__ opts, const int32_t *__restrict_
 // Kernel addresses by (paths per thread, degree) for one precision and basis
 // kind; `kind` selects the single-option kernel with 256-thread groups (0),
 // the many-option kernel (1) or the single-option kernel with 512-thread
-// groups (2; for slab-resident tiles the put form), and the call form of a
-// slab-resident tile (3).  Null where not built.  Each (precision, basis
+// groups (2; for slab-resident tiles the put form, for register-resident ones
+// the form of more groups than spins_on_rows), the call form of a
+// slab-resident tile (3) and the few-group form of a register-resident one
+// (4).  Null where not built.  Each (precision, basis
 // kind) pair is instantiated in its own translation unit.
 // ---------------------------------------------------------------------------
 template <typename T, int PPT, int D, bool LAG, int KIND>
 inline const void *sweep_addr()
 {
-    constexpr bool res = Resident<T, PPT, 512, LAG>::on;
+    constexpr bool res = Resident<T, PPT, 512, LAG>::on, keep = SweepShape<T, PPT>::KEEP;
     if constexpr (KIND == 1) return (const void *)&sweep_batch_kernel<T, PPT, D, LAG>;
     else if constexpr (KIND == 3) {
         if constexpr (res) return (const void *)&sweep_kernel<T, PPT, D, LAG, 512, 1>;
         else return nullptr;
-    } else if constexpr (KIND == 2) return (const void *)&sweep_kernel<T, PPT, D, LAG, 512, res ? 2 : 0>;
+    } else if constexpr (KIND == 2) {
+        return (const void *)&sweep_kernel<T, PPT, D, LAG, 512, res ? 2 : 0, keep ? kCounterForm : kAnyForm>;
+    } else if constexpr (KIND == 4) return (const void *)&sweep_kernel<T, PPT, D, LAG, 512, 0, kFewForm>;
     else return (const void *)&sweep_kernel<T, PPT, D, LAG, kWG>;
 }
 
@@ -1778,6 +1785,14 @@ inline const void *sweep_table(int ppt, int degree, int kind)
             default: return nullptr;
             }
         }
+        if (kind == 4) {
+            switch (ppt) {
+            case 2: return sweep_entry<T, 2, LAG, 4>(degree);
+            case 4: return sweep_entry<T, 4, LAG, 4>(degree);
+            case 8: return sweep_entry<T, 8, LAG, 4>(degree);
+            default: return nullptr;
+            }
+        }
         if (kind == 2) {
             switch (ppt) {
             case 2: return sweep_entry<T, 2, LAG, 2>(degree);
@@ -1801,6 +1816,13 @@ inline const void *sweep_table(int ppt, int degree, int kind)
             switch (ppt) {
             case 16: return sweep_entry<T, 16, LAG, 1>(degree);
             case 64: return sweep_entry<T, 64, LAG, 1>(degree);
+            default: return nullptr;
+            }
+        }
+        if (kind == 4) {
+            switch (ppt) {
+            case 4: return sweep_entry<T, 4, LAG, 4>(degree);
+            case 8: return sweep_entry<T, 8, LAG, 4>(degree);
             default: return nullptr;
             }
         }

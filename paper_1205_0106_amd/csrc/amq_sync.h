@@ -278,10 +278,10 @@ __device__ void reduce_partials(const double *part, uint32_t G, double *tot, dou
 // fixed order.  Three forms by group count:
 //  - few groups (spins_on_rows): the first wave of every group reads all rows;
 //  - up to kFlatMaxGroups, in tiles with work to do behind the exchange
-//    (register-resident; RELAY false): flat.  Thread 0 bumps its team's arrival
+//    (register-resident): flat.  Thread 0 bumps its team's arrival
 //    counter with the row; behind the overlapped work the whole group reads
 //    every row at once, and only on a miss waits for the counters;
-//  - up to kFlatMaxGroups, in other tiles (RELAY): relayed.  Group g belongs to
+//  - up to kFlatMaxGroups, in other tiles: relayed.  Group g belongs to
 //    team g mod kXcds, on one XCD where workgroups are dealt to XCDs in turn;
 //    the first member (group t of team t) adds its team's rows, up to 32 and
 //    from its own L2, and publishes a team row; every group reads the kXcds
@@ -314,13 +314,9 @@ __device__ void reduce_partials(const double *part, uint32_t G, double *tot, dou
 // read again, at most `limit` times.  Each thread adds its rows in ascending
 // order, then the group's lanes and waves in a fixed tree.  tot: LDS
 // [>= NV], valid in every thread on true.
-// meanwhile(): work of the whole group that needs no total, done once behind
-// the first batch of reads.
-struct Nothing { __device__ __forceinline__ void operator()() const {} };
-template <int NV, int RW, int WG, typename OnMiss, typename Work = Nothing>
+template <int NV, int RW, int WG, typename OnMiss>
 __device__ inline bool sum_rows(const uint64_t *slots, uint32_t count, uint64_t tag, uint32_t *err,
-                                uint32_t limit, double *tot, double (*s_red)[32], int *s_flag, OnMiss on_miss,
-                                Work meanwhile = Work())
+                                uint32_t limit, double *tot, double (*s_red)[32], int *s_flag, OnMiss on_miss)
 {
     const uint32_t tx = tid_x();
     static_assert(RW == 16 || RW == 32, "row width");
@@ -345,7 +341,6 @@ __device__ inline bool sum_rows(const uint64_t *slots, uint32_t count, uint64_t 
                            ? __hip_atomic_load(slots + (size_t)r * RW + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                            : tag;
             }
-            if (it == 0 && r0 == 0) meanwhile();
 #pragma unroll
             for (int k = 0; k < KB; ++k) {
                 bad |= (w[k] & 3u) != tag;
@@ -418,6 +413,27 @@ constexpr uint32_t kXcds = 8;
 constexpr uint32_t kFlatMaxGroups = 32 * kXcds;
 template <int RW> __host__ __device__ __forceinline__ bool spins_on_rows(uint32_t G) { return G * (uint32_t)RW <= kSpinWords; }
 
+// Which forms of the sum a kernel holds.  The single-option sweeps of
+// register-resident tiles are compiled apart for few groups and for counters:
+// with both in one kernel each date took 0.15 to 0.25 us longer (binary32,
+// degree 2, 49 groups x 50 dates 214 us per call, apart 203; 10^5 paths x 10
+// dates 51.8 and 49.4).
+enum : int {
+    kAnyForm,       // few groups, flat and teams
+    kRelayForm,     // few groups, relayed and teams
+    kFewForm,       // few groups
+    kCounterForm,   // flat and teams
+};
+
+// Whether the first wave gathers the totals alone: rows spun on, or relayed.
+template <int FORM, int RW>
+__device__ __forceinline__ bool first_wave_gathers(uint32_t G)
+{
+    if constexpr (FORM == kFewForm) return true;
+    else if constexpr (FORM == kCounterForm) return false;
+    else return spins_on_rows<RW>(G) || (FORM == kRelayForm && G <= kFlatMaxGroups);
+}
+
 // Publishing half of the sum: the first wave's lanes store the group's row
 // (lane c: word c); where counters are kept (flat, and above kFlatMaxGroups)
 // thread 0 bumps its team's, and above kFlatMaxGroups the team's last arriver
@@ -425,7 +441,7 @@ template <int RW> __host__ __device__ __forceinline__ bool spins_on_rows(uint32_
 // The caller may do independent work before the gathering half with the same
 // epoch.  Uses s_flag[1 + WG / 64] (the team-last flag), so that the
 // gathering half's flags never overlap it.  local: see put_row.
-template <int NV, int RW, int WG, bool RELAY>
+template <int NV, int RW, int WG, int FORM>
 __device__ inline bool allreduce_publish(double v, uint32_t gid, uint32_t G, uint64_t *rows,
                                          uint32_t *words, uint32_t *err, uint32_t epoch, uint32_t limit,
                                          double *tot, double (*s_red)[32], int *s_flag, bool local = false)
@@ -433,7 +449,7 @@ __device__ inline bool allreduce_publish(double v, uint32_t gid, uint32_t G, uin
     const uint32_t tx = tid_x();
     static_assert(NV <= RW && RW <= 32 && (RW & (RW - 1)) == 0, "row width");
     const uint64_t tag = epoch & 3u;
-    if (G == 1) {
+    if (FORM != kCounterForm && G == 1) {
         // alone: the group's sums are the totals (rounded as a row's words are)
         if (tx < (uint32_t)NV)
             tot[tx] = __longlong_as_double((long long)((uint64_t)__double_as_longlong(v) & ~3ull));
@@ -441,7 +457,7 @@ __device__ inline bool allreduce_publish(double v, uint32_t gid, uint32_t G, uin
     }
     uint64_t *slots = rows + (size_t)(epoch & 1u) * G * RW;
     put_row<NV>(slots + (size_t)gid * RW, v, tag, local);
-    if (spins_on_rows<RW>(G) || (RELAY && G <= kFlatMaxGroups)) return true;
+    if (first_wave_gathers<FORM, RW>(G)) return true;
     uint64_t *tslots = rows + (size_t)2 * G * RW + (size_t)(epoch & 1u) * kMaxTeams * RW;
     const uint32_t TS = team_size(G);
     const uint32_t tau = gid / TS;
@@ -519,7 +535,7 @@ __device__ __forceinline__ bool spin_rows(const uint64_t *slots, uint32_t stride
 
 // The totals of `epoch` where rows are spun on or relayed, by the first wave
 // alone.  tot: LDS [>= NV], written by lanes 0..NV-1.
-template <int NV, int RW, int WG, bool RELAY>
+template <int NV, int RW, int WG, int FORM>
 __device__ __forceinline__ bool first_wave_totals(uint64_t *rows, uint32_t gid, uint32_t G, uint32_t *err,
                                                   uint32_t epoch, uint32_t limit, double *tot)
 {
@@ -528,12 +544,12 @@ __device__ __forceinline__ bool first_wave_totals(uint64_t *rows, uint32_t gid, 
     const uint64_t *slots = rows + (size_t)(epoch & 1u) * G * RW;
     const uint32_t lane = tid_x() & 63u;
     double t = 0.0;
-    if (spins_on_rows<RW>(G)) {
+    if (FORM == kFewForm || spins_on_rows<RW>(G)) {
         const bool ok = G * (uint32_t)RW <= kSpinWords / 2
                             ? spin_rows<NV, RW, WG, 4>(slots, RW, G, tag, err, limit, t)
                             : spin_rows<NV, RW, WG, 8>(slots, RW, G, tag, err, limit, t);
         if (!ok) return false;
-    } else if constexpr (RELAY) {
+    } else if constexpr (FORM == kRelayForm) {
         uint64_t *tslots = rows + (size_t)2 * G * RW + (size_t)(epoch & 1u) * kMaxTeams * RW;
         if (gid < kXcds) {
             if (!spin_rows<NV, RW, WG, RW / 2>(slots + (size_t)gid * RW, kXcds * RW, (G - gid + kXcds - 1) / kXcds, tag,
@@ -610,10 +626,10 @@ __device__ __forceinline__ void wave_lds_fence()
 // work since publishing, so the rows usually all carry the tag already) the
 // rows are read once before the counters, which saves their round trip.
 // Teams: wave 0 waits on the team rows' tags, then the team rows are summed.
-template <int NV, int RW, int WG, typename Work>
+template <int NV, int RW, int WG>
 __device__ inline bool allreduce_gather(uint32_t G, uint64_t *rows, uint32_t *words, uint32_t *err,
                                         uint32_t epoch, uint32_t limit, double *tot, double (*s_red)[32],
-                                        int *s_flag, bool rows_first, Work meanwhile)
+                                        int *s_flag, bool rows_first)
 {
     const uint32_t tx = tid_x();
     const uint64_t tag = epoch & 3u;
@@ -656,27 +672,32 @@ __device__ inline bool allreduce_gather(uint32_t G, uint64_t *rows, uint32_t *wo
     return sum_rows<NV, RW, WG>(flat ? slots : tslots, flat ? G : NT, tag, err, limit, tot, s_red, s_flag,
                                 [&](uint32_t attempt) {
                                     return (early && attempt == 1) ? poll() : rows_backoff(err, s_flag);
-                                },
-                                meanwhile);
+                                });
 }
 
 // Gathering half with the follow-up work `solve` (the first wave only, on the
 // totals in LDS): one group barrier between the totals and the group's use of
 // what `solve` left in LDS.  s_flag[0] carries the outcome.  meanwhile():
-// work that needs no total and in which, where rows are spun on or relayed,
-// the first wave has no part: the other waves do it while the first waits.
-template <int NV, int RW, int WG, bool RELAY, typename Solve, typename Work = Nothing>
+// work that needs no total and in which the first wave has no part.  Where rows
+// are spun on or relayed the other waves do it while the first waits; else it
+// comes before the rows are first read, which then more often finds them there
+// (400000 paths x 100 dates, Laguerre, binary64 514 us per call, behind the
+// first reads 523; binary32, degree 2, 10^5 x 50 203 and 208; 2^20 x 100 the same
+// either way).
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <int NV, int RW, int WG, int FORM, typename Solve, typename Work = Nothing>
 __device__ inline bool gather_and_solve(uint32_t gid, uint32_t G, uint64_t *rows, uint32_t *words, uint32_t *err,
                                         uint32_t epoch, uint32_t limit, double *tot, double (*s_red)[32], int *s_flag,
                                         bool rows_first, Solve solve, Work meanwhile = Work())
 {
     const uint32_t tx = tid_x();
-    const bool one = spins_on_rows<RW>(G) || (RELAY && G <= kFlatMaxGroups);
-    if (!one && !allreduce_gather<NV, RW, WG>(G, rows, words, err, epoch, limit, tot, s_red, s_flag, rows_first,
-                                              meanwhile))
-        return false;
+    const bool one = first_wave_gathers<FORM, RW>(G);
+    if (!one) {
+        meanwhile();
+        if (!allreduce_gather<NV, RW, WG>(G, rows, words, err, epoch, limit, tot, s_red, s_flag, rows_first)) return false;
+    }
     if (tx < 64) {
-        const bool ok = !one || first_wave_totals<NV, RW, WG, RELAY>(rows, gid, G, err, epoch, limit, tot);
+        const bool ok = !one || first_wave_totals<NV, RW, WG, FORM>(rows, gid, G, err, epoch, limit, tot);
         if (ok) {
             wave_lds_fence();
             solve();

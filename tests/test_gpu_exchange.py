@@ -38,3 +38,29 @@ def test_row_exchange_edges(orc, groups, degree, ragged):
     rec = pr.views(N, M, b, "fp64")["rec"].cpu().numpy()
     for k in range(1, M):
         assert rec[k, 8] == 1.0 and 0 < rec[k, 36] <= rec[k, 32] <= rec[k, 33] <= rec[k, 34]
+
+
+# 512-thread register-resident tiles are compiled apart for few groups and for
+# more; 256-thread ones hold every form.  The two differ in the order of their
+# sums only: 1e-16 relative each, amplified by a condition number below 1e4, in a
+# price of order 10.
+@pytest.mark.parametrize("dtype,ppt", [("fp32", 4), ("fp64", 2)])
+@pytest.mark.parametrize("basis,degree,groups", [("monomial", 1, 32), ("monomial", 2, 33), ("monomial", 4, 32), ("monomial", 4, 33),
+                                                 ("monomial", 5, 16), ("monomial", 5, 17), ("laguerre", 3, 9),
+                                                 ("laguerre", 3, 32), ("laguerre", 3, 33), ("laguerre", 3, 200)])
+def test_few_and_more_groups(dtype, ppt, basis, degree, groups):
+    import torch
+    import paper_1205_0106_amd as amq
+    assert torch.cuda.is_available()
+    pr = amq.Pricer(0)
+    p, b = amq.make_params(S0=100.0, K=102.0, r=0.05, sigma=0.3, T=1.0, is_call=False), amq.make_basis(basis, degree)
+    N, M = groups * 512 * ppt - 3, 7
+    print(f"  exchange: {dtype} {basis} {degree} groups={groups}", flush=True)
+    got = {}
+    for wg in (512, 256):
+        amq.am_debug_set_sweep_tile(wg, ppt)
+        try:
+            got[wg] = pr.price(p, N, M, b, dtype)
+        finally:
+            amq.am_debug_set_sweep_tile(0, 0)
+    assert abs(got[512][0] - got[256][0]) <= 1e-10 and abs(got[512][1] - got[256][1]) <= 1e-10
