@@ -423,7 +423,7 @@ void am_debug_set_sweep_tile(int32_t wg, int32_t ppt);
 
 /* Test hook: bound the device-side barrier waits of subsequent calls on this
  * thread, and of the servers it creates from then on, to `spins` polls (0
- * restores the default).  A wait that runs out
+ * restores the default; at most 2^30 - 2 are counted).  A wait that runs out
  * makes the call return AM_ETIMEOUT after every workgroup has exited. */
 void am_debug_set_spin_limit(uint32_t spins);
 

@@ -46,6 +46,9 @@ int g_live_servers = 0;
 thread_local uint32_t g_spin_limit = 0;
 thread_local int32_t g_batch_ppt = 0;   // batch tile choice (0 = default or tuned)
 constexpr uint32_t kDefaultSpin = 1u << 22;
+// Waits that count four polls as one (spin_rows) compare with a 32-bit count:
+// a limit beyond this would never be reached.
+constexpr uint32_t kMaxSpin = (1u << 30) - 2;
 
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 int fail(int code, const char *fmt, ...)
@@ -2228,7 +2231,7 @@ int am_debug_schedule(int32_t n_dates, int32_t *m, int32_t *dim, int32_t *left, 
     return AM_OK;
 }
 
-void am_debug_set_spin_limit(uint32_t spins) { g_spin_limit = spins; }
+void am_debug_set_spin_limit(uint32_t spins) { g_spin_limit = spins < kMaxSpin ? spins : kMaxSpin; }
 
 int am_shutdown(void)
 {

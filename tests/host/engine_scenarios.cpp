@@ -330,6 +330,25 @@ static void tile_table()
         }
 }
 
+// No limit on the polls of a wait makes it endless: a wait that counts four polls
+// as one exceeds the limit before its 32-bit count wraps.
+static void spin_limit()
+{
+    const am_basis b{AM_BASIS_MONOMIAL, 2};
+    const am_option o = option(20000, 4);
+    const size_t nb = am_workspace_bytes(o.n_paths, o.n_dates, b, AM_FP64);
+    void *w = nullptr;
+    CHECK(fake::alloc(&w, nb) == hipSuccess);
+    uint32_t seen = 0;
+    fake::on_sweep = [&](const amq::SweepArgs &a) { seen = a.spin_limit; };
+    for (uint32_t limit : {1u, 1000u, (1u << 30) - 2, (1u << 30) - 1, 1u << 30, 0xFFFFFFFFu, 0u}) {
+        am_debug_set_spin_limit(limit);
+        CHECK(am_price_american_ex(&o.params, o.n_paths, o.n_dates, b, AM_FP64, w, nb, (hipStream_t)0xA0, nullptr) == AM_OK);
+        CHECK(seen > 0 && seen < 0xFFFFFFFFu / 4);
+        if (limit && limit <= (1u << 30) - 2) CHECK(seen == limit);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
@@ -339,6 +358,7 @@ int main(int argc, char **argv)
         {"served_share", served_share},
         {"segments", segments},
         {"tile_table", tile_table},
+        {"spin_limit", spin_limit},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {
