@@ -421,6 +421,13 @@ void am_debug_set_sweep_wide(int32_t allow);
  * (differences at rounding level). */
 void am_debug_set_sweep_tile(int32_t wg, int32_t ppt);
 
+/* Test hook: launch single-option sweeps of few groups on this thread as every
+ * stride-th workgroup (0 restores the default, 8, which places them on one XCD;
+ * another stride spreads them over several, whose exchange then goes through
+ * memory).  Ignored where groups x stride exceed the compute units.  Results are
+ * the same. */
+void am_debug_set_group_stride(int32_t stride);
+
 /* Test hook: bound the device-side barrier waits of subsequent calls on this
  * thread, and of the servers it creates from then on, to `spins` polls (0
  * restores the default; at most 2^30 - 2 are counted).  A wait that runs out

@@ -176,6 +176,8 @@ def lib():
         L.am_profile_enable.restype = ctypes.c_int
         L.am_profile_read.argtypes = [P(dbl), P(i64)]
         L.am_profile_read.restype = ctypes.c_int
+        L.am_debug_set_group_stride.argtypes = [i32]
+        L.am_debug_set_group_stride.restype = None
         L.am_debug_set_spin_limit.argtypes = [ctypes.c_uint32]
         L.am_debug_set_spin_limit.restype = None
         _lib = L
@@ -504,6 +506,11 @@ def am_profile_read():
     n = ctypes.c_int64()
     _check(lib().am_profile_read(ms, ctypes.byref(n)))
     return ms[0], ms[1], n.value
+
+
+def am_debug_set_group_stride(stride: int) -> None:
+    """Workgroups per group of few-group sweeps on this thread (0: default)."""
+    lib().am_debug_set_group_stride(int(stride))
 
 
 def am_debug_set_spin_limit(spins: int) -> None:

@@ -44,6 +44,7 @@ std::vector<void *> g_pinned_all;       // every thread's pinned result buffer
 std::vector<hipEvent_t> g_events_all;   // every thread's profiling events
 int g_live_servers = 0;
 thread_local uint32_t g_spin_limit = 0;
+thread_local int32_t g_group_stride = 0;   // workgroups per group of few-group sweeps (0: one XCD's)
 thread_local int32_t g_batch_ppt = 0;   // batch tile choice (0 = default or tuned)
 constexpr uint32_t kDefaultSpin = 1u << 22;
 // Waits that count four polls as one (spin_rows) compare with a 32-bit count:
@@ -619,6 +620,7 @@ int enqueue(DevState *st, const am_params *p, int64_t N, int32_t M, am_basis b, 
     sa.rep = rep;
     sa.n_rep = n_rep;
     sa.host_out = host_out;
+    sa.xcd_stride = g_group_stride;
     hipError_t e = hipSuccess;
     rc = launch_persistent(st, stream, noalloc_sched == nullptr,
                            [&]() { return amq::launch_sweep(sa, fp64, plan.wg, plan.ppt, stream); }, &e);
@@ -2230,6 +2232,8 @@ int am_debug_schedule(int32_t n_dates, int32_t *m, int32_t *dim, int32_t *left, 
     }
     return AM_OK;
 }
+
+void am_debug_set_group_stride(int32_t stride) { g_group_stride = stride > 1 ? stride : 0; }
 
 void am_debug_set_spin_limit(uint32_t spins) { g_spin_limit = spins < kMaxSpin ? spins : kMaxSpin; }
 

@@ -142,7 +142,7 @@ struct SweepArgs {
     double S0, K;
     uint32_t spin_limit;
     int32_t xcd_stride;       // > 1: every xcd_stride-th workgroup is a group; > 0: groups announce their XCD
-                              // (set by launch_sweep)
+                              // (set by launch_sweep; above 1 on entry: a test's stride)
     double *rep_out;          // randomised QMC: replicate prices [n_rep] or nullptr
     int32_t rep, n_rep;
     double *host_out;         // pinned host copy of the result (put_host_result), or nullptr

@@ -689,9 +689,10 @@ hipError_t launch_sweep(const SweepArgs &a, int fp64, int wg, int ppt, hipStream
     // measured 19 us slower per call, in the kernel's own event interval)
     // few groups of a register-resident tile: all on one XCD, where its compute
     // units hold one each; more of another tile are relayed, as dealt
-    const bool strided = G > 1 && spin && keep && dyn > 0 && G * kXcds <= (uint32_t)cus;
-    args.xcd_stride = strided ? (int)kXcds : !spin && !keep && G <= kFlatMaxGroups ? 1 : 0;
-    const uint32_t grid = strided ? G * kXcds : G;
+    const uint32_t stride = a.xcd_stride > 1 ? (uint32_t)a.xcd_stride : kXcds;   // (else a test's)
+    const bool strided = G > 1 && spin && keep && dyn > 0 && (uint64_t)G * stride <= (uint64_t)cus;
+    args.xcd_stride = strided ? (int)stride : !spin && !keep && G <= kFlatMaxGroups ? 1 : 0;
+    const uint32_t grid = strided ? G * stride : G;
     return hipLaunchKernel(f, dim3(grid), dim3((unsigned)wg), params, (unsigned)dyn, s);
 }
 

@@ -64,3 +64,29 @@ def test_few_and_more_groups(dtype, ppt, basis, degree, groups):
         finally:
             amq.am_debug_set_sweep_tile(0, 0)
     assert abs(got[512][0] - got[256][0]) <= 1e-10 and abs(got[512][1] - got[256][1]) <= 1e-10
+
+
+# groups dealt to several XCDs (stride 3: all eight in turn; 4: two): they find
+# that the others announced another one and exchange through memory.  The same
+# sums in the same order.
+@pytest.mark.parametrize("stride", [2, 3, 4, 7])
+@pytest.mark.parametrize("dtype,ppt,basis,degree,groups", [("fp64", 2, "monomial", 2, 2), ("fp64", 2, "monomial", 4, 17),
+                                                           ("fp64", 2, "monomial", 2, 32), ("fp64", 2, "laguerre", 3, 9),
+                                                           ("fp64", 2, "monomial", 5, 16), ("fp32", 4, "monomial", 2, 25)])
+def test_groups_on_several_xcds(stride, dtype, ppt, basis, degree, groups):
+    import torch
+    import paper_1205_0106_amd as amq
+    assert torch.cuda.is_available()
+    pr = amq.Pricer(0)
+    p, b = amq.make_params(S0=100.0, K=102.0, r=0.05, sigma=0.3, T=1.0, is_call=False), amq.make_basis(basis, degree)
+    N, M = groups * 512 * ppt - 3, 25
+    print(f"  exchange: stride={stride} {dtype} {basis} {degree} groups={groups}", flush=True)
+    amq.am_debug_set_sweep_tile(512, ppt)
+    try:
+        want = pr.price(p, N, M, b, dtype)
+        amq.am_debug_set_group_stride(stride)
+        for _ in range(3):
+            assert pr.price(p, N, M, b, dtype) == want
+    finally:
+        amq.am_debug_set_group_stride(0)
+        amq.am_debug_set_sweep_tile(0, 0)
