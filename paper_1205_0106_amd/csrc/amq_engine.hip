@@ -377,6 +377,8 @@ struct TileShape { int wg, ppt; };
 // call, 40 of 2 189; at 64000 181 and 194)
 constexpr double kOneXcdGain = 0.2;
 constexpr double kSlabOps = 40.0;   // lane operations per path and date of a slab tile's group
+// Monomials take 256-thread tiles only where 512-thread groups are forbidden (a
+// test's choice), and binary64 (256, 64) past the slab tile's paths.
 const TileShape kTiles32[] = {{512, 4}, {256, 4}, {512, 8}, {256, 16}, {512, 64}, {256, 64}, {512, 128}, {256, 128}};
 const TileShape kTiles64[] = {{512, 2}, {256, 2}, {512, 4}, {256, 8}, {512, 8}, {512, 32}, {256, 16}, {256, 64}};
 const int kNTiles32 = 8, kNTiles64 = 8;
@@ -431,11 +433,12 @@ int choose_plan(DevState *st, int64_t N, int fp64, int laguerre, int degree, Pla
             const int64_t ld = (N + amq::kLdAlign - 1) / amq::kLdAlign * amq::kLdAlign;
             if (ld % tile != 0) continue;
             int64_t G = (N + tile - 1) / tile;
-            // slab tiles (512 threads, 256 bytes of path values a thread) take
-            // one to four quarter tiles a group: as few as fill the CUs
-            const bool slab = !laguerre && wg == 512 && ppt * (fp64 ? 8 : 4) == 256;
-            int64_t paths_cu = 0;
-            if (slab) {
+            // slab tiles (256 bytes of path values a thread) of 512 threads take
+            // one to four quarter tiles a group, as few as fill the CUs; of 256
+            // threads (batches; here only without the wide ones) a whole one
+            const bool slab = !laguerre && ppt * (fp64 ? 8 : 4) == 256;
+            int64_t paths_cu = (G + st->num_cu - 1) / st->num_cu * tile;
+            if (slab && wg == 512) {
                 const int64_t U = (N + tile / 4 - 1) / (tile / 4);
                 const int64_t nu = (U + gmax - 1) / gmax;
                 if (nu > 4) continue;
