@@ -282,9 +282,6 @@ int get_state(DevState **out)
     std::unique_ptr<DevState> st(new DevState);
     st->dev = dev;
     HIP_TRY(hipDeviceGetAttribute(&st->num_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    int coop = 0;
-    HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-    if (!coop) return fail(AM_EDEVICE, "device %d does not support cooperative launches", dev);
     st->vdims = (int)amq_sobol_v32_dims < amq::kMaxDates ? (int)amq_sobol_v32_dims : amq::kMaxDates;
     const size_t vb = (size_t)st->vdims * 32 * sizeof(uint32_t);
     if (hipMalloc((void **)&st->d_V, vb) != hipSuccess)
@@ -934,10 +931,8 @@ struct BatchPlan {
     std::vector<int> order;                       // options by decreasing work
     std::vector<int64_t> ld, offS, offPV;
     std::vector<size_t> offDatec, offRec;
-    std::vector<int32_t> G, tile_base;
     size_t off_part = 0, off_res = 0, off_sync = 0, off_gsync = 0, off_desc = 0, off_tiles = 0,
            off_units = 0, total = 0;
-    int total_tiles = 0;
     int64_t total_blocks = 0, max_units = 0;
 };
 
@@ -954,16 +949,14 @@ int batch_plan(const am_option *opts, int32_t n, int32_t dtype, BatchPlan &P)
         return wa > wb;
     });
     P.ld.assign(n, 0); P.offS.assign(n, 0); P.offPV.assign(n, 0);
-    P.offDatec.assign(n, 0); P.offRec.assign(n, 0); P.G.assign(n, 0); P.tile_base.assign(n, 0);
+    P.offDatec.assign(n, 0); P.offRec.assign(n, 0);
     size_t o = 0;
-    int tiles = 0;
     for (int q = 0; q < n; ++q) {
         const int i = P.order[q];
         const int64_t ld = (opts[i].n_paths + kBatchTileAlign - 1) / kBatchTileAlign * kBatchTileAlign;
         P.ld[i] = ld;
         P.offS[i] = (int64_t)o;  o = align256(o + (size_t)opts[i].n_dates * ld * s);
         P.offPV[i] = (int64_t)o; o = align256(o + (size_t)ld * s);
-        P.tile_base[i] = tiles;
         P.total_blocks += ld / 64;
     }
     for (int q = 0; q < n; ++q) {
@@ -984,7 +977,6 @@ int batch_plan(const am_option *opts, int32_t n, int32_t dtype, BatchPlan &P)
     P.off_part = o;  o = align256(o + ((size_t)max_tiles + (size_t)n * amq::kMaxTeams) * 2 * amq::kMaxRowWords * 8);
     P.off_units = o; o = align256(o + (size_t)P.max_units * sizeof(amq::GenUnit));
     P.total = o;
-    (void)tiles;
     return AM_OK;
 }
 
