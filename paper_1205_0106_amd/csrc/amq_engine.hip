@@ -443,6 +443,11 @@ int choose_plan(DevState *st, int64_t N, int fp64, int laguerre, int degree, Pla
                 paths_cu = nu * (tile / 4);
             }
             if (G > gmax) continue;
+            // register-resident tiles with one group per CU: more sum over teams,
+            // and the larger tiles are faster then (degree 0, 1.5 10^6 paths x 50
+            // dates: 512 x 8 binary32 450 us per call, 512 x 64 401; binary64 529,
+            // 512 x 32 483)
+            if (small && !g_tile_wg && G > st->num_cu) continue;
             double t;
             if (pass == 0) {
                 t = 0.005 * (double)G + 0.0125 * sums * (double)ppt -

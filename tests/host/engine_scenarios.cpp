@@ -349,6 +349,23 @@ static void spin_limit()
     }
 }
 
+// However many groups of a register-resident tile a compute unit holds, a single
+// option takes one a unit at most, and every size has a tile.
+static void one_group_a_unit()
+{
+    DevState *st = nullptr;
+    CHECK(get_state(&st) == AM_OK);
+    fake::small_groups_per_cu = 2;
+    for (int fp64 : {0, 1})
+        for (int laguerre : {0, 1})
+            for (int degree : {0, 2, 6})
+                for (int64_t n = 1000; n < 4000000; n += n / 7) {
+                    Plan p{0, 0, 0};
+                    CHECK(choose_plan(st, n, fp64, laguerre, degree, &p) == AM_OK);
+                    if (p.wg == 512 && p.ppt <= 8) CHECK(p.G <= fake::kCus);
+                }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
@@ -359,6 +376,7 @@ int main(int argc, char **argv)
         {"segments", segments},
         {"tile_table", tile_table},
         {"spin_limit", spin_limit},
+        {"one_group_a_unit", one_group_a_unit},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {

@@ -79,7 +79,7 @@ inline hipError_t symbol_address(void **p, const void *) { return alloc(p, 1); }
 std::function<void(const amq::BatchOpt *, const int32_t *, const amq::BatchGlobal &, int grid, int mode)> on_sweep_batch;
 std::function<void(const amq::GenUnit *, int n, int max_seg_len)> on_generate_batch;
 std::function<void(const amq::SweepArgs &)> on_sweep;
-int batch_groups_per_cu = 2, batch_sure_per_cu = 1;
+int small_groups_per_cu = 1, batch_groups_per_cu = 2, batch_sure_per_cu = 1;
 
 }  // namespace fake
 
@@ -100,7 +100,7 @@ hipError_t launch_sweep(const SweepArgs &a, int, int, int, hipStream_t s)
     if (fake::on_sweep) fake::on_sweep(a);
     return hipSuccess;
 }
-int sweep_blocks_per_cu(int, int, int wg, int ppt, int) { return wg == 512 || ppt > 16 ? 1 : 2; }
+int sweep_blocks_per_cu(int, int, int wg, int ppt, int) { return wg == 512 && ppt > 8 ? 1 : fake::small_groups_per_cu; }
 hipError_t launch_paper(const PaperArgs &, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_generate_batch(const BatchOpt *, const GenUnit *u, int n, const uint32_t *, uint32_t *gsync, int max_seg_len,
                                  int, bool, hipStream_t)
