@@ -248,8 +248,11 @@ size_t am_batch_workspace_bytes(const am_option *opts, int32_t n_opts, am_basis 
  * counts overlap on the device.  Each option's result depends only on its own
  * data (fixed-order reductions): the same alone and in any mix.  Under
  * AM_FP32_BULK, options below AM_FP32_MIN_PATHS paths form a second
- * sub-batch stored in binary64 (a second generation and sweep launch on the
- * stream; am_batch_workspace_bytes covers both).  h_out (2 * n_opts
+ * sub-batch stored in binary64 (with a generation launch of its own; on
+ * monomials with the default tiles both share the sweep, else a second one
+ * follows on the stream; am_batch_workspace_bytes covers both).  If a device-side
+ * wait runs out the call fails with AM_ETIMEOUT and h_out may hold values of
+ * options that were not priced.  h_out (2 * n_opts
  * doubles, or NULL to return after enqueueing) receives price and std_err
  * per option in the caller's order.  Fails with AM_EDIM if one option needs
  * more tiles than the device holds resident.  An option of more tiles than

@@ -345,7 +345,7 @@ def am_batch_workspace_bytes(opts, basis: am_basis, dtype) -> int:
 
 
 def am_price_batch(opts, basis: am_basis, dtype, workspace, stream=None, wait: bool = True):
-    """Price a batch (am_option array) in two launches; returns an [n][2]
+    """Price a batch (am_option array) in one persistent sweep; returns an [n][2]
     numpy array of (price, std_err) or None when wait=False."""
     import numpy as np
     import torch

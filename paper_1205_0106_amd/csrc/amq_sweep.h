@@ -1648,7 +1648,7 @@ __device__ __forceinline__ bool batch_tile(const BatchOpt &o, int t, int queues,
     a.spin_limit = spin_limit;
     const uint32_t G = (uint32_t)o.G;
     const bool shared = spins_on_rows<row_words(D)>(G) || (!SweepShape<T, PPT>::KEEP && G <= kFlatMaxGroups);
-    a.xcd_stride = queues > 1 && shared ? 1 : 0;   // an option's groups mostly share an XCD
+    a.xcd_stride = queues > 1 && shared ? 1 : 0;   // a queue's groups are dealt to one XCD
     a.rep_out = nullptr; a.rep = 0; a.n_rep = 0;
     a.host_out = nullptr;
     const uint32_t gid = (uint32_t)(t - o.tile_base);

@@ -275,7 +275,7 @@ __device__ void reduce_partials(const double *part, uint32_t G, double *tot, dou
 // replaced by epoch & 3 (a change of at most 3 units in the last place, the
 // same in every run).  A reader reads rows until every word carries this
 // epoch's tag (no store needs to drain before another), then adds them in a
-// fixed order.  Three forms by group count:
+// fixed order.  Forms by group count and tile:
 //  - few groups (spins_on_rows): the first wave of every group reads all rows;
 //  - up to kFlatMaxGroups, in tiles with work to do behind the exchange
 //    (register-resident): flat.  Thread 0 bumps its team's arrival
