@@ -255,10 +255,9 @@ size_t am_batch_workspace_bytes(const am_option *opts, int32_t n_opts, am_basis 
  * options that were not priced.  h_out (2 * n_opts
  * doubles, or NULL to return after enqueueing) receives price and std_err
  * per option in the caller's order.  Fails with AM_EDIM if one option needs
- * more tiles than the device holds resident.  An option of more tiles than
- * compute units (binary32 monomials from 2^22 paths, binary64 from 2^21) needs
- * two workgroups on a unit: other work on the device while the sweep starts can
- * keep them apart, and the call then fails with AM_ETIMEOUT. */
+ * more tiles than the device holds resident.  An option that alone has more
+ * tiles than the device compute units (monomials, default tile: binary32 from
+ * 2^22 paths, binary64 from 2^21) is swept by itself after the others. */
 int am_price_batch(const am_option *opts, int32_t n_opts, am_basis basis, int32_t dtype,
                    void *d_workspace, size_t ws_bytes, void *hip_stream, double *h_out);
 

@@ -1268,6 +1268,35 @@ int generate_part(DevState *st, const BatchPart &B, const std::vector<int32_t> &
 constexpr int kClaimWord = 4;   // the batch's shared words: [1] error, [4..11] claim counters
 static_assert(kClaimWord + amq::kClaimQueues <= 16, "batch words");
 
+// The sweep of one option of a batch that alone fills the device: the
+// single-option slab tile, 512 threads and one group a compute unit, which finds
+// room whatever else runs; two of the batch's 66 KB groups a unit may not (see
+// kAnyPlacement).  Its groups divide the option's units as choose_plan has them.
+hipError_t sweep_wide(const amq::BatchOpt &o, bool fp64, int degree, int num_cu, uint32_t *err, uint32_t spin_limit,
+                      hipStream_t stream)
+{
+    const int ppt = default_batch_ppt(fp64 ? AM_FP64 : AM_FP32_BULK);
+    const int64_t unit = 512 * ppt / 4, U = (o.N + unit - 1) / unit, nu = (U + num_cu - 1) / num_cu;
+    if (nu > 4) return hipErrorInvalidValue;
+    amq::SweepArgs a;
+    memset(&a, 0, sizeof a);
+    a.S = o.S;
+    a.pv_out = o.pv;
+    a.rows = o.rows;
+    a.rec = o.rec;
+    a.result = o.result;
+    a.sync = o.sync;
+    a.err = err;
+    a.datec = o.datec;
+    a.N = o.N; a.ld = o.ld;
+    a.M = o.M; a.G = (int32_t)((U + nu - 1) / nu);
+    a.is_call = o.is_call; a.allow_exercise = o.allow_exercise;
+    a.degree = degree;
+    a.S0 = o.S0; a.K = o.K;
+    a.spin_limit = spin_limit;
+    return amq::launch_sweep(a, fp64, 512, ppt, stream);
+}
+
 // Enqueue the parts h0 .. h1 of a split batch (their generations and one
 // persistent sweep) on `stream`: one part with its own tile, or both (mode
 // kMixed) with the default ones.  grid_cap
@@ -1317,10 +1346,18 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
     // they hold the largest one.  (A book that claims
     // again and again is bound by its total work, and the queues' uneven ends
     // cost more: 1024 options 41.4 ms with queues, 40.8 without.)
+    // A slab tile's option of more tiles than compute units would need two groups
+    // a unit: it is swept by itself (sweep_wide).
+    if (max_G > capacity)
+        return fail(AM_EDIM, "an option needs %d tiles but only %d workgroups are resident", max_G, capacity);
     struct Item { int h, i; const am_option *o; };
-    std::vector<Item> items;
+    std::vector<Item> items, wide;
     for (int h = h0; h <= h1; ++h)
-        for (int i : S.P[h].order) items.push_back({h, i, &S.opts[h][i]});
+        for (int i : S.P[h].order) {
+            const bool w = !laguerre && ppt[h] == default_batch_ppt(S.storage[h]) && B[h].desc[i].G > st->num_cu;
+            (w ? wide : items).push_back({h, i, &S.opts[h][i]});
+            if (w) tiles -= B[h].desc[i].G;
+        }
     std::stable_sort(items.begin(), items.end(), [](const Item &x, const Item &y) {
         return x.o->n_dates != y.o->n_dates ? x.o->n_dates > y.o->n_dates : x.o->n_paths > y.o->n_paths;
     });
@@ -1342,8 +1379,6 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
     const int nq = queued ? amq::kClaimQueues : 1;
     if (!queued) std::fill(queue_of.begin(), queue_of.end(), 0);
     const int grid = queued ? amq::kClaimQueues * most : tiles < capacity ? tiles : capacity;
-    if (max_G > grid)
-        return fail(AM_EDIM, "an option needs %d tiles but only %d workgroups are resident", max_G, grid);
     std::vector<int32_t> tile_opt;
     tile_opt.reserve(tiles);
     int32_t q_off[amq::kClaimQueues + 1] = {0};
@@ -1394,15 +1429,28 @@ int enqueue_parts(DevState *st, const SplitBatch &S, int h0, int h1, int mode, a
                                        (const int32_t *)(ws + S.off[ht] + S.P[ht].off_tiles), g, grid, mode, ppt[h0],
                                        basis.degree, alone && grid <= st->num_cu, stream);
     };
-    hipError_t e = hipSuccess;
-    if (alone) {
-        const int rc = launch_persistent(st, stream, true, launch, &e);
+    const auto ordered = [&](auto go) -> int {
+        hipError_t e = hipSuccess;
+        if (alone) {
+            const int rc = launch_persistent(st, stream, true, go, &e);
+            if (rc) return rc;
+        } else {
+            e = go();
+        }
+        if (e != hipSuccess)
+            return fail(AM_EDEVICE, "batch sweep launch (grid %d, ppt %d) failed: %s", grid, ppt[h0], hipGetErrorString(e));
+        return AM_OK;
+    };
+    if (!items.empty()) {
+        const int rc = ordered(launch);
         if (rc) return rc;
-    } else {
-        e = launch();
     }
-    if (e != hipSuccess)
-        return fail(AM_EDEVICE, "batch sweep launch (grid %d, ppt %d) failed: %s", grid, ppt[h0], hipGetErrorString(e));
+    for (const Item &w : wide) {
+        const int rc = ordered([&]() {
+            return sweep_wide(B[w.h].desc[w.i], S.storage[w.h] == AM_FP64, basis.degree, st->num_cu, g.err, g.spin_limit, stream);
+        });
+        if (rc) return rc;
+    }
     if (pr) HIP_TRY(hipEventRecord(pr->e[2], stream));
     return AM_OK;
 }

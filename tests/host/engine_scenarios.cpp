@@ -6,6 +6,8 @@
 
 #include <set>
 
+#include <sys/mman.h>
+
 static int g_failed = 0;
 #define CHECK(c)                                                                  \
     do {                                                                          \
@@ -199,8 +201,6 @@ static void claim_queues()
         for (int dtype : {AM_FP64, AM_FP32_BULK}) {
             std::vector<am_option> o;
             for (int i = 0; i < s.n; ++i) o.push_back(option(s.n_paths + (int64_t)s.step * i, s.n_dates + i % 5));
-            const int64_t tile = 256 * (dtype == AM_FP64 ? 32 : 64);
-            if ((s.n_paths + tile - 1) / tile > fake::kCus) continue;   // (more tiles than units: needs what it needs)
             const size_t nb = am_batch_workspace_bytes(o.data(), s.n, b, dtype);
             void *w = nullptr;
             CHECK(nb > 0 && fake::alloc(&w, nb) == hipSuccess);
@@ -234,14 +234,18 @@ static void served_share()
             am_server *sv = nullptr;
             std::mutex mu;
             std::map<int, bool> alone;   // by tiles
-            fake::on_sweep_batch = [&](const amq::BatchOpt *o, const int32_t *, const amq::BatchGlobal &, int grid, int) {
-                CHECK(grid >= o[0].G);
+            const auto note = [&](int tiles) {
                 for (Slot &sl : sv->slots)
-                    if (sl.reqs.size() == 1 && !sl.busy && (sl.reqs[0].opt.n_paths + tile - 1) / tile == o[0].G) {
+                    if (sl.reqs.size() == 1 && !sl.busy && (sl.reqs[0].opt.n_paths + tile - 1) / tile == tiles) {
                         std::lock_guard<std::mutex> lk(mu);
-                        alone[o[0].G] = sl.exclusive;
+                        alone[tiles] = sl.exclusive;
                     }
             };
+            fake::on_sweep_batch = [&](const amq::BatchOpt *o, const int32_t *, const amq::BatchGlobal &, int grid, int) {
+                CHECK(grid >= o[0].G);
+                note(o[0].G);
+            };
+            fake::on_sweep = [&](const amq::SweepArgs &a) { note((int)((a.N + tile - 1) / tile)); };
             CHECK(am_server_create(&cfg, &sv) == AM_OK);
             const int sizes[] = {1, share - 1, share, share + 1, 2 * fake::kCus};
             int id = 0;
@@ -366,6 +370,54 @@ static void one_group_a_unit()
                 }
 }
 
+// Options of more tiles than compute units leave the book's tile list and are swept
+// by themselves, with a group a unit at most and on the book's error word; one
+// that the device does not hold is refused.
+static void wide_options()
+{
+    const am_basis b{AM_BASIS_MONOMIAL, 2};
+    for (int dtype : {AM_FP64, AM_FP32_BULK}) {
+        const int64_t tile = 256 * (dtype == AM_FP64 ? 32 : 64), top = 2 * fake::kCus * tile;
+        const am_option sizes[] = {option(256 * tile, 2), option(256 * tile + 1, 2), option(30000, 3), option(top, 2), option(700, 4)};
+        for (int mask = 1; mask < 32; ++mask) {
+            std::vector<am_option> o;
+            std::set<int64_t> expect, seen;
+            int listed = 0;
+            for (int i = 0; i < 5; ++i) {
+                if (!(mask >> i & 1)) continue;
+                o.push_back(sizes[i]);
+                if (i == 1 || i == 3) expect.insert(sizes[i].n_paths);
+                else ++listed;
+            }
+            uint32_t *err = nullptr;
+            int books = 0;
+            fake::on_sweep_batch = [&](const amq::BatchOpt *o32, const int32_t *tile_opt, const amq::BatchGlobal &g, int grid, int) {
+                ++books;
+                err = g.err;
+                std::set<int32_t> in(tile_opt, tile_opt + g.total_tiles);
+                listed -= (int)in.size();
+                for (int32_t t : in) CHECK((t < 0 ? g.opts64[t & 0x7FFFFFFF] : o32[t]).G <= fake::kCus);
+                CHECK(finishes(g, tile_opt, grid, fake::kCus));
+            };
+            fake::on_sweep = [&](const amq::SweepArgs &a) {
+                seen.insert(a.N);
+                CHECK(a.G <= fake::kCus && a.G > fake::kCus / 2);
+                CHECK((int64_t)a.G * 2 * tile >= a.N);   // (a 512-thread tile has two of the batch's)
+                CHECK(!books || a.err == err);
+            };
+            const size_t nb = am_batch_workspace_bytes(o.data(), (int32_t)o.size(), b, dtype);
+            void *w = mmap(nullptr, nb, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+            CHECK(w != MAP_FAILED);
+            CHECK(am_price_batch(o.data(), (int32_t)o.size(), b, dtype, w, nb, (hipStream_t)0xA0, nullptr) == AM_OK);
+            munmap(w, nb);
+            CHECK(seen == expect && listed == 0);
+        }
+        const am_option too_big = option(top + 1, 2);
+        const size_t nb = am_batch_workspace_bytes(&too_big, 1, b, dtype);
+        CHECK(am_price_batch(&too_big, 1, b, dtype, (void *)256, nb, (hipStream_t)0xA0, nullptr) == AM_EDIM);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
@@ -377,6 +429,7 @@ int main(int argc, char **argv)
         {"tile_table", tile_table},
         {"spin_limit", spin_limit},
         {"one_group_a_unit", one_group_a_unit},
+        {"wide_options", wide_options},
     };
     const auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) {

@@ -26,7 +26,7 @@ def scenarios(tmp_path_factory):
 
 @pytest.mark.parametrize("name", ["mixed_timeout", "order_across_streams", "claim_queues",
                                   "served_share", "segments", "tile_table", "spin_limit",
-                                  "one_group_a_unit"])
+                                  "one_group_a_unit", "wide_options"])
 def test_scenario(scenarios, name):
     r = subprocess.run([scenarios, name], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "passed" in r.stdout, r.stdout + r.stderr

@@ -213,3 +213,35 @@ def test_batch_long_date_counts(amq, orc, pricer, dtype):
         assert abs(got[i, 0] - want.price) <= TOL[dtype], (i, got[i], want.price)
     alone = pricer.price_batch(amq.make_options([specs[3]]), b, dtype)
     assert alone[0, 0] == got[3, 0] and alone[0, 1] == got[3, 1]
+
+
+# an option of more tiles than the device has compute units is swept by itself,
+# after the others: the same alone, in a book, in a book of both storage types
+# and replayed, and within rounding of the single option (1e-16 relative sums,
+# condition below 1e4, price of order 10)
+@pytest.mark.parametrize("dtype,wide", [("fp32", (1 << 22) + 1), ("fp32", 6000000), ("fp64", (1 << 21) + 1), ("fp64", 1 << 22)])
+def test_batch_option_of_more_tiles_than_units(amq, dtype, wide):
+    import torch
+    pr = amq.Pricer(0)
+    kw = dict(S0=100.0, r=0.04, sigma=0.3, T=1.0)
+    big = dict(kw, K=103.0, is_call=False, n_paths=wide, n_dates=4)
+    rest = [dict(kw, K=95.0, is_call=True, n_paths=70001, n_dates=5), dict(kw, K=99.0, is_call=False, n_paths=3001, n_dates=3)]
+    b = amq.make_basis("monomial", 2)
+    print(f"  wide option: {dtype} N={wide}", flush=True)
+    alone = np.asarray(pr.price_batch(amq.make_options([big]), b, dtype))
+    few = np.asarray(pr.price_batch(amq.make_options(rest), b, dtype))
+    opts = amq.make_options([rest[0], big, rest[1]])
+    mix = np.asarray(pr.price_batch(opts, b, dtype))
+    assert np.array_equal(mix[1], alone[0]) and np.array_equal(mix[[0, 2]], few)
+    p = amq.make_params(**kw, K=103.0, is_call=False)
+    single = amq.Pricer(0).price(p, wide, 4, b, dtype)
+    assert abs(single[0] - alone[0, 0]) <= 1e-9 and abs(single[1] - alone[0, 1]) <= 1e-9
+    ws = torch.empty(amq.am_batch_workspace_bytes(opts, b, dtype), dtype=torch.uint8, device="cuda")
+    g = amq.BatchGraph(opts, b, dtype, ws)
+    s, other = torch.cuda.Stream(), amq.Pricer(0, stream=torch.cuda.Stream())
+    torch.cuda.synchronize()
+    for _ in range(3):
+        g.launch(s)
+        other.price(p, 1 << 20, 6, b, dtype, wait=False)   # its generation runs beside the replay's sweeps
+        assert np.array_equal(g.results(), mix)
+    g.close()
